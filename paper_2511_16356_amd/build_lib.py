@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkc_mi355x.so")
-SOURCES = ["kc_device.hip", "kc_host.cpp", "kc_static.hip", "kc_batch.cpp", "kc_tune.cpp"]
+SOURCES = ["kc_device.hip", "kc_frontier.hip", "kc_host.cpp", "kc_static.hip", "kc_batch.cpp", "kc_tune.cpp"]
 # memory-ceiling probes used by the benchmark's roofline calibration
 PROBE_LIB = os.path.join(HERE, "libkc_probe.so")
 PROBE_SOURCES = ["kc_probe.hip"]
@@ -17,6 +17,9 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed FP32 instructions (v_pk_add/mul/fma_f32): the library is built without them
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # LDS counters are added to by few lanes: a scan over the wavefront before each add costs
+    # more than the adds (a round of the frontier sampler's walks: 5.6k against 4.1k cycles)
+    "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
     "-Wall", "-Wno-unused-function",
 ]
 

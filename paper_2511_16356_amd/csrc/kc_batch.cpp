@@ -44,6 +44,12 @@ void batch_free(kc_batch *b) {
     delete b;
 }
 
+// Resident workgroups per CU of the batch's kernel.
+int blocks_per_cu(const kc::BatchArgs &a, int chains) {
+    if (!kc::batch_is_frontier(a)) return kc::batch_blocks_per_cu(chains);
+    return kc::frontier_batch_blocks_per_cu(a);
+}
+
 template <typename T>
 hipError_t alloc_n(T **p, size_t count) {
     return hipMalloc(reinterpret_cast<void **>(p), std::max<size_t>(count, 1) * sizeof(T));
@@ -92,12 +98,13 @@ kc_status kc_batch_create(kc_graph *const *graphs, int32_t k, const uint64_t *se
         job.walkers = rp.walkers;
         job.traversal = rp.traversal;
         job.lean = rp.lean;
+        job.route = rp.route;
     }
     // samples in flight: the first graph's slots option (else the kernel's resident
     // workgroups), within its memory budget for slots sized for the largest graph
     const size_t n = (size_t)max_n, ch = (size_t)kc::sampler_chains();
     const int64_t per_slot = kc::state_bytes(max_n) + (int64_t)(20 * ch + 16 * n + 8 * (size_t)max_fen);
-    int want = graphs[0]->slots_opt > 0 ? graphs[0]->slots_opt : default_slots(graphs[0], true);
+    int want = graphs[0]->slots_opt > 0 ? graphs[0]->slots_opt : resident_slots(blocks_per_cu(a, b->chains));
     want = (int)std::min<int64_t>(want, total);
     size_t free_b = 0, total_b = 0;
     hipError_t e = hipMemGetInfo(&free_b, &total_b);

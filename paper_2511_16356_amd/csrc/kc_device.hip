@@ -29,108 +29,13 @@
 // relaxed atomics (L2-coherent on gfx950) ordered by workgroup fences; every
 // lane of a sample is in the same wavefront.
 
-#include "kc_internal.h"
+#include "kc_tree.h"
 
 namespace kc {
 namespace {
 
-constexpr int WAVE = 64;
-
-// ------------------------------------------------------------ memory helpers
-
-template <typename T>
-__device__ __forceinline__ T aload(const T *p) {
-    return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
-__device__ __forceinline__ void astore(T *p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
-__device__ __forceinline__ T afetch_add(T *p, T v) {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
-__device__ __forceinline__ T afetch_and(T *p, T v) {
-    return __hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
-__device__ __forceinline__ T afetch_xor(T *p, T v) {
-    return __hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
-__device__ __forceinline__ T acas(T *p, T expected, T desired) {
-    __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_WORKGROUP);
-    return expected;  // value found at *p
-}
-__device__ __forceinline__ void fence_wg() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
-
-// ------------------------------------------------------------- wave helpers
-
-__device__ __forceinline__ int rank_in(uint64_t mask) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-__device__ __forceinline__ int64_t wave_sum(int64_t v) {
-    for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-    for (int o = WAVE / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    return v;
-}
-
-__device__ void report_error(int32_t *ctl, int code, int idx) {
-    if (threadIdx.x == 0) {
-        int expected = 0;
-        if (__hip_atomic_compare_exchange_strong(&ctl[1], &expected, code, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            __hip_atomic_store(&ctl[2], idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// ------------------------------------------------------------------ arrows
-
-// Philox4x32-10 block function (Salmon, Moraes, Dror, Shaw, SC'11): ten
-// rounds of two 32x32->64 multiplies with the Weyl key schedule.  Counter
-// (k, v, s_lo, s_hi), key (seed_lo, seed_hi).  The neighbour slot is the
-// high word of x * deg with x = out0 | out1 << 32, i.e. floor(x deg / 2^64),
-// computed from two 32x32 products.
-struct Bits {
-    uint32_t lo, hi;
-};
-__device__ __forceinline__ Bits philox_bits(uint64_t seed, uint64_t s, uint32_t v, uint32_t k) {
-    uint32_t x0 = k, x1 = v, x2 = (uint32_t)s, x3 = (uint32_t)(s >> 32);
-    uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
-#pragma unroll
-    for (int round = 0; round < 10; ++round) {
-        // one full 32x32->64 product each (a single v_mad_u64_u32, not mul_lo + mul_hi)
-        const uint64_t a = (uint64_t)0xD2511F53u * x0;
-        const uint64_t b = (uint64_t)0xCD9E8D57u * x2;
-        const uint32_t y0 = (uint32_t)(b >> 32) ^ x1 ^ key0;
-        const uint32_t y2 = (uint32_t)(a >> 32) ^ x3 ^ key1;
-        x0 = y0; x1 = (uint32_t)b; x2 = y2; x3 = (uint32_t)a;
-        key0 += 0x9E3779B9u;
-        key1 += 0xBB67AE85u;
-    }
-    return Bits{x0, x1};
-}
-__device__ __forceinline__ uint32_t slot_of(Bits x, uint32_t deg) {
-    const uint64_t lowprod = (uint64_t)x.lo * deg;
-    const uint64_t highprod = (uint64_t)x.hi * deg + (lowprod >> 32);
-    return (uint32_t)(highprod >> 32);
-}
-__device__ __forceinline__ uint32_t arrow_slot(uint64_t seed, uint64_t s, uint32_t v, uint32_t k,
-                                               uint32_t deg) {
-    return slot_of(philox_bits(seed, s, v, k), deg);
-}
-
 // ------------------------------------------------------------ sampler state
 
-// Neighbours kept inline in a vertex's 32-byte graph record (see GraphDev::vrec).
-constexpr int VREC_INLINE = 6;
-//
 // Two 8-byte words per (sample, vertex), in two arrays, so that the claim
 // (an atomic on the tag word) and the read of the arrow word go to different
 // cache lines and overlap:
@@ -702,654 +607,54 @@ __device__ int64_t sample_tree(const GraphDev &g, const SamplerWS &ws, SamplerSh
     return wave_sum(mysteps);
 }
 
-// --------------------------------------------------------- tree traversal
-
-// The numbered tree: one 16-byte record per vertex, two 8-byte words, so that
-// every step of the numbering touches one line per vertex it visits:
-//   rec[2v]     pending children << 44 | volume while the volumes are summed
-//               (starting at deg(v)); tin(v) + vol(v) once the numbering is done
-//   rec[2v + 1] parent (low half, -1 at the root) | deg(v) (high half) until the
-//               top-down step, then parent | tin(v)
-struct SlotPtrs {
-    SamplerWS ws;
-    uint64_t *rec;
-    int4 *ord;             // finished vertices {v, parent, vol, offset in the parent's interval} in
-                           // completion order; the leaves {v, parent, deg, 0} wait at its end
-    int32_t *grp;
-    int64_t *fen;
-};
-
-__device__ __forceinline__ int32_t rec_parent(const uint64_t *rec, int v) {
-    return (int32_t)(uint32_t)aload(&rec[2 * (size_t)v + 1]);
-}
-// The numbering of a vertex once it is complete: tin, vol and tree parent.
-struct TNum {
-    uint32_t tin, vol;
-    int32_t par;
-};
-__device__ __forceinline__ TNum rec_num(const uint64_t *rec, int v) {
-    const uint64_t w = aload(&rec[2 * (size_t)v]), h = aload(&rec[2 * (size_t)v + 1]);
-    TNum t;
-    t.tin = (uint32_t)(h >> 32);
-    t.vol = (uint32_t)(w - (h >> 32));
-    t.par = (int32_t)(uint32_t)h;
-    return t;
-}
-__device__ __forceinline__ uint32_t rec_tin(const uint64_t *rec, int v) {
-    return (uint32_t)(aload(&rec[2 * (size_t)v + 1]) >> 32);
-}
-
-// Vertices each lane keeps in flight in the tree numbering: the memory
-// operations of one step are issued together, so a wavefront has this many
-// times as many requests outstanding as it has lanes.  The streaming passes
-// take twice as many.
-constexpr int NB = 4;
-constexpr int NBS = 8;
-
-constexpr uint64_t PEND_ONE = 1ull << 44;
-constexpr uint64_t VOL_MASK = PEND_ONE - 1;
-
-__device__ __forceinline__ uint32_t degree(const GraphDev &g, int v) {
-    return (uint32_t)(g.off[v + 1] - g.off[v]);
-}
-
-// Fenwick tree over positions 0..2m storing a difference array.
-__device__ __forceinline__ void fen_point_add(int64_t *fen, int64_t len, int64_t pos, int64_t val) {
-    if (pos < 0) pos = 0;
-    for (int64_t i = pos + 1; i < len; i += i & (-i)) afetch_add(&fen[i], val);
-}
-__device__ __forceinline__ void fen_range_add(int64_t *fen, int64_t len, int64_t lo, int64_t hi,
-                                              int64_t val) {
-    if (val == 0 || hi <= lo) return;
-    fen_point_add(fen, len, lo, val);
-    fen_point_add(fen, len, hi, -val);
-}
-__device__ __forceinline__ int64_t fen_prefix(const int64_t *fen, int64_t len, int64_t pos) {
-    int64_t i = pos + 1;
-    if (i >= len) i = len - 1;
-    int64_t sum = 0;
-    for (; i > 0; i -= i & (-i)) sum += aload(&fen[i]);
-    return sum;
-}
-
-// The two contributions attached to tau0 vertex x (Theorem 3.4), as
-// ranges of tin with a weight, active for every u in Sub(tau0, x):
-//   forward : p(x) = p0(x)          -> +(2m - vol(x)) on Sub(tau, x)
-//   reverse : p(p0(x)) = x, p0(x)!=r -> -(2m - vol(p0(x))) on Sub(tau, p0(x))
-struct Items {
-    uint32_t flo, fhi, rlo, rhi;
-    int64_t fw, rw;
-};
-__device__ __forceinline__ Items items_of(const GraphDev &g, const uint64_t *rec, int x) {
-    Items it{0u, 0u, 0u, 0u, 0, 0};
-    if (x == g.root) return it;
-    const TNum nx = rec_num(rec, x);
-    const int z = g.p0[x];
-    if (nx.par == z) {
-        it.flo = nx.tin; it.fhi = nx.tin + nx.vol; it.fw = g.two_m - (int64_t)nx.vol;
-    }
-    if (z != g.root) {
-        const TNum nz = rec_num(rec, z);
-        if (nz.par == x) {
-            it.rlo = nz.tin; it.rhi = nz.tin + nz.vol; it.rw = (int64_t)nz.vol - g.two_m;
-        }
-    }
-    return it;
-}
-__device__ __forceinline__ int64_t items_at(const Items &it, uint32_t t) {
-    int64_t s = 0;
-    if (it.flo <= t && t < it.fhi) s += it.fw;
-    if (it.rlo <= t && t < it.rhi) s += it.rw;
-    return s;
-}
-
-// Volumes and the volume-weighted preorder of the tree whose parents are in
-// rec (rec[2v] = deg(v), rec[2v+1] = parent | deg(v) << 32 already).  Returns
-// false if the parents do not form a tree rooted at r.
-//
-// Bottom-up: each lane carries up to NB finished vertices; a carrier pushes
-// its vertex's volume into the parent's word with one atomic, and the last
-// child to arrive carries the parent on in the next round.  The volume part
-// the atomic returns is the parent's degree plus the volumes of the siblings
-// that arrived before: the vertex's offset in its parent's interval.  Every
-// round's finished vertices form a completion group.  Top-down: the groups in
-// reverse order (a parent always finishes in a later group than its
-// children); a vertex's tin is its parent's tin plus its offset.
-__device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp) {
-    const int lane = threadIdx.x;
-    const int n = g.n;
-    // one PEND_ONE per child in the parent's word
-    for (int b = 0; b < n; b += WAVE * NBS) {
-        int32_t p[NBS];
-#pragma unroll
-        for (int k = 0; k < NBS; ++k) {
-            const int v = b + k * WAVE + lane;
-            p[k] = v < n ? rec_parent(sp.rec, v) : -1;
-        }
-#pragma unroll
-        for (int k = 0; k < NBS; ++k)
-            if (p[k] >= 0) afetch_add(&sp.rec[2 * (size_t)p[k]], PEND_ONE);
-    }
-    fence_wg();
-    // leaves {v, parent, deg, 0}: leaf number j at ord[n - 1 - j]
-    int L = 0;
-    for (int b = 0; b < n; b += WAVE * NBS) {
-        uint64_t w[NBS], h[NBS];
-#pragma unroll
-        for (int k = 0; k < NBS; ++k) {
-            const int v = b + k * WAVE + lane;
-            w[k] = v < n ? aload(&sp.rec[2 * (size_t)v]) : PEND_ONE;  // past the end: not a leaf
-            h[k] = v < n ? aload(&sp.rec[2 * (size_t)v + 1]) : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < NBS; ++k) {
-            const bool leaf = (w[k] >> 44) == 0;
-            const uint64_t m = __ballot(leaf);
-            if (leaf)
-                sp.ord[n - 1 - (L + rank_in(m))] = make_int4(b + k * WAVE + lane, (int32_t)(uint32_t)h[k],
-                                                             (int)(w[k] & VOL_MASK), 0);
-            L += __popcll(m);
-        }
-    }
-    fence_wg();
-    // bottom-up.  Leaves are taken from the low end of their block, ord[n-L ..]:
-    // the finished entries written at ord[0 .. nord) never reach an untaken leaf,
-    // since nord + (leaves not yet taken) <= n.
-    int cv[NB], cp[NB];
-    uint64_t cval[NB];
-#pragma unroll
-    for (int k = 0; k < NB; ++k) { cv[k] = -1; cp[k] = -1; cval[k] = 0; }
-    int li = 0, nord = 0, ngrp = 0;
-    while (true) {
-        if (li < L) {
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const uint64_t freem = __ballot(cv[k] < 0);
-                const int j = li + rank_in(freem);
-                if (cv[k] < 0 && j < L) {
-                    const int4 e = sp.ord[n - L + j];
-                    cv[k] = e.x;
-                    cp[k] = e.y;
-                    cval[k] = (uint64_t)(uint32_t)e.z;
-                }
-                li = min(L, li + (int)__popcll(freem));
-            }
-        }
-        uint64_t busy = 0;
-#pragma unroll
-        for (int k = 0; k < NB; ++k) busy |= __ballot(cv[k] >= 0);
-        if (busy == 0ull) break;
-        if (lane == 0) astore(&sp.grp[ngrp], nord);
-        ngrp++;
-        uint64_t old[NB];
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            old[k] = 0;
-            if (cv[k] >= 0 && cp[k] >= 0) old[k] = afetch_add(&sp.rec[2 * (size_t)cp[k]], cval[k] - PEND_ONE);
-        }
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            const uint64_t bm = __ballot(cv[k] >= 0);
-            if (cv[k] >= 0)
-                sp.ord[nord + rank_in(bm)] = make_int4(cv[k], cp[k], (int)cval[k], (int)(uint32_t)(old[k] & VOL_MASK));
-            nord += __popcll(bm);
-        }
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            const bool last = cv[k] >= 0 && cp[k] >= 0 && (old[k] >> 44) == 1;
-            cv[k] = last ? cp[k] : -1;
-            if (last) cval[k] = (old[k] & VOL_MASK) + cval[k];
-        }
-        // the new carrier's parent, from the record line the atomic just used
-#pragma unroll
-        for (int k = 0; k < NB; ++k)
-            if (cv[k] >= 0) cp[k] = rec_parent(sp.rec, cv[k]);
-        if (nord > n) break;  // more entries than vertices: not a tree
-    }
-    if (lane == 0) astore(&sp.grp[ngrp], nord);
-    fence_wg();
-    if (nord != n) return false;
-    // top-down; the group boundaries are read 64 at a time
-    for (int g0 = ngrp - 1; g0 >= 0; g0 -= WAVE) {
-        const int bnd = g0 - lane >= 0 ? aload(&sp.grp[g0 - lane]) : 0;
-        const int nb = min(WAVE, g0 + 1);
-        int hi = aload(&sp.grp[g0 + 1]);
-        for (int t = 0; t < nb; ++t) {
-            const int lo = __shfl(bnd, t);
-            for (int i0 = lo; i0 < hi; i0 += WAVE * NB) {
-                int4 e[NB];
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const int i = i0 + k * WAVE + lane;
-                    e[k] = i < hi ? sp.ord[i] : make_int4(-1, -1, 0, 0);
-                }
-                // tin = the parent's tin (written by its own group) + the offset the
-                // bottom-up atomic returned
-                uint64_t tin[NB];
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    tin[k] = 0;
-                    if (e[k].x >= 0 && e[k].y >= 0) tin[k] = (uint64_t)rec_tin(sp.rec, e[k].y) + (uint32_t)e[k].w;
-                }
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    if (e[k].x < 0) continue;
-                    astore(&sp.rec[2 * (size_t)e[k].x], tin[k] + (uint64_t)(uint32_t)e[k].z);
-                    astore(&sp.rec[2 * (size_t)e[k].x + 1], (uint64_t)(uint32_t)e[k].y | (tin[k] << 32));
-                }
-            }
-            fence_wg();  // the next group reads the intervals of this one
-            hi = lo;
-        }
-    }
-    return true;
-}
-
-// f by walking each vertex's tau0 ancestors (Theorem 3.4 as a sum over
-// vertices u of d(u) q(u): every tau0 edge x -> p0(x) on u's tau0 path adds
-// 2m - vol(x) when tau uses it in the same direction and x is a tau ancestor
-// of u, and subtracts 2m - vol(p0(x)) when tau uses it the other way and
-// p0(x) (not the root) is a tau ancestor of u).
-//
-// With the graph's ancestor table (shallow tau0: anc0[i n + u] is the
-// (i+1)-th tau0 ancestor of u, -1 past the root) every record a vertex needs
-// is loaded at once; otherwise the walk follows p0 step by step.
-
-template <int D>
-__device__ __forceinline__ int64_t q_of_table(const GraphDev &g, const SlotPtrs &sp, int u) {
-    const int root = g.root;
-    const int64_t two_m = g.two_m;
-    const size_t n = (size_t)g.n;
-    int z[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) z[i] = g.anc0[(size_t)i * n + (size_t)u];
-    TNum nz[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-        nz[i] = TNum{0u, 0u, -2};
-        if (z[i] >= 0 && z[i] != root) nz[i] = rec_num(sp.rec, z[i]);
-    }
-    const TNum nu = rec_num(sp.rec, u);
-    const uint32_t tu = nu.tin;
-    int x = u;
-    TNum nx = nu;
-    int64_t q = 0;
-    bool go = u != root;
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-        if (go && z[i] >= 0) {
-            if (nx.par == z[i]) {
-                if (nx.tin <= tu && tu < nx.tin + nx.vol) q += two_m - (int64_t)nx.vol;
-            }
-            if (z[i] == root) {
-                go = false;
-            } else {
-                if (nz[i].par == x) {
-                    if (nz[i].tin <= tu && tu < nz[i].tin + nz[i].vol) q -= two_m - (int64_t)nz[i].vol;
-                }
-                x = z[i];
-                nx = nz[i];
-            }
-        }
-    }
-    return q;
-}
-
-// U vertices per lane and step (their loads in flight together); the deeper
-// table takes one, to keep the kernel's register count at its occupancy (a
-// table of more than 8 levels would not fit it, so deeper trees follow p0).
-template <int D, int U>
-__device__ int64_t f_walk_table(const GraphDev &g, const SlotPtrs &sp) {
-    const int lane = threadIdx.x;
-    const int n = g.n;
-    int64_t acc = 0;
-    for (int b = 0; b < n; b += U * WAVE) {
-        int64_t q[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int u = b + k * WAVE + lane;
-            q[k] = u < n ? q_of_table<D>(g, sp, u) : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int u = b + k * WAVE + lane;
-            if (u < n) acc += (int64_t)degree(g, u) * q[k];
-        }
-    }
-    return wave_sum(acc);
-}
-
-__device__ int64_t f_walk(const GraphDev &g, const SlotPtrs &sp) {
-    if (g.anc0 && g.anc_depth <= 4) return f_walk_table<4, 2>(g, sp);
-    if (g.anc0 && g.anc_depth <= 8) return f_walk_table<8, 1>(g, sp);
-    const int lane = threadIdx.x;
-    const int n = g.n, root = g.root;
-    const int64_t two_m = g.two_m;
-    int64_t acc = 0;
-    for (int u = lane; u < n; u += WAVE) {
-        const TNum nu = rec_num(sp.rec, u);
-        const uint32_t tu = nu.tin;
-        int64_t q = 0;
-        int x = u;
-        TNum nx = nu;
-        while (x != root) {
-            const int z = g.p0[x];
-            if (nx.par == z) {
-                if (nx.tin <= tu && tu < nx.tin + nx.vol) q += two_m - (int64_t)nx.vol;
-            }
-            if (z == root) break;
-            const TNum nz = rec_num(sp.rec, z);
-            if (nz.par == x) {
-                if (nz.tin <= tu && tu < nz.tin + nz.vol) q -= two_m - (int64_t)nz.vol;
-            }
-            x = z;
-            nx = nz;
-        }
-        acc += (int64_t)degree(g, u) * q;
-    }
-    return wave_sum(acc);
-}
-
-// f by a tau0-preorder sweep, 64 preorder positions per step.  The Fenwick
-// tree holds the items of every tau0 vertex whose subtree started before the
-// step and is still open; items of the step's own vertices and of subtrees
-// closing inside the step are handled exactly from LDS.  The tree returns
-// to all zeros at the end of the sweep.
-struct SweepShared {
-    Items it[WAVE];
-    int32_t out[WAVE];
-    Items eit[WAVE];
-    int32_t eout[WAVE];
-};
-
-__device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_len, SweepShared &ss) {
-    Items *sh_it = ss.it;
-    int32_t *sh_out = ss.out;
-    Items *se_it = ss.eit;
-    int32_t *se_out = ss.eout;
-    const int lane = threadIdx.x;
-    const int n = g.n;
-    int64_t acc = 0;
-    int blk = 0;
-    for (int P0 = 0; P0 < n; P0 += WAVE, ++blk) {
-        const int p = P0 + lane;
-        const bool valid = p < n;
-        Items it{0u, 0u, 0u, 0u, 0, 0};
-        int32_t o = -1;
-        uint32_t tu = 0;
-        int u = g.root;
-        if (valid) {
-            u = g.pre0[p];
-            it = items_of(g, sp.rec, u);
-            o = g.out0[u];
-            tu = rec_tin(sp.rec, u);
-        }
-        int64_t S = valid ? fen_prefix(sp.fen, fen_len, tu) : 0;
-        sh_it[lane] = it;
-        sh_out[lane] = o;
-        __syncthreads();
-        if (valid) {
-            for (int j = 0; j <= lane; ++j)
-                if (sh_out[j] >= p) S += items_at(sh_it[j], tu);
-        }
-        const int e0 = g.eoff[blk], e1 = g.eoff[blk + 1];
-        for (int c = e0; c < e1; c += WAVE) {
-            const int k = c + lane;
-            Items ex{0u, 0u, 0u, 0u, 0, 0};
-            int32_t xo = -1;
-            if (k < e1) {
-                const int x = g.elist[k];
-                ex = items_of(g, sp.rec, x);
-                xo = g.out0[x];
-            }
-            se_it[lane] = ex;
-            se_out[lane] = xo;
-            __syncthreads();
-            if (valid) {
-                const int cnt = min(WAVE, e1 - c);
-                for (int j = 0; j < cnt; ++j)
-                    if (se_out[j] < p) S -= items_at(se_it[j], tu);
-            }
-            if (k < e1) {
-                fen_range_add(sp.fen, fen_len, ex.flo, ex.fhi, -ex.fw);
-                fen_range_add(sp.fen, fen_len, ex.rlo, ex.rhi, -ex.rw);
-            }
-            __syncthreads();
-        }
-        if (valid) {
-            acc += (int64_t)degree(g, u) * S;
-            if (o >= P0 + WAVE) {
-                fen_range_add(sp.fen, fen_len, it.flo, it.fhi, it.fw);
-                fen_range_add(sp.fen, fen_len, it.rlo, it.rhi, it.rw);
-            }
-        }
-        fence_wg();
-        __syncthreads();
-    }
-    return wave_sum(acc);
-}
-
-// Signed count of the edges of a fixed u -> v path that the tree's own u -> v
-// path uses (+1 along the path's direction, -1 against it); its mean over
-// uniform spanning trees is the effective resistance R(u, v) (Kirchhoff: the
-// tree path's direction on an edge has mean equal to the unit current there,
-// and currents summed along any u -> v path give the potential difference).
-// Ancestry from the tree numbering: x is an ancestor of y (or y itself) iff
-// tin(x) <= tin(y) < tin(x) + vol(x).
-__device__ int64_t path_current(const SlotPtrs &sp, const int32_t *path, int len) {
-    const int lane = threadIdx.x;
-    const int u = path[0], v = path[len - 1];
-    const uint32_t tu = rec_tin(sp.rec, u), tv = rec_tin(sp.rec, v);
-    auto anc_u = [&](uint32_t t, uint32_t vol) { return t <= tu && tu < t + vol; };
-    auto anc_v = [&](uint32_t t, uint32_t vol) { return t <= tv && tv < t + vol; };
-    int64_t c = 0;
-    for (int i = lane; i + 1 < len; i += WAVE) {
-        const int a = path[i], b = path[i + 1];
-        const TNum na = rec_num(sp.rec, a), nb = rec_num(sp.rec, b);
-        const uint32_t ta = na.tin, va = na.vol, tb = nb.tin, vb = nb.vol;
-        const int32_t pa = na.par, pb = nb.par;
-        const bool up_a = anc_u(ta, va) && !anc_v(ta, va), up_b = anc_u(tb, vb) && !anc_v(tb, vb);
-        const bool dn_a = anc_v(ta, va) && !anc_u(ta, va), dn_b = anc_v(tb, vb) && !anc_u(tb, vb);
-        if ((up_a && pa == b) || (dn_b && pb == a)) c += 1;
-        else if ((up_b && pb == a) || (dn_a && pa == b)) c -= 1;
-    }
-    return wave_sum(c);
-}
-
-// Number of graph edges {x, y} that join the two trees left when the tree
-// edge {cut_u, cut_v} is removed (the side away from the root is Sub(tau, c)
-// with c the child endpoint; membership from the tree numbering).  With
-// relink, also cut-link (section 4.2): edge number j of them, in the order
-// (x ascending, row order, x < y), with j drawn by Philox on counter
-// (slot, serial, ISM_CTR_LO, ISM_CTR_HI), joins the two parts; the path from
-// its inner endpoint up to c is reversed so the tree stays rooted at r.
-__device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const RunParams &rp, int32_t slot,
-                                  int idx) {
-    const int lane = threadIdx.x;
-    const int n = g.n;
-    const int a = rp.cut_u, b = rp.cut_v;
-    const int32_t pa = rec_parent(sp.rec, a);
-    const int32_t pb = rec_parent(sp.rec, b);
-    const int c = pa == b ? a : (pb == a ? b : -1);
-    if (c < 0) {
-        report_error(rp.ctl, DEV_BADTREE, idx);
-        return 0;
-    }
-    const TNum nc = rec_num(sp.rec, c);
-    const uint32_t lo = nc.tin, hi = nc.tin + nc.vol;
-    auto inside = [&](int x) {
-        const uint32_t t = rec_tin(sp.rec, x);
-        return lo <= t && t < hi;
-    };
-    auto row_count = [&](int x, bool ix) {
-        int64_t k = 0;
-        for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
-            const int y = g.adj[e];
-            if (y > x && inside(y) != ix) ++k;
-        }
-        return k;
-    };
-    int64_t cnt = 0;
-    for (int x = lane; x < n; x += WAVE) cnt += row_count(x, inside(x));
-    const int64_t total = wave_sum(cnt);
-    if (!rp.relink) return total;
-    if (total <= 0) {
-        report_error(rp.ctl, DEV_BADTREE, idx);
-        return 0;
-    }
-    const int64_t j = arrow_slot(rp.seed, ((uint64_t)ISM_CTR_HI << 32) | ISM_CTR_LO, rp.serial, (uint32_t)slot,
-                                 (uint32_t)total);
-    int64_t base = 0;
-    for (int x0 = 0; x0 < n; x0 += WAVE) {
-        const int x = x0 + lane;
-        const bool ix = x < n && inside(x);
-        const int64_t k = x < n ? row_count(x, ix) : 0;
-        int64_t incl = k;
-        for (int d = 1; d < WAVE; d <<= 1) {
-            const int64_t t = __shfl_up(incl, d);
-            if (lane >= d) incl += t;
-        }
-        const int64_t chunk = __shfl(incl, WAVE - 1);
-        if (base + chunk > j) {
-            if (k > 0 && base + incl - k <= j && j < base + incl) {
-                int64_t r = j - (base + incl - k);
-                int y = -1;
-                for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
-                    const int z = g.adj[e];
-                    if (z > x && inside(z) != ix) {
-                        if (r == 0) { y = z; break; }
-                        --r;
-                    }
-                }
-                if (y < 0) {
-                    report_error(rp.ctl, DEV_BADTREE, idx);
-                } else {
-                    const int xi = ix ? x : y, yo = ix ? y : x;
-                    int32_t *out = rp.parents_mut + (size_t)slot * (size_t)n;
-                    int32_t prev = yo, z = xi;
-                    for (int guard = 0; guard <= n; ++guard) {
-                        const int32_t nz = rec_parent(sp.rec, z);
-                        out[z] = prev;
-                        if (z == c) break;
-                        if (nz < 0 || nz >= n) {  // c is an ancestor of xi: not reached
-                            report_error(rp.ctl, DEV_BADTREE, idx);
-                            break;
-                        }
-                        prev = z;
-                        z = nz;
-                    }
-                }
-            }
-            break;
-        }
-        base += chunk;
-    }
-    return total;
-}
-
 // ------------------------------------------------------------ the kernels
+
+// The sampler's arrays inside a slot's state block.
+__device__ __forceinline__ SamplerWS sampler_ws(const SlotPtrs &sp) {
+    SamplerWS ws;
+    ws.tagw = reinterpret_cast<uint64_t *>(sp.state);
+    ws.arrow = reinterpret_cast<uint64_t *>(sp.state + 8 * sp.stride);
+    ws.rq = reinterpret_cast<int32_t *>(sp.state + 16 * sp.stride);
+    ws.queue = sp.queue;
+    ws.start = sp.cstart;
+    return ws;
+}
 
 // The sampler and the sweep run one after the other: one LDS block serves both.
 template <int CH>
 union KernelShared {
     SamplerShared<CH> samp;
-    SweepShared sweep;
+    SweepItem sweep[2 * WAVE];
 };
-
-// The per-slot arrays of workgroup blockIdx.x, each `stride` vertices long.
-__device__ __forceinline__ SlotPtrs slot_ptrs(const SlotDev &sd, size_t stride) {
-    SlotPtrs sp;
-    const size_t b = (size_t)blockIdx.x;
-    unsigned char *st = sd.state + b * (size_t)state_bytes((int64_t)stride);
-    sp.ws.tagw = reinterpret_cast<uint64_t *>(st);
-    sp.ws.arrow = reinterpret_cast<uint64_t *>(st + 8 * stride);
-    sp.ws.rq = reinterpret_cast<int32_t *>(st + 16 * stride);
-    sp.ws.queue = sd.queue + b * (size_t)sd.chains;
-    sp.ws.start = sd.cstart + b * (size_t)sd.chains;
-    sp.rec = sd.rec ? reinterpret_cast<uint64_t *>(sd.rec) + 2 * b * stride : nullptr;
-    // the numbering's arrays reuse the sampler's block (dead once the parents are in rec)
-    sp.ord = sd.rec ? reinterpret_cast<int4 *>(st) : nullptr;
-    sp.grp = sd.rec ? reinterpret_cast<int32_t *>(st + 16 * stride) : nullptr;
-    sp.fen = sd.fen ? sd.fen + b * (size_t)sd.fen_len : nullptr;
-    return sp;
-}
 
 // One sample s (work item idx) of graph g through the whole path in the
 // calling workgroup: the tree, then (except in RUN_SAMPLE) its numbering and
 // f.  Returns false when the workgroup must stop (an error was recorded).
-// CROSS: the instantiation for RUN_CROSS only (no sampler, no f), kept apart
-// so that its code does not weigh on the sampler's register allocation.
-template <int CH, bool CROSS, bool LEAN>
-__device__ bool process_one(const GraphDev &g, const SlotPtrs &sp, KernelShared<CH> &lds, const RunParams &rp,
-                            int64_t fen_len, int idx, uint64_t s) {
+template <int CH, bool LEAN>
+__device__ bool process_one(const GraphDev &g, const SlotPtrs &sp, KernelShared<CH> &lds, TreeShared<WAVE> &tree,
+                            const RunParams &rp, int64_t fen_len, int idx, uint64_t s) {
     const int lane = threadIdx.x;
     const size_t n = (size_t)g.n;
-    int64_t steps = 0, iters = 0;
-    if (!CROSS && (rp.mode == RUN_SAMPLE || rp.mode == RUN_ESTIMATE)) {
-        steps = sample_tree<CH, LEAN>(g, sp.ws, lds.samp, rp.seed, s, rp.walkers, rp.iter_cap, rp.ctl, idx, &iters,
-                                rp.root_u, rp.root_v);
-        if (steps < 0) return false;
-    }
-    if (!CROSS && rp.mode == RUN_SAMPLE) {
+    int64_t iters = 0;
+    const SamplerWS ws = sampler_ws(sp);
+    const int64_t steps = sample_tree<CH, LEAN>(g, ws, lds.samp, rp.seed, s, rp.walkers, rp.iter_cap, rp.ctl, idx,
+                                                &iters, rp.root_u, rp.root_v);
+    if (steps < 0) return false;
+    if (rp.mode == RUN_SAMPLE) {
         int32_t *po = rp.parents_out + (size_t)idx * n;
         uint32_t *co = rp.cnt_out ? rp.cnt_out + (size_t)idx * n : nullptr;
         for (int v = lane; v < g.n; v += WAVE) {
-            const uint64_t ar = aload(&sp.ws.arrow[v]);
+            const uint64_t ar = aload(&ws.arrow[v]);
             po[v] = (int32_t)(uint32_t)ar;  // -1 at vertices that started in the tree
             if (co) co[v] = (uint32_t)(ar >> 32);
         }
     } else {
-        // parent and degree into each vertex's tree record; its volume word starts at deg(v)
-        const size_t row = rp.rows ? (size_t)rp.rows[idx] : (size_t)idx;
-        bool bad = false;
-        for (int b = 0; b < g.n; b += WAVE * NBS) {
-            int32_t p[NBS];
-#pragma unroll
-            for (int k = 0; k < NBS; ++k) {
-                const int v = b + k * WAVE + lane;
-                p[k] = -1;
-                if (v < g.n && v != g.root)
-                    p[k] = (rp.mode != RUN_ESTIMATE) ? rp.parents_in[row * n + v]
-                                                     : (int32_t)(uint32_t)aload(&sp.ws.arrow[v]);
-            }
-#pragma unroll
-            for (int k = 0; k < NBS; ++k) {
-                const int v = b + k * WAVE + lane;
-                if (v >= g.n) continue;
-                if (v != g.root && (p[k] < 0 || p[k] >= g.n || p[k] == v)) { bad = true; p[k] = g.root; }
-                const uint64_t d = degree(g, v);
-                astore(&sp.rec[2 * (size_t)v], d);
-                astore(&sp.rec[2 * (size_t)v + 1], (uint64_t)(uint32_t)p[k] | (d << 32));
-            }
-        }
-        fence_wg();
-        bool ok = tree_numbering(g, sp);
-        if (__ballot(bad) != 0ull) ok = false;
-        int64_t f = 0;
-        if constexpr (CROSS) {
-            f = ok ? crossing_edges(g, sp, rp, (int32_t)row, idx) : 0;
-        } else {
-            if (rp.mode == RUN_CURRENT) f = path_current(sp, rp.path, rp.path_len);
-            else if (rp.traversal == 2) f = f_sweep(g, sp, fen_len, lds.sweep);
-            else f = f_walk(g, sp);
-        }
-        if (!ok) report_error(rp.ctl, DEV_BADTREE, idx);
-        if (lane == 0) rp.f_out[idx] = f;
+        evaluate_tree<WAVE>(g, sp, tree, lds.sweep, rp, fen_len, idx, (size_t)idx,
+                            [&](int v) { return (int32_t)(uint32_t)aload(&ws.arrow[v]); });
     }
     if (rp.steps_out && lane == 0) rp.steps_out[idx] = steps;
     if (rp.iters_out && lane == 0) rp.iters_out[idx] = iters;
     return true;
-}
-
-// The next work item for the calling workgroup (one atomic per workgroup).
-__device__ __forceinline__ int next_item(int32_t *ctl) {
-    int idx = 0;
-    if (threadIdx.x == 0) idx = __hip_atomic_fetch_add(&ctl[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // lane 0 is the first active lane: the index becomes a wave-uniform (scalar) value
-    return __builtin_amdgcn_readfirstlane(idx);
-}
-__device__ __forceinline__ bool stopped(const int32_t *ctl) {
-    return __hip_atomic_load(const_cast<int32_t *>(&ctl[1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
 
 // Waves per SIMD the kernel is built to fit: three at 1,024 chains (168 VGPRs;
@@ -1357,16 +662,17 @@ __device__ __forceinline__ bool stopped(const int32_t *ctl) {
 template <int CH>
 constexpr int waves_per_simd() { return CH <= 1024 ? 3 : 2; }
 
-template <int CH, bool CROSS = false, bool LEAN = false>
+template <int CH, bool LEAN>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(waves_per_simd<CH>())))
 persistent_kernel(GraphDev g, SlotDev sd, RunParams rp) {
     __shared__ KernelShared<CH> lds;
+    __shared__ TreeShared<WAVE> tree;
     const SlotPtrs sp = slot_ptrs(sd, (size_t)g.n);
     int64_t done = 0;
     while (true) {
-        const int idx = next_item(rp.ctl);
-        if (idx >= rp.count || stopped(rp.ctl)) break;
-        if (!process_one<CH, CROSS, LEAN>(g, sp, lds, rp, sd.fen_len, idx, (uint64_t)(rp.first + idx))) break;
+        const int idx = next_item<WAVE>(rp.ctl, tree);
+        if (idx >= rp.count) break;
+        if (!process_one<CH, LEAN>(g, sp, lds, tree, rp, sd.fen_len, idx, (uint64_t)(rp.first + idx))) break;
         // samples finished by this workgroup, for a host that watches a long batch
         ++done;
         if (rp.progress && threadIdx.x == 0)
@@ -1385,11 +691,12 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(waves
 batch_kernel(BatchArgs a, SlotDev sd, int32_t *ctl,
                                                      const int64_t *launch) {
     __shared__ KernelShared<CH> lds;
+    __shared__ TreeShared<WAVE> tree;
     const SlotPtrs sp = slot_ptrs(sd, (size_t)sd.stride);
     const int64_t L = *launch;
     while (true) {
-        const int idx = next_item(ctl);
-        if (idx >= a.base[a.k] || stopped(ctl)) break;
+        const int idx = next_item<WAVE>(ctl, tree);
+        if (idx >= a.base[a.k]) break;
         int j = 0;
         while (j + 1 < a.k && idx >= a.base[j + 1]) ++j;
         const BatchJob &job = a.job[j];
@@ -1404,7 +711,7 @@ batch_kernel(BatchArgs a, SlotDev sd, int32_t *ctl,
         rp.steps_out = a.steps;
         rp.iters_out = a.iters;
         const uint64_t s = (uint64_t)(job.first + L * (int64_t)(a.base[j + 1] - a.base[j]) + (idx - a.base[j]));
-        if (!process_one<CH, false, LEAN>(job.g, sp, lds, rp, job.g.two_m + 2, idx, s)) break;
+        if (!process_one<CH, LEAN>(job.g, sp, lds, tree, rp, job.g.two_m + 2, idx, s)) break;
     }
 }
 
@@ -1578,16 +885,14 @@ bool valid_chains(int chains) {
 
 hipError_t launch_persistent(const GraphDev &g, const SlotDev &s, const RunParams &rp, int chains,
                              int slots, hipStream_t stream) {
-    if (rp.mode == RUN_CROSS) {
-        hipLaunchKernelGGL((persistent_kernel<1024, true>), dim3(slots), dim3(WAVE), 0, stream, g, s, rp);
-        return hipGetLastError();
-    }
+    if (rp.mode != RUN_SAMPLE && rp.mode != RUN_ESTIMATE) return launch_tree(g, s, rp, slots, stream);
+    if (rp.route != ROUTE_CHAINS) return launch_frontier(g, s, rp, slots, stream);
 #define KC_CASE(C)                                                                                   \
     if (chains == C) {                                                                              \
         if (rp.lean)                                                                                \
-            hipLaunchKernelGGL((persistent_kernel<C, false, true>), dim3(slots), dim3(WAVE), 0, stream, g, s, rp); \
+            hipLaunchKernelGGL((persistent_kernel<C, true>), dim3(slots), dim3(WAVE), 0, stream, g, s, rp); \
         else                                                                                        \
-            hipLaunchKernelGGL((persistent_kernel<C, false, false>), dim3(slots), dim3(WAVE), 0, stream, g, s, rp); \
+            hipLaunchKernelGGL((persistent_kernel<C, false>), dim3(slots), dim3(WAVE), 0, stream, g, s, rp); \
         return hipGetLastError();                                                                   \
     }
     KC_CHAIN_VARIANTS(KC_CASE)
@@ -1615,7 +920,7 @@ int persistent_blocks_per_cu(int chains) {
     int blocks = 0;
 #define KC_CASE(C)                                                                                   \
     if (chains == C) {                                                                              \
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, persistent_kernel<C>, WAVE, 0) !=   \
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, persistent_kernel<C, false>, WAVE, 0) !=   \
             hipSuccess)                                                                             \
             return 0;                                                                               \
         return blocks;                                                                              \
@@ -1652,7 +957,8 @@ hipError_t launch_batch(const BatchArgs &a, const SlotDev &s, int32_t *ctl, int6
         e = hipGetLastError();                                                                   \
     }
     e = hipErrorInvalidValue;
-    KC_CHAIN_VARIANTS(KC_CASE)
+    if (batch_is_frontier(a)) e = launch_frontier_batch(a, s, ctl, launch, slots, stream);
+    else { KC_CHAIN_VARIANTS(KC_CASE) }
 #undef KC_CASE
     if (e != hipSuccess) return e;
     Ranges r{};

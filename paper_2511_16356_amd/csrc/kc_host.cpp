@@ -206,14 +206,32 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 
 }  // namespace
 
-// One slot per resident single-wave workgroup of the persistent kernel.
-int kc_host::default_slots(const kc_graph *g, bool batch) {
-    int dev = 0, cus = 0, per_cu = 0;
+// The frontier sampler takes every graph whose words fit a CU's LDS.  Of the
+// larger ones it takes those with short walks: a shallow reference tree (the
+// traversal's own rule) and a mean degree of at least 8.
+int kc_host::route_of(const kc_graph *g) {
+    if (g->n <= kc::LDS_MAX_N) return kc::ROUTE_LDS;
+    return g->two_m >= 8 * g->n && g->depth0 <= 12 ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
+}
+
+// One slot per resident workgroup of the launch's kernel (per_cu of them on a CU).
+int kc_host::resident_slots(int per_cu) {
+    int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 1024;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 1024;
-    per_cu = batch ? kc::batch_blocks_per_cu(g->chains) : kc::persistent_blocks_per_cu(g->chains);
-    if (cus <= 0 || per_cu <= 0) return 1024;
-    return cus * per_cu;
+    return cus > 0 && per_cu > 0 ? cus * per_cu : 1024;
+}
+int kc_host::default_slots(const kc_graph *g, int mode) {
+    const int route = route_of(g);
+    int per_cu = 0;
+    if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n);
+    else if (route == kc::ROUTE_CHAINS) per_cu = kc::persistent_blocks_per_cu(g->chains);
+    else per_cu = kc::frontier_blocks_per_cu(route, g->n);
+    return resident_slots(per_cu);
+}
+
+int kc_host::workspace_slots(const kc_graph *g) {
+    return std::max(default_slots(g), default_slots(g, kc::RUN_EVALUATE));
 }
 
 // Workspace bytes a launch may allocate: the graph's budget option, else 80%
@@ -261,6 +279,7 @@ void kc_host::fill_run_options(const kc_graph *g, kc::RunParams &rp) {
     // lean looks pay where walks are short, so that most looks at a walk's next
     // vertex meet the tree: by default when the mean degree is at least 8
     rp.lean = g->lean_opt == 2 || (g->lean_opt == 0 && g->two_m >= 8 * g->n);
+    rp.route = route_of(g);
     rp.iter_cap = g->step_limit > 0 ? g->step_limit : 1024 * g->n + (1 << 22);
     rp.ctl = g->d_ctl;
 }
@@ -295,11 +314,12 @@ namespace {
 kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
     const bool trav = rp.mode != kc::RUN_SAMPLE;
     const bool fen = trav && g->traversal == KC_TRAV_SWEEP;
-    int want = g->slots_opt > 0 ? g->slots_opt : default_slots(g);
+    int want = g->slots_opt > 0 ? g->slots_opt : workspace_slots(g);
     want = std::min(want, rp.count);
     int slots = 0;
     kc_status st = ensure_workspace(g, want, trav, fen, stream, &slots);
     if (st != KC_OK) return st;
+    if (g->slots_opt <= 0) slots = std::min(slots, default_slots(g, rp.mode));
     slots = balanced_slots(slots, rp.count);
     kc::SlotDev sd;
     sd.state = g->d_state;
@@ -875,7 +895,7 @@ kc_status kc_reserve(kc_graph *g, int32_t count, void *hip_stream) {
     g_last_error.clear();
     if (!g) return fail(KC_ERR_INVALID, "NULL graph");
     if (count < 1) return fail(KC_ERR_INVALID, "count must be >= 1");
-    int want = g->slots_opt > 0 ? g->slots_opt : default_slots(g);
+    int want = g->slots_opt > 0 ? g->slots_opt : workspace_slots(g);
     want = std::min(want, count);
     int slots = 0;
     kc_status st = ensure_workspace(g, want, true, g->traversal == KC_TRAV_SWEEP, (hipStream_t)hip_stream, &slots);

@@ -59,9 +59,14 @@ struct BatchJob {
     uint64_t seed;
     int64_t first;      // sample index of the job's first item at launch 0
     int64_t iter_cap;   // sampler rounds per sample
-    int32_t walkers, traversal, lean;
+    int32_t walkers, traversal, lean, route;
 };
 
+// How a graph's trees are sampled: by the chain sampler (kc_device.hip), or by
+// the frontier sampler (kc_frontier.hip) with its words in LDS or in the slot's
+// state block.
+enum Route { ROUTE_CHAINS = 0, ROUTE_LDS = 1, ROUTE_GLOBAL = 2 };
+constexpr int64_t LDS_MAX_N = (1 << 15) - 1;  // a word holds two vertices and two flags
 constexpr int BATCH_MAX = 8;  // graphs in one batch launch
 
 // Kernel arguments of a batch launch: k jobs; job j owns work items
@@ -89,6 +94,7 @@ struct RunParams {
     int32_t traversal;  // 1 walk, 2 sweep
     int32_t lean;       // 1: a walk's look at its next vertex is the claim alone (results do
                         //    not depend on it)
+    int32_t route;      // Route, for the modes that sample
     int64_t iter_cap;   // sampler iterations per sample
     const int32_t *parents_in; // RUN_EVALUATE input [count*n]
     int32_t *parents_out;      // RUN_SAMPLE  [count*n]
@@ -141,6 +147,21 @@ hipError_t launch_link_cut(int32_t *par, const int32_t *rows, int32_t count, int
                            hipStream_t stream);
 hipError_t launch_flag_trees(const int32_t *par, int32_t count, int64_t n, const int32_t *eu,
                              const int32_t *ev, int32_t ne, uint8_t *flags, hipStream_t stream);
+// The frontier sampler's launches (routes other than ROUTE_CHAINS), and the
+// evaluation of trees the caller holds (kc_frontier.hip).
+hipError_t launch_frontier(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream);
+hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *ctl, const int64_t *launch,
+                                 int slots, hipStream_t stream);
+hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream);
+int frontier_blocks_per_cu(int route, int64_t n);  // resident workgroups per CU
+int frontier_batch_blocks_per_cu(const BatchArgs &a);
+int tree_blocks_per_cu(int64_t n);
+// The batch takes the frontier sampler when every job's route is one of its.
+inline bool batch_is_frontier(const BatchArgs &a) {
+    for (int j = 0; j < a.k; ++j)
+        if (a.job[j].route == ROUTE_CHAINS) return false;
+    return true;
+}
 bool valid_chains(int chains);            // a built chain-table size?
 int persistent_blocks_per_cu(int chains);  // resident workgroups per CU for that size
 int batch_blocks_per_cu(int chains);       // the same for the batch kernel

@@ -1,0 +1,838 @@
+// kc_tree.h -- device code shared by the sampling kernels: memory and wave
+// helpers, the Philox arrows, and everything a sampled tree goes through
+// (volumes, numbering, f).  Included by the kernel files only.
+//
+// The tree code runs in a workgroup of T threads (64: one wavefront) that owns
+// one tree.  Threads exchange data through global memory by workgroup-scope
+// relaxed atomics (L2-coherent on gfx950), ordered by the workgroup barriers.
+#pragma once
+
+#include <type_traits>
+
+#include "kc_internal.h"
+
+namespace kc {
+namespace {
+
+constexpr int WAVE = 64;
+// Neighbours kept inline in a vertex's 32-byte graph record (see GraphDev::vrec).
+constexpr int VREC_INLINE = 6;
+
+// ------------------------------------------------------------ memory helpers
+
+template <typename T>
+__device__ __forceinline__ T aload(const T *p) {
+    return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ void astore(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ T afetch_add(T *p, T v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ T afetch_or(T *p, T v) {
+    return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ T afetch_and(T *p, T v) {
+    return __hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ T afetch_xor(T *p, T v) {
+    return __hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ T acas(T *p, T expected, T desired) {
+    __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+    return expected;  // value found at *p
+}
+// Orders one wavefront's memory operations among its lanes.
+__device__ __forceinline__ void sync_wave() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void fence_wg() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
+
+// ------------------------------------------------------------- wave helpers
+
+__device__ __forceinline__ int rank_in(uint64_t mask) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+__device__ __forceinline__ int64_t wave_sum(int64_t v) {
+    for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+__device__ __forceinline__ int wave_max(int v) {
+    for (int o = WAVE / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
+    return v;
+}
+
+// The first error of a launch stays (whichever threads call this).
+__device__ void report_error(int32_t *ctl, int code, int idx) {
+    int expected = 0;
+    if (__hip_atomic_compare_exchange_strong(&ctl[1], &expected, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT))
+        __hip_atomic_store(&ctl[2], idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ------------------------------------------------------------------ arrows
+
+// Philox4x32-10 block function (Salmon, Moraes, Dror, Shaw, SC'11): ten
+// rounds of two 32x32->64 multiplies with the Weyl key schedule.  Counter
+// (k, v, s_lo, s_hi), key (seed_lo, seed_hi).  The neighbour slot is the
+// high word of x * deg with x = out0 | out1 << 32, i.e. floor(x deg / 2^64),
+// computed from two 32x32 products.
+struct Bits {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Bits philox_bits(uint64_t seed, uint64_t s, uint32_t v, uint32_t k) {
+    uint32_t x0 = k, x1 = v, x2 = (uint32_t)s, x3 = (uint32_t)(s >> 32);
+    uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
+#pragma unroll
+    for (int round = 0; round < 10; ++round) {
+        // one full 32x32->64 product each (a single v_mad_u64_u32, not mul_lo + mul_hi)
+        const uint64_t a = (uint64_t)0xD2511F53u * x0;
+        const uint64_t b = (uint64_t)0xCD9E8D57u * x2;
+        const uint32_t y0 = (uint32_t)(b >> 32) ^ x1 ^ key0;
+        const uint32_t y2 = (uint32_t)(a >> 32) ^ x3 ^ key1;
+        x0 = y0; x1 = (uint32_t)b; x2 = y2; x3 = (uint32_t)a;
+        key0 += 0x9E3779B9u;
+        key1 += 0xBB67AE85u;
+    }
+    return Bits{x0, x1};
+}
+__device__ __forceinline__ uint32_t slot_of(Bits x, uint32_t deg) {
+    const uint64_t lowprod = (uint64_t)x.lo * deg;
+    const uint64_t highprod = (uint64_t)x.hi * deg + (lowprod >> 32);
+    return (uint32_t)(highprod >> 32);
+}
+__device__ __forceinline__ uint32_t arrow_slot(uint64_t seed, uint64_t s, uint32_t v, uint32_t k,
+                                               uint32_t deg) {
+    return slot_of(philox_bits(seed, s, v, k), deg);
+}
+
+// --------------------------------------------------------- tree traversal
+
+// The numbered tree: one 16-byte record per vertex, two 8-byte words, so that
+// every step of the numbering touches one line per vertex it visits:
+//   rec[2v]     pending children << 44 | volume while the volumes are summed
+//               (starting at deg(v)); tin(v) + vol(v) once the numbering is done
+//   rec[2v + 1] parent (low half, -1 at the root) | deg(v) (high half) until the
+//               top-down step, then parent | tin(v)
+struct SlotPtrs {
+    unsigned char *state;  // the sampler's block, 20 bytes per vertex
+    size_t stride;
+    int4 *queue;
+    int32_t *cstart;
+    uint64_t *rec;
+    int4 *ord;             // finished vertices {v, parent, vol, offset in the parent's interval} in
+                           // completion order; the leaves {v, parent, deg, 0} wait at its end
+    int32_t *grp;
+    int64_t *fen;
+};
+
+__device__ __forceinline__ int32_t rec_parent(const uint64_t *rec, int v) {
+    return (int32_t)(uint32_t)aload(&rec[2 * (size_t)v + 1]);
+}
+// The numbering of a vertex once it is complete: tin, vol and tree parent.
+struct TNum {
+    uint32_t tin, vol;
+    int32_t par;
+};
+__device__ __forceinline__ TNum rec_num(const uint64_t *rec, int v) {
+    const uint64_t w = aload(&rec[2 * (size_t)v]), h = aload(&rec[2 * (size_t)v + 1]);
+    TNum t;
+    t.tin = (uint32_t)(h >> 32);
+    t.vol = (uint32_t)(w - (h >> 32));
+    t.par = (int32_t)(uint32_t)h;
+    return t;
+}
+__device__ __forceinline__ uint32_t rec_tin(const uint64_t *rec, int v) {
+    return (uint32_t)(aload(&rec[2 * (size_t)v + 1]) >> 32);
+}
+
+// Vertices each lane keeps in flight in the tree numbering: the memory
+// operations of one step are issued together, so a wavefront has this many
+// times as many requests outstanding as it has lanes.  The streaming passes
+// take twice as many.
+constexpr int NB = 4;
+constexpr int NBS = 8;
+
+constexpr uint64_t PEND_ONE = 1ull << 44;
+constexpr uint64_t VOL_MASK = PEND_ONE - 1;
+
+__device__ __forceinline__ uint32_t degree(const GraphDev &g, int v) {
+    return (uint32_t)(g.off[v + 1] - g.off[v]);
+}
+
+// Fenwick tree over positions 0..2m storing a difference array.
+__device__ __forceinline__ void fen_point_add(int64_t *fen, int64_t len, int64_t pos, int64_t val) {
+    if (pos < 0) pos = 0;
+    for (int64_t i = pos + 1; i < len; i += i & (-i)) afetch_add(&fen[i], val);
+}
+__device__ __forceinline__ void fen_range_add(int64_t *fen, int64_t len, int64_t lo, int64_t hi,
+                                              int64_t val) {
+    if (val == 0 || hi <= lo) return;
+    fen_point_add(fen, len, lo, val);
+    fen_point_add(fen, len, hi, -val);
+}
+// The two contributions attached to tau0 vertex x (Theorem 3.4), as
+// ranges of tin with a weight, active for every u in Sub(tau0, x):
+//   forward : p(x) = p0(x)          -> +(2m - vol(x)) on Sub(tau, x)
+//   reverse : p(p0(x)) = x, p0(x)!=r -> -(2m - vol(p0(x))) on Sub(tau, p0(x))
+struct Items {
+    uint32_t flo, fhi, rlo, rhi;
+    int64_t fw, rw;
+};
+__device__ __forceinline__ Items items_of(const GraphDev &g, const uint64_t *rec, int x) {
+    Items it{0u, 0u, 0u, 0u, 0, 0};
+    if (x == g.root) return it;
+    const TNum nx = rec_num(rec, x);
+    const int z = g.p0[x];
+    if (nx.par == z) {
+        it.flo = nx.tin; it.fhi = nx.tin + nx.vol; it.fw = g.two_m - (int64_t)nx.vol;
+    }
+    if (z != g.root) {
+        const TNum nz = rec_num(rec, z);
+        if (nz.par == x) {
+            it.rlo = nz.tin; it.rhi = nz.tin + nz.vol; it.rw = (int64_t)nz.vol - g.two_m;
+        }
+    }
+    return it;
+}
+// Scratch of the tree code in LDS.
+template <int T>
+struct TreeShared {
+    int32_t count[4], take[4];  // rotating counters of the bottom-up rounds
+    int32_t leaves, bad, item;
+    int64_t red[T / WAVE];
+};
+
+// Sum of v over the workgroup, in every thread.
+template <int T>
+__device__ __forceinline__ int64_t block_sum(int64_t v, TreeShared<T> &sh) {
+    v = wave_sum(v);
+    if constexpr (T > WAVE) {
+        if ((threadIdx.x & (WAVE - 1)) == 0) sh.red[threadIdx.x / WAVE] = v;
+        __syncthreads();
+        v = 0;
+#pragma unroll
+        for (int w = 0; w < T / WAVE; ++w) v += sh.red[w];
+        __syncthreads();
+    }
+    return v;
+}
+// One LDS atomic per wavefront: the wavefront's share `n` of *counter, as its first position.
+__device__ __forceinline__ int take_shared(int32_t *counter, int n) {
+    int base = 0;
+    if ((threadIdx.x & (WAVE - 1)) == 0 && n > 0) base = afetch_add(counter, n);
+    return __builtin_amdgcn_readfirstlane(base);
+}
+
+// Volumes and the volume-weighted preorder of the tree whose parents are in
+// rec (rec[2v] = deg(v), rec[2v+1] = parent | deg(v) << 32 already).  Returns
+// false if the parents do not form a tree rooted at r.
+//
+// Bottom-up: each lane carries up to NB finished vertices; a carrier pushes
+// its vertex's volume into the parent's word with one atomic, and the last
+// child to arrive carries the parent on in the next round.  The volume part
+// the atomic returns is the parent's degree plus the volumes of the siblings
+// that arrived before: the vertex's offset in its parent's interval.  Every
+// round's finished vertices form a completion group.  Top-down: the groups in
+// reverse order (a parent always finishes in a later group than its
+// children); a vertex's tin is its parent's tin plus its offset.
+//
+// A round's counters rotate over four words: the one a round fills is read
+// after that round's barrier and cleared by thread 0 after the next one, two
+// barriers before it is filled again.
+template <int T>
+__device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared<T> &sh) {
+    const int tid = threadIdx.x;
+    const int n = g.n;
+    if (tid < 4) sh.count[tid] = sh.take[tid] = 0;
+    if (tid == 0) sh.leaves = 0;
+    // one PEND_ONE per child in the parent's word
+    for (int b = 0; b < n; b += T * NBS) {
+        int32_t p[NBS];
+#pragma unroll
+        for (int k = 0; k < NBS; ++k) {
+            const int v = b + k * T + tid;
+            p[k] = v < n ? rec_parent(sp.rec, v) : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < NBS; ++k)
+            if (p[k] >= 0) afetch_add(&sp.rec[2 * (size_t)p[k]], PEND_ONE);
+    }
+    __syncthreads();
+    // leaves {v, parent, deg, 0}: leaf number j at ord[n - 1 - j]
+    for (int b = 0; b < n; b += T * NBS) {
+        uint64_t w[NBS], h[NBS];
+#pragma unroll
+        for (int k = 0; k < NBS; ++k) {
+            const int v = b + k * T + tid;
+            w[k] = v < n ? aload(&sp.rec[2 * (size_t)v]) : PEND_ONE;  // past the end: not a leaf
+            h[k] = v < n ? aload(&sp.rec[2 * (size_t)v + 1]) : 0;
+        }
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < NBS; ++k) c += __popcll(__ballot((w[k] >> 44) == 0));
+        int at = take_shared(&sh.leaves, c);
+#pragma unroll
+        for (int k = 0; k < NBS; ++k) {
+            const bool leaf = (w[k] >> 44) == 0;
+            const uint64_t m = __ballot(leaf);
+            if (leaf)
+                sp.ord[n - 1 - (at + rank_in(m))] = make_int4(b + k * T + tid, (int32_t)(uint32_t)h[k],
+                                                              (int)(w[k] & VOL_MASK), 0);
+            at += __popcll(m);
+        }
+    }
+    __syncthreads();
+    const int L = sh.leaves;
+    // bottom-up.  Leaves are taken from the low end of their block, ord[n-L ..]:
+    // the finished entries of all rounds so far never reach a leaf that is still
+    // to be taken, since nord + (leaves not yet taken) <= n; within a round every
+    // leaf is read before the first entry is written.
+    int cv[NB], cp[NB];
+    uint64_t cval[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) { cv[k] = -1; cp[k] = -1; cval[k] = 0; }
+    int li = 0, nord = 0, ngrp = 0;
+    while (true) {
+        const int r = ngrp & 3;
+        if (li < L) {  // (uniform)
+            int c = 0;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) c += __popcll(__ballot(cv[k] < 0));
+            int at = li + take_shared(&sh.take[r], c);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const uint64_t freem = __ballot(cv[k] < 0);
+                const int j = at + rank_in(freem);
+                if (cv[k] < 0 && j < L) {
+                    const int4 e = sp.ord[n - L + j];
+                    cv[k] = e.x;
+                    cp[k] = e.y;
+                    cval[k] = (uint64_t)(uint32_t)e.z;
+                }
+                at += __popcll(freem);
+            }
+            if constexpr (T > WAVE) __syncthreads();
+        }
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) c += __popcll(__ballot(cv[k] >= 0));
+        int at = nord + take_shared(&sh.count[r], c);
+        // the parent's own parent, the next vertex if this child is the last, comes
+        // from the record line the atomic uses
+        uint64_t old[NB];
+        int32_t up[NB];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            old[k] = 0;
+            up[k] = -1;
+            if (cv[k] >= 0 && cp[k] >= 0) {
+                old[k] = afetch_add(&sp.rec[2 * (size_t)cp[k]], cval[k] - PEND_ONE);
+                up[k] = rec_parent(sp.rec, cp[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const uint64_t bm = __ballot(cv[k] >= 0);
+            const int i = at + rank_in(bm);
+            if (cv[k] >= 0 && i < n)
+                sp.ord[i] = make_int4(cv[k], cp[k], (int)cval[k], (int)(uint32_t)(old[k] & VOL_MASK));
+            at += __popcll(bm);
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const bool last = cv[k] >= 0 && cp[k] >= 0 && (old[k] >> 44) == 1;
+            cv[k] = last ? cp[k] : -1;
+            cp[k] = up[k];
+            if (last) cval[k] = (old[k] & VOL_MASK) + cval[k];
+        }
+        __syncthreads();
+        const int done = sh.count[r];
+        if (li < L) li = min(L, li + sh.take[r]);
+        if (tid == 0) {
+            sh.count[(r + 3) & 3] = sh.take[(r + 3) & 3] = 0;
+            if (ngrp <= n) astore(&sp.grp[ngrp], nord);
+        }
+        nord += done;
+        if (done == 0 || nord > n) break;  // nothing left; more entries than vertices: not a tree
+        ngrp++;
+    }
+    __syncthreads();
+    if (nord != n) return false;
+    // top-down; the group boundaries are read 64 at a time
+    const int lane = tid & (WAVE - 1);
+    for (int g0 = ngrp - 1; g0 >= 0; g0 -= WAVE) {
+        const int bnd = g0 - lane >= 0 ? aload(&sp.grp[g0 - lane]) : 0;
+        const int nb = min(WAVE, g0 + 1);
+        int hi = aload(&sp.grp[g0 + 1]);
+        for (int t = 0; t < nb; ++t) {
+            const int lo = __shfl(bnd, t);
+            for (int i0 = lo; i0 < hi; i0 += T * NB) {
+                int4 e[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const int i = i0 + k * T + tid;
+                    e[k] = i < hi ? sp.ord[i] : make_int4(-1, -1, 0, 0);
+                }
+                // tin = the parent's tin (written by its own group) + the offset the
+                // bottom-up atomic returned
+                uint64_t tin[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    tin[k] = 0;
+                    if (e[k].x >= 0 && e[k].y >= 0) tin[k] = (uint64_t)rec_tin(sp.rec, e[k].y) + (uint32_t)e[k].w;
+                }
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    if (e[k].x < 0) continue;
+                    astore(&sp.rec[2 * (size_t)e[k].x], tin[k] + (uint64_t)(uint32_t)e[k].z);
+                    astore(&sp.rec[2 * (size_t)e[k].x + 1], (uint64_t)(uint32_t)e[k].y | (tin[k] << 32));
+                }
+            }
+            __syncthreads();  // the next group reads the intervals of this one
+            hi = lo;
+        }
+    }
+    return true;
+}
+
+// f by walking each vertex's tau0 ancestors (Theorem 3.4 as a sum over
+// vertices u of d(u) q(u): every tau0 edge x -> p0(x) on u's tau0 path adds
+// 2m - vol(x) when tau uses it in the same direction and x is a tau ancestor
+// of u, and subtracts 2m - vol(p0(x)) when tau uses it the other way and
+// p0(x) (not the root) is a tau ancestor of u).
+//
+// With the graph's ancestor table (shallow tau0: anc0[i n + u] is the
+// (i+1)-th tau0 ancestor of u, -1 past the root) every record a vertex needs
+// is loaded at once; otherwise the walk follows p0 step by step.
+
+template <int D>
+__device__ __forceinline__ int64_t q_of_table(const GraphDev &g, const SlotPtrs &sp, int u) {
+    const int root = g.root;
+    const int64_t two_m = g.two_m;
+    const size_t n = (size_t)g.n;
+    int z[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) z[i] = g.anc0[(size_t)i * n + (size_t)u];
+    TNum nz[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        nz[i] = TNum{0u, 0u, -2};
+        if (z[i] >= 0 && z[i] != root) nz[i] = rec_num(sp.rec, z[i]);
+    }
+    const TNum nu = rec_num(sp.rec, u);
+    const uint32_t tu = nu.tin;
+    int x = u;
+    TNum nx = nu;
+    int64_t q = 0;
+    bool go = u != root;
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        if (go && z[i] >= 0) {
+            if (nx.par == z[i]) {
+                if (nx.tin <= tu && tu < nx.tin + nx.vol) q += two_m - (int64_t)nx.vol;
+            }
+            if (z[i] == root) {
+                go = false;
+            } else {
+                if (nz[i].par == x) {
+                    if (nz[i].tin <= tu && tu < nz[i].tin + nz[i].vol) q -= two_m - (int64_t)nz[i].vol;
+                }
+                x = z[i];
+                nx = nz[i];
+            }
+        }
+    }
+    return q;
+}
+
+// U vertices per lane and step (their loads in flight together); the deeper
+// table takes one, to keep the kernel's register count at its occupancy (a
+// table of more than 8 levels would not fit it, so deeper trees follow p0).
+template <int T, int D, int U>
+__device__ int64_t f_walk_table(const GraphDev &g, const SlotPtrs &sp) {
+    const int tid = threadIdx.x;
+    const int n = g.n;
+    int64_t acc = 0;
+    for (int b = 0; b < n; b += U * T) {
+        int64_t q[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int u = b + k * T + tid;
+            q[k] = u < n ? q_of_table<D>(g, sp, u) : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int u = b + k * T + tid;
+            if (u < n) acc += (int64_t)degree(g, u) * q[k];
+        }
+    }
+    return acc;
+}
+
+// (each thread's share of f)
+template <int T>
+__device__ int64_t f_walk(const GraphDev &g, const SlotPtrs &sp) {
+    if (g.anc0 && g.anc_depth <= 4) return f_walk_table<T, 4, 2>(g, sp);
+    if (g.anc0 && g.anc_depth <= 8) return f_walk_table<T, 8, 1>(g, sp);
+    const int n = g.n, root = g.root;
+    const int64_t two_m = g.two_m;
+    int64_t acc = 0;
+    for (int u = threadIdx.x; u < n; u += T) {
+        const TNum nu = rec_num(sp.rec, u);
+        const uint32_t tu = nu.tin;
+        int64_t q = 0;
+        int x = u;
+        TNum nx = nu;
+        while (x != root) {
+            const int z = g.p0[x];
+            if (nx.par == z) {
+                if (nx.tin <= tu && tu < nx.tin + nx.vol) q += two_m - (int64_t)nx.vol;
+            }
+            if (z == root) break;
+            const TNum nz = rec_num(sp.rec, z);
+            if (nz.par == x) {
+                if (nz.tin <= tu && tu < nz.tin + nz.vol) q -= two_m - (int64_t)nz.vol;
+            }
+            x = z;
+            nx = nz;
+        }
+        acc += (int64_t)degree(g, u) * q;
+    }
+    return acc;
+}
+
+// f by a tau0-preorder sweep, 64 preorder positions per step.  The Fenwick tree
+// holds the items of every tau0 vertex whose subtree started before the step and
+// is still open; items of the step's own vertices and of subtrees closing inside
+// the step are listed in LDS with the positions they hold for.  The tree returns
+// to all zeros at the end of the sweep.  Each thread's share of f.
+//
+// A step is bound by its dependent loads (vertex, record, tau0 parent, its
+// record), so the rest of it is spread over the workgroup: every wavefront has
+// all 64 positions and takes its share of the Fenwick tree's levels and of the
+// list, and the listing threads update the tree.  One wavefront doing all of it
+// took 40k cycles a step (17 ms for the 700 steps of a road-like graph of 44,780
+// vertices).
+struct SweepItem {
+    uint32_t lo, hi;  // holds for tin in [lo, hi)
+    int32_t from, to; // at preorder positions from .. to
+    int64_t w;
+};
+template <int T>
+constexpr size_t sweep_lds() { return 2 * T * sizeof(SweepItem); }
+
+template <int T>
+__device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_len, SweepItem *list,
+                           TreeShared<T> &sh) {
+    constexpr int WAVES = T / WAVE;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const int n = g.n;
+    int64_t acc = 0;
+    int blk = 0;
+    int levels = 1;
+    while ((1ll << levels) < fen_len) ++levels;
+    if (tid < 2) sh.count[tid] = 0;
+    __syncthreads();
+    int turn = 0;  // of the two list counters
+    for (int P0 = 0; P0 < n; P0 += WAVE, ++blk) {
+        const int p = P0 + lane;
+        const bool valid = p < n;
+        const int u = valid ? g.pre0[p] : g.root;
+        const uint32_t tu = rec_tin(sp.rec, u);
+        int64_t S = 0;
+        const int e0 = g.eoff[blk], e1 = g.eoff[blk + 1];
+        // the first list: the step's own vertices (wavefront 0) and closing subtrees
+        // (the others); then further closing subtrees
+        for (int c = e0, own = 1; own != 0 || c < e1;) {
+            const int k = own ? c + tid - WAVE : c + tid;
+            const bool mine = own && wave == 0, closing = !mine && k < e1;
+            int x = -1;
+            if (mine) x = valid ? u : -1;
+            else if (closing) x = g.elist[k];
+            Items it{0u, 0u, 0u, 0u, 0, 0};
+            int o = -1;
+            if (x >= 0) {
+                it = items_of(g, sp.rec, x);
+                o = g.out0[x];
+            }
+            if (own && valid) {
+                // this wavefront's levels of the prefix sum at tu
+                const int64_t i = min((int64_t)tu + 1, fen_len - 1);
+                for (int b = wave; b < levels; b += WAVES)
+                    if (i >> b & 1) S += aload(&sp.fen[i >> b << b]);
+            }
+            const int32_t from = mine ? p : o + 1, to = mine ? o : n;
+            const bool f1 = it.fw != 0, r1 = it.rw != 0;
+            const uint64_t fm = __ballot(f1), rm = __ballot(r1);
+            const int at = take_shared(&sh.count[turn], __popcll(fm) + __popcll(rm));
+            if (f1) list[at + rank_in(fm)] = {it.flo, it.fhi, from, to, mine ? it.fw : -it.fw};
+            if (r1) list[at + __popcll(fm) + rank_in(rm)] = {it.rlo, it.rhi, from, to, mine ? it.rw : -it.rw};
+            __syncthreads();
+            const int cnt = sh.count[turn];
+            turn ^= 1;
+            if (tid == 0) sh.count[turn] = 0;
+            // the tree as it stands after the step (every prefix sum has been read)
+            if (closing || (mine && o >= P0 + WAVE)) {
+                const int64_t sgn = mine ? 1 : -1;
+                fen_range_add(sp.fen, fen_len, it.flo, it.fhi, sgn * it.fw);
+                fen_range_add(sp.fen, fen_len, it.rlo, it.rhi, sgn * it.rw);
+            }
+            for (int j = wave; j < cnt; j += WAVES) {
+                const SweepItem e = list[j];
+                if (e.from <= p && p <= e.to && e.lo <= tu && tu < e.hi) S += e.w;
+            }
+            c += own ? T - WAVE : T;
+            own = 0;
+            __syncthreads();
+        }
+        if (valid) acc += (int64_t)degree(g, u) * S;
+    }
+    return acc;
+}
+
+// Signed count of the edges of a fixed u -> v path that the tree's own u -> v
+// path uses (+1 along the path's direction, -1 against it); its mean over
+// uniform spanning trees is the effective resistance R(u, v) (Kirchhoff: the
+// tree path's direction on an edge has mean equal to the unit current there,
+// and currents summed along any u -> v path give the potential difference).
+// Ancestry from the tree numbering: x is an ancestor of y (or y itself) iff
+// tin(x) <= tin(y) < tin(x) + vol(x).
+// (each thread's share of the count)
+template <int T>
+__device__ int64_t path_current(const SlotPtrs &sp, const int32_t *path, int len) {
+    const int u = path[0], v = path[len - 1];
+    const uint32_t tu = rec_tin(sp.rec, u), tv = rec_tin(sp.rec, v);
+    auto anc_u = [&](uint32_t t, uint32_t vol) { return t <= tu && tu < t + vol; };
+    auto anc_v = [&](uint32_t t, uint32_t vol) { return t <= tv && tv < t + vol; };
+    int64_t c = 0;
+    for (int i = threadIdx.x; i + 1 < len; i += T) {
+        const int a = path[i], b = path[i + 1];
+        const TNum na = rec_num(sp.rec, a), nb = rec_num(sp.rec, b);
+        const uint32_t ta = na.tin, va = na.vol, tb = nb.tin, vb = nb.vol;
+        const int32_t pa = na.par, pb = nb.par;
+        const bool up_a = anc_u(ta, va) && !anc_v(ta, va), up_b = anc_u(tb, vb) && !anc_v(tb, vb);
+        const bool dn_a = anc_v(ta, va) && !anc_u(ta, va), dn_b = anc_v(tb, vb) && !anc_u(tb, vb);
+        if ((up_a && pa == b) || (dn_b && pb == a)) c += 1;
+        else if ((up_b && pb == a) || (dn_a && pa == b)) c -= 1;
+    }
+    return c;
+}
+
+// Number of graph edges {x, y} that join the two trees left when the tree
+// edge {cut_u, cut_v} is removed (the side away from the root is Sub(tau, c)
+// with c the child endpoint; membership from the tree numbering).  With
+// relink, also cut-link (section 4.2): edge number j of them, in the order
+// (x ascending, row order, x < y), with j drawn by Philox on counter
+// (slot, serial, ISM_CTR_LO, ISM_CTR_HI), joins the two parts; the path from
+// its inner endpoint up to c is reversed so the tree stays rooted at r.
+// The counts of each 64 rows stay in grp (free after the numbering), so that
+// the drawn edge's rows are found without a second pass over the edges.
+template <int T>
+__device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const RunParams &rp, int32_t slot,
+                                  int idx, TreeShared<T> &sh) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int n = g.n;
+    const int a = rp.cut_u, b = rp.cut_v;
+    const int32_t pa = rec_parent(sp.rec, a);
+    const int32_t pb = rec_parent(sp.rec, b);
+    const int c = pa == b ? a : (pb == a ? b : -1);
+    if (c < 0) {
+        report_error(rp.ctl, DEV_BADTREE, idx);
+        return 0;
+    }
+    const TNum nc = rec_num(sp.rec, c);
+    const uint32_t lo = nc.tin, hi = nc.tin + nc.vol;
+    auto inside = [&](int x) {
+        const uint32_t t = rec_tin(sp.rec, x);
+        return lo <= t && t < hi;
+    };
+    auto row_count = [&](int x, bool ix) {
+        int64_t k = 0;
+        for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
+            const int y = g.adj[e];
+            if (y > x && inside(y) != ix) ++k;
+        }
+        return k;
+    };
+    const int nchunk = (n + WAVE - 1) / WAVE;
+    int64_t cnt = 0;
+    for (int ch = threadIdx.x / WAVE; ch < nchunk; ch += T / WAVE) {
+        const int x = ch * WAVE + lane;
+        const int64_t k = x < n ? row_count(x, inside(x)) : 0;
+        cnt += k;
+        const int64_t all = wave_sum(k);
+        if (lane == 0) astore(&sp.grp[ch], (int32_t)all);
+    }
+    const int64_t total = block_sum<T>(cnt, sh);
+    if (!rp.relink) return total;
+    if (total <= 0) {
+        report_error(rp.ctl, DEV_BADTREE, idx);
+        return 0;
+    }
+    __syncthreads();
+    if (threadIdx.x >= WAVE) return total;
+    const int64_t j = arrow_slot(rp.seed, ((uint64_t)ISM_CTR_HI << 32) | ISM_CTR_LO, rp.serial, (uint32_t)slot,
+                                 (uint32_t)total);
+    auto scan = [&](int64_t k) {
+        for (int d = 1; d < WAVE; d <<= 1) {
+            const int64_t t = __shfl_up(k, d);
+            if (lane >= d) k += t;
+        }
+        return k;
+    };
+    // the 64 rows that hold edge j, and the edges before them
+    int64_t base = 0;
+    int chunk = -1;
+    for (int c0 = 0; c0 < nchunk; c0 += WAVE) {
+        const int64_t k = c0 + lane < nchunk ? (int64_t)aload(&sp.grp[c0 + lane]) : 0;
+        const int64_t incl = scan(k);
+        const uint64_t past = __ballot(base + incl > j);
+        if (past != 0ull) {
+            const int l = __ffsll((unsigned long long)past) - 1;
+            chunk = c0 + l;
+            base += __shfl(incl - k, l);
+            break;
+        }
+        base += __shfl(incl, WAVE - 1);
+    }
+    if (chunk < 0) {
+        report_error(rp.ctl, DEV_BADTREE, idx);
+        return total;
+    }
+    const int x = chunk * WAVE + lane;
+    const bool ix = x < n && inside(x);
+    const int64_t k = x < n ? row_count(x, ix) : 0;
+    const int64_t incl = scan(k);
+    if (k > 0 && base + incl - k <= j && j < base + incl) {
+        int64_t r = j - (base + incl - k);
+        int y = -1;
+        for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
+            const int z = g.adj[e];
+            if (z > x && inside(z) != ix) {
+                if (r == 0) { y = z; break; }
+                --r;
+            }
+        }
+        if (y < 0) {
+            report_error(rp.ctl, DEV_BADTREE, idx);
+        } else {
+            const int xi = ix ? x : y, yo = ix ? y : x;
+            int32_t *out = rp.parents_mut + (size_t)slot * (size_t)n;
+            int32_t prev = yo, z = xi;
+            for (int guard = 0; guard <= n; ++guard) {
+                const int32_t nz = rec_parent(sp.rec, z);
+                out[z] = prev;
+                if (z == c) break;
+                if (nz < 0 || nz >= n) {  // c is an ancestor of xi: not reached
+                    report_error(rp.ctl, DEV_BADTREE, idx);
+                    break;
+                }
+                prev = z;
+                z = nz;
+            }
+        }
+    }
+    return total;
+}
+
+// The per-slot arrays of workgroup blockIdx.x, each `stride` vertices long.
+__device__ __forceinline__ SlotPtrs slot_ptrs(const SlotDev &sd, size_t stride) {
+    SlotPtrs sp;
+    const size_t b = (size_t)blockIdx.x;
+    unsigned char *st = sd.state + b * (size_t)state_bytes((int64_t)stride);
+    sp.state = st;
+    sp.stride = stride;
+    sp.queue = sd.queue + b * (size_t)sd.chains;
+    sp.cstart = sd.cstart + b * (size_t)sd.chains;
+    sp.rec = sd.rec ? reinterpret_cast<uint64_t *>(sd.rec) + 2 * b * stride : nullptr;
+    // the numbering's arrays reuse the sampler's block (dead once the parents are in rec)
+    sp.ord = sd.rec ? reinterpret_cast<int4 *>(st) : nullptr;
+    sp.grp = sd.rec ? reinterpret_cast<int32_t *>(st + 16 * stride) : nullptr;
+    sp.fen = sd.fen ? sd.fen + b * (size_t)sd.fen_len : nullptr;
+    return sp;
+}
+
+__device__ __forceinline__ bool stopped(const int32_t *ctl) {
+    return __hip_atomic_load(const_cast<int32_t *>(&ctl[1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+// The next work item for the calling workgroup (one atomic per workgroup), or
+// INT32_MAX once an error was recorded.  The same value in every thread, as a
+// scalar; it is a barrier of the workgroup.
+template <int T>
+__device__ __forceinline__ int next_item(int32_t *ctl, TreeShared<T> &sh) {
+    int idx = 0;
+    __syncthreads();  // the LDS of the item before is free
+    if (threadIdx.x == 0) {
+        idx = __hip_atomic_fetch_add(&ctl[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (stopped(ctl)) idx = INT32_MAX;
+    }
+    if constexpr (T > WAVE) {
+        if (threadIdx.x == 0) sh.item = idx;
+        __syncthreads();
+        idx = sh.item;
+    }
+    return __builtin_amdgcn_readfirstlane(idx);
+}
+
+// A tree of graph g (work item idx; its parents by parent_of(v), checked here)
+// through its record, its numbering and its value: f, the path current
+// (RUN_CURRENT) or the crossing edges (RUN_CROSS), into f_out[idx].
+template <int T, typename ParentOf>
+__device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<T> &sh, SweepItem *scratch,
+                              const RunParams &rp, int64_t fen_len, int idx, size_t row, ParentOf parent_of) {
+    const int tid = threadIdx.x;
+    if (tid == 0) sh.bad = 0;
+    // parent and degree into each vertex's tree record; its volume word starts at deg(v)
+    bool bad = false;
+    for (int b = 0; b < g.n; b += T * NBS) {
+        int32_t p[NBS];
+#pragma unroll
+        for (int k = 0; k < NBS; ++k) {
+            const int v = b + k * T + tid;
+            p[k] = v < g.n && v != g.root ? parent_of(v) : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < NBS; ++k) {
+            const int v = b + k * T + tid;
+            if (v >= g.n) continue;
+            if (v != g.root && (p[k] < 0 || p[k] >= g.n || p[k] == v)) { bad = true; p[k] = g.root; }
+            const uint64_t d = degree(g, v);
+            astore(&sp.rec[2 * (size_t)v], d);
+            astore(&sp.rec[2 * (size_t)v + 1], (uint64_t)(uint32_t)p[k] | (d << 32));
+        }
+    }
+    __syncthreads();
+    if (bad) sh.bad = 1;  // (read after the numbering's barriers)
+    bool ok = tree_numbering<T>(g, sp, sh);
+    if (sh.bad) ok = false;
+    int64_t f = 0;
+    if (!ok) {
+        // (the call fails; nothing is evaluated)
+    } else if (rp.mode == RUN_CROSS) {
+        f = crossing_edges<T>(g, sp, rp, (int32_t)row, idx, sh);
+    } else if (rp.mode == RUN_CURRENT) {
+        f = block_sum<T>(path_current<T>(sp, rp.path, rp.path_len), sh);
+    } else if (rp.traversal == 2) {
+        f = block_sum<T>(f_sweep<T>(g, sp, fen_len, scratch, sh), sh);
+    } else {
+        f = block_sum<T>(f_walk<T>(g, sp), sh);
+    }
+    if (tid == 0) {
+        if (!ok) report_error(rp.ctl, DEV_BADTREE, idx);
+        rp.f_out[idx] = f;
+    }
+}
+
+}  // namespace
+}  // namespace kc
