@@ -621,10 +621,12 @@ __device__ __forceinline__ SamplerWS sampler_ws(const SlotPtrs &sp) {
 }
 
 // The sampler and the sweep run one after the other: one LDS block serves both.
+constexpr int CHAIN_BITS = 1 << 16;
 template <int CH>
 union KernelShared {
     SamplerShared<CH> samp;
     SweepItem sweep[2 * WAVE];
+    uint32_t bitmap[CHAIN_BITS / 32];
 };
 
 // One sample s (work item idx) of graph g through the whole path in the
@@ -649,7 +651,7 @@ __device__ bool process_one(const GraphDev &g, const SlotPtrs &sp, KernelShared<
             if (co) co[v] = (uint32_t)(ar >> 32);
         }
     } else {
-        evaluate_tree<WAVE>(g, sp, tree, lds.sweep, rp, fen_len, idx, (size_t)idx,
+        evaluate_tree<WAVE>(g, sp, tree, lds.bitmap, min(CHAIN_BITS, path_bits(g.n)), rp, fen_len, idx, (size_t)idx,
                             [&](int v) { return (int32_t)(uint32_t)aload(&ws.arrow[v]); });
     }
     if (rp.steps_out && lane == 0) rp.steps_out[idx] = steps;

@@ -565,7 +565,7 @@ __device__ __forceinline__ bool process_frontier(const GraphDev &g, const SlotPt
             if (co) co[v] = aload(&ws.cnt[v]);
         }
     } else {
-        evaluate_tree<T>(g, sp, lds.tree, reinterpret_cast<SweepItem *>(dyn), rp, fen_len, idx, (size_t)idx, parent_of);
+        evaluate_tree<T>(g, sp, lds.tree, dyn, path_bits(g.n), rp, fen_len, idx, (size_t)idx, parent_of);
     }
     if (threadIdx.x == 0) {
         if (rp.steps_out) rp.steps_out[idx] = steps;
@@ -629,7 +629,7 @@ __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev s
         if (idx >= rp.count) break;
         const size_t row = rp.rows ? (size_t)rp.rows[idx] : (size_t)idx;
         const int32_t *par = rp.parents_in + row * (size_t)g.n;
-        evaluate_tree<T>(g, sp, tree, reinterpret_cast<SweepItem *>(dyn_words), rp, sd.fen_len, idx, row, [&](int v) { return par[v]; });
+        evaluate_tree<T>(g, sp, tree, dyn_words, path_bits(g.n), rp, sd.fen_len, idx, row, [&](int v) { return par[v]; });
         if (threadIdx.x == 0) {
             if (rp.steps_out) rp.steps_out[idx] = 0;
             if (rp.iters_out) rp.iters_out[idx] = 0;
@@ -641,11 +641,11 @@ __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev s
 }
 
 // Dynamic LDS of a workgroup of T threads: the words of the tree being sampled; in
-// their place, once its parents are read, the list of its evaluation.
+// their place, once its parents are read, the map or the list of its evaluation.
 template <int T>
 size_t dyn_lds(int route, int64_t n) {
     const size_t words = route == ROUTE_LDS ? 4 * (size_t)n : 0;
-    return (std::max(words, sweep_lds<T>()) + 15) / 16 * 16;
+    return (std::max({words, (size_t)path_bits(n) / 8, sweep_lds<T>()}) + 15) / 16 * 16;
 }
 
 template <typename K>

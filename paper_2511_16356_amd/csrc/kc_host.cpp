@@ -266,6 +266,7 @@ kc::GraphDev kc_host::graph_dev(const kc_graph *g) {
     gd.eoff = g->d_eoff;
     gd.elist = g->d_elist;
     gd.vrec = g->d_vrec;
+    gd.int0 = g->d_int0;
     gd.anc0 = g->d_anc0;
     gd.anc_depth = g->anc_depth;
     return gd;
@@ -563,7 +564,11 @@ kc_status prepare_graph(const std::vector<int64_t> &off, const std::vector<int32
     // 8 levels with -1 past the root, so the per-tree walk loads them without following p0
     pg->anc_depth = depth0 <= 4 ? 4 : depth0 <= 8 ? 8 : 0;
     pg->anc0.clear();
+    pg->int0.clear();
     if (pg->anc_depth > 0) {
+        pg->int0.assign(((size_t)n + 31) / 32, 0u);
+        for (int64_t v = 0; v < n; ++v)
+            if (v != root) pg->int0[(size_t)p0[(size_t)v] / 32] |= 1u << (p0[(size_t)v] & 31);
         const int32_t D = pg->anc_depth;
         pg->anc0.assign((size_t)D * (size_t)n, -1);
         for (int64_t v = 0; v < n; ++v) {
@@ -590,7 +595,9 @@ kc_status prepare_graph(const std::vector<int64_t> &off, const std::vector<int32
 void free_graph_arrays(kc_graph *g) {
     dev_free(g->d_vrec);
     dev_free(g->d_anc0);
+    dev_free(g->d_int0);
     g->d_anc0 = nullptr;
+    g->d_int0 = nullptr;
     g->anc_depth = 0;
     dev_free(g->d_off); dev_free(g->d_adj); dev_free(g->d_p0); dev_free(g->d_order);
     dev_free(g->d_pre0); dev_free(g->d_out0); dev_free(g->d_eoff); dev_free(g->d_elist);
@@ -636,6 +643,7 @@ kc_status rebuild_graph(kc_graph *g, int32_t root, hipStream_t stream) {
     if (e == hipSuccess) e = up(&g->d_elist, pg.elist.data(), pg.elist.size());
     if (e == hipSuccess) e = up(&g->d_vrec, reinterpret_cast<const int4 *>(pg.vrec.data()), (size_t)n * 2);
     if (e == hipSuccess && pg.anc_depth > 0) e = up(&g->d_anc0, pg.anc0.data(), pg.anc0.size());
+    if (e == hipSuccess && pg.anc_depth > 0) e = up(&g->d_int0, pg.int0.data(), pg.int0.size());
     g->anc_depth = pg.anc_depth;
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess)

@@ -14,6 +14,7 @@
 struct PreparedGraph {
     int32_t root = -1, depth0 = 0, nblk = 0, anc_depth = 0;
     std::vector<int32_t> order, p0, pre0, out0, eoff, elist, vrec, anc0;
+    std::vector<uint32_t> int0;
 };
 
 struct kc_graph {
@@ -54,6 +55,7 @@ struct kc_graph {
     int32_t *d_out0 = nullptr, *d_eoff = nullptr, *d_elist = nullptr;
     int4 *d_vrec = nullptr;
     int32_t *d_anc0 = nullptr;
+    uint32_t *d_int0 = nullptr;
     int32_t anc_depth = 0;
     // workspace
     int ws_slots = 0;

@@ -22,6 +22,7 @@ struct GraphDev {
     const int32_t *elist; //          subtree started before the block and ends in it
     const int4 *vrec;     // [2n]  32-byte record per vertex: {offset, degree, first six
                           //       neighbours (-1 past the degree)}
+    const uint32_t *int0; // [n / 32] bit per vertex: it has a child in tau0; null without anc0
     const int32_t *anc0;  // [anc_depth * n] level-major tau0 ancestors: anc0[i n + v] is the
                           //       (i+1)-th ancestor of v, -1 past the root; null if tau0 is deep
     int32_t anc_depth;    //       levels in anc0 (4 or 8), 0 without the table
@@ -67,6 +68,13 @@ struct BatchJob {
 // state block.
 enum Route { ROUTE_CHAINS = 0, ROUTE_LDS = 1, ROUTE_GLOBAL = 2 };
 constexpr int64_t LDS_MAX_N = (1 << 15) - 1;  // a word holds two vertices and two flags
+// Bits of the map of tau0 vertices that the evaluation on a shallow tau0 keeps in
+// LDS: a power of two, one bit per vertex up to 2^19.
+__host__ __device__ inline int path_bits(int64_t n) {
+    int b = 32;
+    while (b < n && b < (1 << 19)) b <<= 1;
+    return b;
+}
 constexpr int BATCH_MAX = 8;  // graphs in one batch launch
 
 // Kernel arguments of a batch launch: k jobs; job j owns work items

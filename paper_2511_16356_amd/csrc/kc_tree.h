@@ -205,11 +205,15 @@ __device__ __forceinline__ Items items_of(const GraphDev &g, const uint64_t *rec
     }
     return it;
 }
+struct PathShared {
+    int32_t n_mark, n_left, n_user, extra, bad;
+};
 // Scratch of the tree code in LDS.
 template <int T>
 struct TreeShared {
     int32_t count[4], take[4];  // rotating counters of the bottom-up rounds
     int32_t leaves, bad, item;
+    PathShared paths;
     int64_t red[T / WAVE];
 };
 
@@ -406,85 +410,13 @@ __device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared
     return true;
 }
 
-// f by walking each vertex's tau0 ancestors (Theorem 3.4 as a sum over
+// f by walking each vertex's tau0 ancestors along p0 (Theorem 3.4 as a sum over
 // vertices u of d(u) q(u): every tau0 edge x -> p0(x) on u's tau0 path adds
 // 2m - vol(x) when tau uses it in the same direction and x is a tau ancestor
 // of u, and subtracts 2m - vol(p0(x)) when tau uses it the other way and
-// p0(x) (not the root) is a tau ancestor of u).
-//
-// With the graph's ancestor table (shallow tau0: anc0[i n + u] is the
-// (i+1)-th tau0 ancestor of u, -1 past the root) every record a vertex needs
-// is loaded at once; otherwise the walk follows p0 step by step.
-
-template <int D>
-__device__ __forceinline__ int64_t q_of_table(const GraphDev &g, const SlotPtrs &sp, int u) {
-    const int root = g.root;
-    const int64_t two_m = g.two_m;
-    const size_t n = (size_t)g.n;
-    int z[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) z[i] = g.anc0[(size_t)i * n + (size_t)u];
-    TNum nz[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-        nz[i] = TNum{0u, 0u, -2};
-        if (z[i] >= 0 && z[i] != root) nz[i] = rec_num(sp.rec, z[i]);
-    }
-    const TNum nu = rec_num(sp.rec, u);
-    const uint32_t tu = nu.tin;
-    int x = u;
-    TNum nx = nu;
-    int64_t q = 0;
-    bool go = u != root;
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-        if (go && z[i] >= 0) {
-            if (nx.par == z[i]) {
-                if (nx.tin <= tu && tu < nx.tin + nx.vol) q += two_m - (int64_t)nx.vol;
-            }
-            if (z[i] == root) {
-                go = false;
-            } else {
-                if (nz[i].par == x) {
-                    if (nz[i].tin <= tu && tu < nz[i].tin + nz[i].vol) q -= two_m - (int64_t)nz[i].vol;
-                }
-                x = z[i];
-                nx = nz[i];
-            }
-        }
-    }
-    return q;
-}
-
-// U vertices per lane and step (their loads in flight together); the deeper
-// table takes one, to keep the kernel's register count at its occupancy (a
-// table of more than 8 levels would not fit it, so deeper trees follow p0).
-template <int T, int D, int U>
-__device__ int64_t f_walk_table(const GraphDev &g, const SlotPtrs &sp) {
-    const int tid = threadIdx.x;
-    const int n = g.n;
-    int64_t acc = 0;
-    for (int b = 0; b < n; b += U * T) {
-        int64_t q[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int u = b + k * T + tid;
-            q[k] = u < n ? q_of_table<D>(g, sp, u) : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int u = b + k * T + tid;
-            if (u < n) acc += (int64_t)degree(g, u) * q[k];
-        }
-    }
-    return acc;
-}
-
-// (each thread's share of f)
+// p0(x) (not the root) is a tau ancestor of u).  Each thread's share of f.
 template <int T>
 __device__ int64_t f_walk(const GraphDev &g, const SlotPtrs &sp) {
-    if (g.anc0 && g.anc_depth <= 4) return f_walk_table<T, 4, 2>(g, sp);
-    if (g.anc0 && g.anc_depth <= 8) return f_walk_table<T, 8, 1>(g, sp);
     const int n = g.n, root = g.root;
     const int64_t two_m = g.two_m;
     int64_t acc = 0;
@@ -746,6 +678,281 @@ __device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const R
     return total;
 }
 
+// f on a shallow reference tree (the tau0-ancestor table, depth(tau0) <= 8),
+// without volumes or a numbering.
+//
+// Write Theorem 3.4's sum as f = sum_x c(x) (2m - vol(x)): c(x) is the weight of
+// the vertices u whose q has the term 2m - vol(x).  u = x always has it if tau uses
+// x -> p0(x) (FWD); a tau0 descendant u of x has it if x is also a tau ancestor of
+// u, and -1 times that of z = p0(x) if tau uses z -> x and z is a tau ancestor of u.
+// The second kind needs an internal vertex x of tau0 whose tau0 edge is in tau; on
+// a power-law graph those are hubs with many other edges, so that few u (0 to 3%
+// there) have one on their tau0 path: only those are looked at one by one.
+// And sum_x c(x) vol(x) = sum_w d(w) C(w) with C(w) the sum of c along w's tau path,
+// so the volumes are not needed either: C runs down the tree.  A vertex climbs
+// until it meets one whose path sum is known and writes those of the vertices it
+// passed; nearly all climb one step.  Per vertex that is one random line (the
+// parent's record) and some path lines, where the volumes and the numbering take
+// about six (child count, carry, tin and record, most of them written back).
+//
+// Records: rec[2v] = parent | flags | deg << 32, rec[2v + 1] = the path sum of the
+// first kind of c (at most 2m < 2^32) << 32 | the nearest MARKed vertex on v's
+// path (itself included), all ones while unknown.  MARKed are the x and z above,
+// so that "t is a tau ancestor of u" is a walk along the marks of u's path.
+constexpr uint32_t P_FWD = 1u << 31, P_MARK = 1u << 30, P_PAR = P_MARK - 1;
+constexpr uint32_t P_NONE = 0xFFFFFFFFu;
+constexpr uint64_t P_UNKNOWN = ~0ull;
+constexpr int64_t PATHS_MAX_N = 1 << 30;  // (a parent and two flags in 32 bits)
+
+__device__ __forceinline__ uint32_t next_mark(const uint64_t *rec, uint32_t y) {
+    const uint32_t p = (uint32_t)aload(&rec[2 * (size_t)y]) & P_PAR;
+    return (uint32_t)aload(&rec[2 * (size_t)p + 1]);
+}
+
+// bitmap: nbits (a power of two) bits of LDS; a vertex's bit is that of its index
+// modulo nbits (a bit too many costs a look, no error).  Returns false if the
+// parents do not form a tree rooted at r; else *f is the thread's share of f.
+template <int T, int D, typename ParentOf>
+__device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, uint32_t *bitmap, int nbits,
+                        ParentOf parent_of, int64_t *f) {
+    const int tid = threadIdx.x, n = g.n;
+    const int64_t two_m = g.two_m;
+    uint64_t *rec = sp.rec;
+    // the slot's block, free once the parents are read: the second kind of c and its
+    // path sums (at marked vertices), the vertices with terms of that kind, the marked
+    int64_t *extra = reinterpret_cast<int64_t *>(sp.state);
+    int64_t *extra_sum = reinterpret_cast<int64_t *>(sp.state + 8 * sp.stride);
+    int32_t *left = reinterpret_cast<int32_t *>(sp.state + 8 * sp.stride);  // (before those)
+    int32_t *user = reinterpret_cast<int32_t *>(sp.state + 8 * sp.stride);
+    int32_t *marked = reinterpret_cast<int32_t *>(sp.state + 16 * sp.stride);
+    auto tau0_parent = [&](int v) { return g.anc0[v]; };
+    if (tid == 0) sh.n_mark = sh.n_left = sh.n_user = sh.extra = sh.bad = 0;
+    __syncthreads();
+    // ---- the records
+    constexpr int U = 4;
+    for (int b = 0; b < n; b += T * U) {
+        int32_t p[U], z[U], pz[U];
+        uint32_t d[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = b + k * T + tid;
+            p[k] = v < n && v != g.root ? parent_of(v) : g.root;
+            d[k] = v < n ? degree(g, v) : 0;
+            z[k] = v < n ? tau0_parent(v) : -1;
+            if (v < n && v != g.root && (p[k] < 0 || p[k] >= n || p[k] == v)) {
+                sh.bad = 1;
+                p[k] = g.root;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) pz[k] = tau0_parent(p[k]);
+        int c = 0;
+        uint32_t marks = 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = b + k * T + tid;
+            const bool inner = v < n && v != g.root;
+            const bool fwd = inner && p[k] == z[k];
+            const bool mark = inner && ((fwd && (g.int0[v >> 5] >> (v & 31) & 1u)) || pz[k] == v);
+            if (v < n) {
+                astore(&rec[2 * (size_t)v], (uint64_t)((uint32_t)p[k] | (fwd ? P_FWD : 0u) | (mark ? P_MARK : 0u)) |
+                                                (uint64_t)d[k] << 32);
+                astore(&rec[2 * (size_t)v + 1], v == g.root ? (uint64_t)P_NONE : P_UNKNOWN);
+            }
+            if (mark) marks |= 1u << k;
+            c += __popcll(__ballot(mark));
+        }
+        int at = take_shared(&sh.n_mark, c);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const uint64_t m = __ballot(marks >> k & 1u);
+            if (marks >> k & 1u) marked[at + rank_in(m)] = b + k * T + tid;
+            at += __popcll(m);
+        }
+    }
+    __syncthreads();
+    const int n_mark = sh.n_mark;
+    for (int i = tid; i < nbits / 32; i += T) bitmap[i] = 0;  // (its memory held the parents, on one route)
+    __syncthreads();
+    auto set_bit = [&](int v) {
+        const int k = v & (nbits - 1);
+        (void)afetch_or(&bitmap[k >> 5], 1u << (k & 31));
+    };
+    for (int i = tid; i < n_mark; i += T) {
+        const int u = marked[i];
+        const uint32_t node = (uint32_t)aload(&rec[2 * (size_t)u]);
+        const int p = (int)(node & P_PAR);
+        if (node & P_FWD) set_bit(u);
+        if (tau0_parent(p) == u) set_bit(p);
+        extra[u] = 0;
+    }
+    // ---- the path sums.  A few thousand vertices climb as far as it takes, which writes the
+    // trunk of the tree; the others climb WALK steps at most, and those not done, once more
+    constexpr int SEED = 4096, SHORT = 8;
+    const int4 *rec4 = reinterpret_cast<const int4 *>(rec);
+    int64_t acc = 0;
+    auto climb = [&](auto wu, auto is_short, int at, int count, auto vertex) __attribute__((always_inline)) {
+        constexpr int WU = decltype(wu)::value;
+        constexpr bool CUT = decltype(is_short)::value;
+        int v[WU], x[WU], mark[WU];
+        uint32_t sum[WU], la[WU], own[WU], dv[WU], up[WU], len[WU];
+        int4 r[WU];
+        bool go[WU];
+#pragma unroll
+        for (int k = 0; k < WU; ++k) {
+            const int i = at + k * T;
+            v[k] = i < count ? vertex(i) : -1;
+            x[k] = v[k] >= 0 ? v[k] : g.root;
+            sum[k] = 0;
+            la[k] = P_NONE;
+            len[k] = 0;
+            mark[k] = -1;
+            own[k] = dv[k] = up[k] = 0;
+        }
+        uint32_t step = 0;
+        uint64_t any;
+        do {
+            any = 0;
+#pragma unroll
+            for (int k = 0; k < WU; ++k) r[k] = rec4[x[k]];
+#pragma unroll
+            for (int k = 0; k < WU; ++k) {
+                const uint32_t node = (uint32_t)r[k].x;
+                const uint32_t c = node & P_FWD ? (uint32_t)r[k].y : 0u;
+                if (step == 0) {
+                    own[k] = c;
+                    dv[k] = (uint32_t)r[k].y;
+                    up[k] = node & P_PAR;
+                }
+                go[k] = (uint32_t)r[k].w == P_NONE;  // (a path sum is less)
+                if (!CUT && go[k] && x[k] == mark[k]) {  // Brent's cycle finding: not a tree
+                    sh.bad = 1;
+                    go[k] = false;
+                }
+                if (!CUT && (step & (step - 1)) == 0) mark[k] = x[k];
+                sum[k] += go[k] ? c : 0u;
+                la[k] = go[k] && la[k] == P_NONE && (node & P_MARK) ? (uint32_t)x[k] : la[k];
+                x[k] = go[k] ? (int)(node & P_PAR) : x[k];
+                len[k] += go[k] ? 1u : 0u;
+                any |= __builtin_amdgcn_ballot_w64(go[k]);
+            }
+        } while ((!CUT || step < SHORT) && ++step && any != 0ull && (CUT || sh.bad == 0));
+#pragma unroll
+        for (int k = 0; k < WU; ++k) {
+            if (v[k] < 0) continue;
+            if (go[k]) {
+                if (CUT) left[afetch_add(&sh.n_left, 1)] = v[k];
+                continue;
+            }
+            if ((uint32_t)r[k].w == P_NONE) continue;  // not a tree
+            const uint32_t total = sum[k] + (uint32_t)r[k].w;
+            uint32_t l = la[k] != P_NONE ? la[k] : (uint32_t)r[k].z;
+            acc += (int64_t)dv[k] * ((own[k] != 0 ? two_m : 0) - (int64_t)total);
+            if (len[k] > 0) astore(&rec[2 * (size_t)v[k] + 1], (uint64_t)total << 32 | l);
+            if (len[k] > 1) {  // the vertices passed: their sums, and the first mark from each on
+                uint32_t rest = total - own[k];
+                bool look = l == (uint32_t)v[k];
+                for (int y = (int)up[k]; y != x[k];) {
+                    if (look) {
+                        int4 q = rec4[y];
+                        for (int a = y; (l = (uint32_t)a, !((uint32_t)q.x & P_MARK));) {
+                            if ((uint32_t)q.w != P_NONE) { l = (uint32_t)q.z; break; }
+                            a = (int)((uint32_t)q.x & P_PAR);
+                            q = rec4[a];
+                        }
+                        look = false;
+                    }
+                    const int4 q = rec4[y];
+                    astore(&rec[2 * (size_t)y + 1], (uint64_t)rest << 32 | l);
+                    rest -= (uint32_t)q.x & P_FWD ? (uint32_t)q.y : 0u;
+                    look = l == (uint32_t)y;
+                    y = (int)((uint32_t)q.x & P_PAR);
+                }
+            }
+        }
+    };
+    constexpr auto one = std::integral_constant<int, 1>{};
+    constexpr auto four = std::integral_constant<int, 4>{};
+    const int seed = min(n, SEED);
+    for (int at = tid; at - tid < seed; at += T) climb(one, std::false_type{}, at, seed, [](int i) { return i; });
+    for (int at = seed + tid; at - tid < n; at += 4 * T) climb(four, std::true_type{}, at, n, [](int i) { return i; });
+    __syncthreads();
+    const int n_left = sh.n_left;
+    for (int at = tid; at - tid < n_left; at += T)
+        climb(one, std::false_type{}, at, n_left, [&](int i) { return left[i]; });
+    __syncthreads();
+    if (sh.bad) return false;  // (uniform)
+    if (n_mark > 0) {
+        // ---- the vertices with a tau0 ancestor in the map
+        for (int b = 0; b < n; b += T) {
+            const int u = b + tid;
+            bool hit = false;
+            if (u < n) {
+                int z[D];
+#pragma unroll
+                for (int i = 0; i < D; ++i) z[i] = g.anc0[(size_t)i * n + u];
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const int k = z[i] & (nbits - 1);
+                    hit = hit || (z[i] >= 0 && (bitmap[k >> 5] >> (k & 31) & 1u));
+                }
+            }
+            const uint64_t m = __ballot(hit);
+            const int at = take_shared(&sh.n_user, __popcll(m));
+            if (hit) user[at + rank_in(m)] = u;
+        }
+        __syncthreads();
+        const int n_user = sh.n_user;
+        for (int i = tid; i < n_user; i += T) {
+            const int u = user[i];
+            const int4 ru = rec4[u];
+            const int64_t d = (int64_t)(uint32_t)ru.y;
+            // the vertices whose terms u has, if they are tau ancestors of u
+            uint32_t plus[D], minus[D];
+            int z[D];
+            bool some = false;
+#pragma unroll
+            for (int l = 0; l < D; ++l) z[l] = g.anc0[(size_t)l * n + u];
+            uint32_t node[D];
+#pragma unroll
+            for (int l = 0; l < D; ++l) node[l] = z[l] >= 0 ? (uint32_t)rec4[z[l]].x : 0u;
+#pragma unroll
+            for (int l = 0; l < D; ++l) {
+                plus[l] = z[l] >= 0 && (node[l] & P_FWD) ? (uint32_t)z[l] : P_NONE;
+                minus[l] = P_NONE;
+                if (l > 0 && z[l] >= 0 && z[l] != g.root && (int)(node[l] & P_PAR) == z[l - 1]) minus[l] = (uint32_t)z[l];
+                some = some || plus[l] != P_NONE || minus[l] != P_NONE;
+            }
+            if (!some) continue;
+            for (uint32_t y = (uint32_t)ru.z; y != P_NONE; y = next_mark(rec, y)) {
+                int64_t t = 0;
+#pragma unroll
+                for (int l = 0; l < D; ++l) t += (plus[l] == y ? 1 : 0) - (minus[l] == y ? 1 : 0);
+                if (t != 0) {
+                    acc += t * d * two_m;
+                    (void)afetch_add(&extra[y], t * d);
+                    sh.extra = 1;
+                }
+            }
+        }
+        __syncthreads();
+        if (sh.extra) {  // (uniform)
+            for (int i = tid; i < n_mark; i += T) {
+                int64_t e = 0;
+                for (uint32_t y = (uint32_t)marked[i]; y != P_NONE; y = next_mark(rec, y)) e += aload(&extra[y]);
+                extra_sum[marked[i]] = e;
+            }
+            __syncthreads();
+            for (int w = tid; w < n; w += T) {
+                const int4 r = rec4[w];
+                if ((uint32_t)r.z != P_NONE) acc -= (int64_t)(uint32_t)r.y * extra_sum[r.z];
+            }
+        }
+    }
+    *f = acc;
+    return true;
+}
+
 // The per-slot arrays of workgroup blockIdx.x, each `stride` vertices long.
 __device__ __forceinline__ SlotPtrs slot_ptrs(const SlotDev &sd, size_t stride) {
     SlotPtrs sp;
@@ -789,9 +996,21 @@ __device__ __forceinline__ int next_item(int32_t *ctl, TreeShared<T> &sh) {
 // through its record, its numbering and its value: f, the path current
 // (RUN_CURRENT) or the crossing edges (RUN_CROSS), into f_out[idx].
 template <int T, typename ParentOf>
-__device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<T> &sh, SweepItem *scratch,
-                              const RunParams &rp, int64_t fen_len, int idx, size_t row, ParentOf parent_of) {
+__device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<T> &sh, uint32_t *scratch,
+                              int nbits, const RunParams &rp, int64_t fen_len, int idx,
+                              size_t row, ParentOf parent_of) {
     const int tid = threadIdx.x;
+    if (rp.mode <= RUN_EVALUATE && rp.traversal != 2 && g.anc0 && g.n < PATHS_MAX_N) {
+        int64_t part = 0;
+        const bool ok = g.anc_depth <= 4 ? f_paths<T, 4>(g, sp, sh.paths, scratch, nbits, parent_of, &part)
+                                         : f_paths<T, 8>(g, sp, sh.paths, scratch, nbits, parent_of, &part);
+        const int64_t f = block_sum<T>(part, sh);
+        if (tid == 0) {
+            if (!ok) report_error(rp.ctl, DEV_BADTREE, idx);
+            rp.f_out[idx] = f;
+        }
+        return;
+    }
     if (tid == 0) sh.bad = 0;
     // parent and degree into each vertex's tree record; its volume word starts at deg(v)
     bool bad = false;
@@ -824,7 +1043,7 @@ __device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<
     } else if (rp.mode == RUN_CURRENT) {
         f = block_sum<T>(path_current<T>(sp, rp.path, rp.path_len), sh);
     } else if (rp.traversal == 2) {
-        f = block_sum<T>(f_sweep<T>(g, sp, fen_len, scratch, sh), sh);
+        f = block_sum<T>(f_sweep<T>(g, sp, fen_len, reinterpret_cast<SweepItem *>(scratch), sh), sh);
     } else {
         f = block_sum<T>(f_walk<T>(g, sp), sh);
     }
