@@ -29,6 +29,8 @@
 // relaxed atomics (L2-coherent on gfx950) ordered by workgroup fences; every
 // lane of a sample is in the same wavefront.
 
+#include <algorithm>
+
 #include "kc_tree.h"
 
 namespace kc {
@@ -651,7 +653,7 @@ __device__ bool process_one(const GraphDev &g, const SlotPtrs &sp, KernelShared<
             if (co) co[v] = (uint32_t)(ar >> 32);
         }
     } else {
-        evaluate_tree<WAVE>(g, sp, tree, lds.bitmap, min(CHAIN_BITS, path_bits(g.n)), rp, fen_len, idx, (size_t)idx,
+        evaluate_tree<WAVE>(g, sp, tree, lds.bitmap, min(CHAIN_BITS, path_bits(g.n)), rp, fen_len, idx,
                             [&](int v) { return (int32_t)(uint32_t)aload(&ws.arrow[v]); });
     }
     if (rp.steps_out && lane == 0) rp.steps_out[idx] = steps;
@@ -736,6 +738,48 @@ __global__ void flag_trees_kernel(const int32_t *par, int32_t count, int64_t n, 
         const int32_t *row = par + t * n;
         if (row[u] == v || row[v] == u) flags[t] = 1;
     }
+}
+
+// The places of a path's vertices: pos[path[i]] = i, -1 elsewhere (two launches).
+__global__ void clear_pos_kernel(int32_t *pos, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        pos[i] = -1;
+}
+__global__ void set_pos_kernel(const int32_t *path, int32_t len, int32_t *pos) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x) pos[path[i]] = i;
+}
+
+// Signed count of the edges of a fixed u -> v path that a tree's own u -> v
+// path uses (+1 along the path's direction, -1 against it); its mean over
+// uniform spanning trees is the effective resistance R(u, v) (Kirchhoff: the
+// tree path's direction on an edge has mean equal to the unit current there,
+// and currents summed along any u -> v path give the potential difference).
+// The edges x -> p(x) from u up to the root count as the path runs along them,
+// those from v up the other way; the tree edges above both cancel, so the tree
+// needs no numbering (1.9 ms for 1,024 trees of 20,000 vertices with one).  Two
+// threads per tree, bound by the longer climb's dependent loads.
+__global__ void path_current_kernel(const int32_t *par, int32_t count, int64_t n, const int32_t *path, int32_t len,
+                                    const int32_t *pos, int64_t *c, int32_t *ctl) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, t = i >> 1;
+    int64_t sum = 0;
+    if (t < count) {
+        const int32_t *row = par + (int64_t)t * n;
+        int32_t x = (i & 1) ? path[len - 1] : path[0];
+        int64_t guard = 0;
+        for (int32_t p; (p = row[x]) >= 0 && p < n; x = p) {
+            const int32_t k = pos[x];
+            if (k >= 0) {
+                if (k + 1 < len && path[k + 1] == p) ++sum;
+                else if (k > 0 && path[k - 1] == p) --sum;
+            }
+            if (++guard > n) {
+                report_error(ctl, DEV_BADTREE, t);
+                break;
+            }
+        }
+    }
+    const int64_t other = __shfl_xor(sum, 1);
+    if (t < count && (i & 1) == 0) c[t] = sum - other;
 }
 
 // Trees drawn with u and v in the tree from the start (a two-tree forest
@@ -986,6 +1030,19 @@ hipError_t launch_link_cut(int32_t *par, const int32_t *rows, int32_t count, int
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(link_cut_kernel, dim3((count + 63) / 64), dim3(64), 0, stream, par, rows, count, n, u, v,
                        seed, serial, relink, d_out, ctl);
+    return hipGetLastError();
+}
+
+hipError_t launch_path_currents(const int32_t *par, int32_t count, int64_t n, const int32_t *path, int32_t len,
+                                int32_t *pos, int64_t *c, int32_t *ctl, hipStream_t stream) {
+    if (count <= 0 || len < 2) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(64), 0, stream, ctl);
+    hipLaunchKernelGGL(clear_pos_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)), dim3(256), 0, stream,
+                       pos, n);
+    hipLaunchKernelGGL(set_pos_kernel, dim3((unsigned)std::min<int64_t>((len + 255) / 256, 4096)), dim3(256), 0, stream,
+                       path, len, pos);
+    hipLaunchKernelGGL(path_current_kernel, dim3((unsigned)((2 * (int64_t)count + 63) / 64)), dim3(64), 0, stream, par,
+                       count, n, path, len, pos, c, ctl);
     return hipGetLastError();
 }
 

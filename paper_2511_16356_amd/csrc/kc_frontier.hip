@@ -565,7 +565,7 @@ __device__ __forceinline__ bool process_frontier(const GraphDev &g, const SlotPt
             if (co) co[v] = aload(&ws.cnt[v]);
         }
     } else {
-        evaluate_tree<T>(g, sp, lds.tree, dyn, path_bits(g.n), rp, fen_len, idx, (size_t)idx, parent_of);
+        evaluate_tree<T>(g, sp, lds.tree, dyn, path_bits(g.n), rp, fen_len, idx, parent_of);
     }
     if (threadIdx.x == 0) {
         if (rp.steps_out) rp.steps_out[idx] = steps;
@@ -618,7 +618,7 @@ __global__ void __launch_bounds__(T, FT_WAVES) frontier_batch_kernel(BatchArgs a
     }
 }
 
-// Trees the caller holds (RUN_EVALUATE, RUN_CURRENT, RUN_CROSS).
+// Trees the caller holds (RUN_EVALUATE, RUN_CROSS).
 template <int T>
 __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev sd, RunParams rp) {
     __shared__ TreeShared<T> tree;
@@ -629,7 +629,13 @@ __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev s
         if (idx >= rp.count) break;
         const size_t row = rp.rows ? (size_t)rp.rows[idx] : (size_t)idx;
         const int32_t *par = rp.parents_in + row * (size_t)g.n;
-        evaluate_tree<T>(g, sp, tree, dyn_words, path_bits(g.n), rp, sd.fen_len, idx, row, [&](int v) { return par[v]; });
+        if (rp.mode == RUN_CROSS) {
+            const int64_t d = crossing_edges<T>(g, sp, rp, par, (int32_t)row, idx, tree);
+            if (threadIdx.x == 0) rp.f_out[idx] = d;
+        } else {
+            evaluate_tree<T>(g, sp, tree, dyn_words, path_bits(g.n), rp, sd.fen_len, idx,
+                             [&](int v) { return par[v]; });
+        }
         if (threadIdx.x == 0) {
             if (rp.steps_out) rp.steps_out[idx] = 0;
             if (rp.iters_out) rp.iters_out[idx] = 0;

@@ -1342,25 +1342,21 @@ static void csr_without_edge(const std::vector<int64_t> &off, const std::vector<
 static kc_status path_currents(kc_graph *g, int32_t a, int32_t b, std::vector<int64_t> *c, hipStream_t stream) {
     const std::vector<int32_t> path = reference_path(g->h_off, g->h_adj, a, b);
     if (path.size() < 2) return fail(KC_ERR_DEVICE, "no path between %d and %d", a, b);
-    DevTmp<int32_t> d_path;
+    DevTmp<int32_t> d_path, d_pos;
     DevTmp<int64_t> d_c;
     HIP_TRY(d_path.alloc(path.size(), stream));
+    HIP_TRY(d_pos.alloc((size_t)g->n, stream));
     HIP_TRY(d_c.alloc((size_t)g->res_count, stream));
-    HIP_TRY(hipMemcpyAsync(d_path.p, path.data(), path.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-    kc::RunParams rp{};
-    rp.count = g->res_count;
-    rp.mode = kc::RUN_CURRENT;
-    rp.parents_in = g->d_res_par;
-    rp.f_out = d_c.p;
-    rp.path = d_path.p;
-    rp.path_len = (int32_t)path.size();
-    kc_status st = run_persistent(g, rp, stream);
     c->assign((size_t)g->res_count, 0);
-    if (st == KC_OK) {
-        const hipError_t e = hipMemcpy(c->data(), d_c.p, c->size() * sizeof(int64_t), hipMemcpyDeviceToHost);
-        if (e != hipSuccess) st = fail(KC_ERR_DEVICE, "copy failed: %s", hipGetErrorString(e));
-    }
-    return st;
+    HIP_TRY(hipMemcpyAsync(d_path.p, path.data(), path.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+    HIP_TRY(kc::launch_path_currents(g->d_res_par, g->res_count, g->n, d_path.p, (int32_t)path.size(), d_pos.p, d_c.p,
+                                     g->d_ctl, stream));
+    int32_t ctl[4] = {0, 0, 0, 0};
+    HIP_TRY(hipMemcpyAsync(ctl, g->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipMemcpyAsync(c->data(), d_c.p, c->size() * sizeof(int64_t), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    if (ctl[1] != 0) return fail(KC_ERR_INVALID, "resident tree %d is not a tree rooted at %d", ctl[2], g->root);
+    return KC_OK;
 }
 
 // One insertion (Algorithm 2, insertion case; Theorem 4.1).

@@ -86,7 +86,7 @@ struct BatchArgs {
     int64_t *f, *steps, *iters;
 };
 
-enum RunMode { RUN_SAMPLE = 0, RUN_ESTIMATE = 1, RUN_EVALUATE = 2, RUN_CURRENT = 3, RUN_CROSS = 4 };
+enum RunMode { RUN_SAMPLE = 0, RUN_ESTIMATE = 1, RUN_EVALUATE = 2, RUN_CROSS = 3 };
 
 // Counter words 2 and 3 of the Philox draw that picks a link-cut or cut-link
 // edge: (tree slot, update number, ISM_CTR_LO, ISM_CTR_HI), a counter no tree
@@ -114,8 +114,6 @@ struct RunParams {
     int64_t *progress;         // [slots] samples finished per workgroup (host-mapped), or null
     int32_t root_u = -1;       // RUN_SAMPLE: if root_u >= 0, u and v start in the tree instead of
     int32_t root_v = -1;       // the graph's root (a forest of two trees rooted at u and v)
-    const int32_t *path = nullptr;  // RUN_CURRENT: vertices of a u -> v path in the graph
-    int32_t path_len = 0;           //              number of vertices (>= 2)
     const int32_t *rows = nullptr;  // modes that read parents_in: tree idx is row rows[idx] (null: idx)
     int32_t *parents_mut = nullptr; // RUN_CROSS with relink: the same rows, rewritten in place
     int32_t cut_u = -1, cut_v = -1; // RUN_CROSS: the tree edge whose removal splits the tree
@@ -153,6 +151,10 @@ hipError_t launch_reroot(int32_t *par, int32_t count, int64_t n, int32_t u, int3
 hipError_t launch_link_cut(int32_t *par, const int32_t *rows, int32_t count, int64_t n, int32_t u, int32_t v,
                            uint64_t seed, uint32_t serial, int relink, int64_t *d_out, int32_t *ctl,
                            hipStream_t stream);
+// c[t] = the path current of tree t (count * n parents at par) along a u -> v path of
+// len vertices; pos: n int32 of scratch.
+hipError_t launch_path_currents(const int32_t *par, int32_t count, int64_t n, const int32_t *path, int32_t len,
+                                int32_t *pos, int64_t *c, int32_t *ctl, hipStream_t stream);
 hipError_t launch_flag_trees(const int32_t *par, int32_t count, int64_t n, const int32_t *eu,
                              const int32_t *ev, int32_t ne, uint8_t *flags, hipStream_t stream);
 // The frontier sampler's launches (routes other than ROUTE_CHAINS), and the

@@ -533,87 +533,89 @@ __device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_le
     return acc;
 }
 
-// Signed count of the edges of a fixed u -> v path that the tree's own u -> v
-// path uses (+1 along the path's direction, -1 against it); its mean over
-// uniform spanning trees is the effective resistance R(u, v) (Kirchhoff: the
-// tree path's direction on an edge has mean equal to the unit current there,
-// and currents summed along any u -> v path give the potential difference).
-// Ancestry from the tree numbering: x is an ancestor of y (or y itself) iff
-// tin(x) <= tin(y) < tin(x) + vol(x).
-// (each thread's share of the count)
-template <int T>
-__device__ int64_t path_current(const SlotPtrs &sp, const int32_t *path, int len) {
-    const int u = path[0], v = path[len - 1];
-    const uint32_t tu = rec_tin(sp.rec, u), tv = rec_tin(sp.rec, v);
-    auto anc_u = [&](uint32_t t, uint32_t vol) { return t <= tu && tu < t + vol; };
-    auto anc_v = [&](uint32_t t, uint32_t vol) { return t <= tv && tv < t + vol; };
-    int64_t c = 0;
-    for (int i = threadIdx.x; i + 1 < len; i += T) {
-        const int a = path[i], b = path[i + 1];
-        const TNum na = rec_num(sp.rec, a), nb = rec_num(sp.rec, b);
-        const uint32_t ta = na.tin, va = na.vol, tb = nb.tin, vb = nb.vol;
-        const int32_t pa = na.par, pb = nb.par;
-        const bool up_a = anc_u(ta, va) && !anc_v(ta, va), up_b = anc_u(tb, vb) && !anc_v(tb, vb);
-        const bool dn_a = anc_v(ta, va) && !anc_u(ta, va), dn_b = anc_v(tb, vb) && !anc_u(tb, vb);
-        if ((up_a && pa == b) || (dn_b && pb == a)) c += 1;
-        else if ((up_b && pb == a) || (dn_a && pa == b)) c -= 1;
-    }
-    return c;
-}
-
 // Number of graph edges {x, y} that join the two trees left when the tree
-// edge {cut_u, cut_v} is removed (the side away from the root is Sub(tau, c)
-// with c the child endpoint; membership from the tree numbering).  With
-// relink, also cut-link (section 4.2): edge number j of them, in the order
-// (x ascending, row order, x < y), with j drawn by Philox on counter
-// (slot, serial, ISM_CTR_LO, ISM_CTR_HI), joins the two parts; the path from
-// its inner endpoint up to c is reversed so the tree stays rooted at r.
-// The counts of each 64 rows stay in grp (free after the numbering), so that
-// the drawn edge's rows are found without a second pass over the edges.
+// edge {cut_u, cut_v} of the tree `par` is removed (the side away from the root is
+// Sub(tau, c) with c the child endpoint).  With relink, also cut-link (section
+// 4.2): edge number j of them, in the order (x ascending, row order, x < y), with
+// j drawn by Philox on counter (slot, serial, ISM_CTR_LO, ISM_CTR_HI), joins the
+// two parts; the path from its inner endpoint up to c is reversed so the tree
+// stays rooted at r.
+//
+// Which side a vertex is on is found by climbing to c, to the root or to a vertex
+// whose side is known (as the path sums below: no volumes, no numbering), and the
+// edges are counted from the rows of the smaller side.  The counts of each 64
+// smaller endpoints stay in grp, so that the drawn edge's rows are found without a
+// second pass.  (1.9 ms a tree of 20,000 vertices by numbering and full scan.)
 template <int T>
-__device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const RunParams &rp, int32_t slot,
-                                  int idx, TreeShared<T> &sh) {
-    const int lane = threadIdx.x & (WAVE - 1);
+__device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const RunParams &rp, const int32_t *par,
+                                  int32_t slot, int idx, TreeShared<T> &sh) {
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int n = g.n;
     const int a = rp.cut_u, b = rp.cut_v;
-    const int32_t pa = rec_parent(sp.rec, a);
-    const int32_t pb = rec_parent(sp.rec, b);
-    const int c = pa == b ? a : (pb == a ? b : -1);
+    const int c = a != g.root && par[a] == b ? a : (b != g.root && par[b] == a ? b : -1);
     if (c < 0) {
-        report_error(rp.ctl, DEV_BADTREE, idx);
+        if (tid == 0) report_error(rp.ctl, DEV_BADTREE, idx);
         return 0;
     }
-    const TNum nc = rec_num(sp.rec, c);
-    const uint32_t lo = nc.tin, hi = nc.tin + nc.vol;
-    auto inside = [&](int x) {
-        const uint32_t t = rec_tin(sp.rec, x);
-        return lo <= t && t < hi;
-    };
-    auto row_count = [&](int x, bool ix) {
-        int64_t k = 0;
-        for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
+    // sides: 0 unknown, OUT, IN; then the counts per 64 smaller endpoints
+    constexpr uint8_t OUT = 1, IN = 2;
+    uint8_t *side = sp.state;
+    const int nchunk = (n + WAVE - 1) / WAVE;
+    if (tid == 0) sh.bad = 0;
+    for (int v = tid; v < n; v += T) side[v] = v == g.root ? OUT : v == c ? IN : 0;
+    for (int ch = tid; ch < nchunk; ch += T) astore(&sp.grp[ch], 0);
+    __syncthreads();
+    int64_t vol_in = 0;
+    for (int v = tid; v < n; v += T) {
+        int x = v, len = 0, s;
+        while ((s = side[x]) == 0) {
+            x = par[x];
+            if ((unsigned)x >= (unsigned)n || ++len > n) {
+                sh.bad = 1;
+                s = OUT;
+                break;
+            }
+        }
+        for (int y = v; y != x && len > 0; --len) {
+            side[y] = (uint8_t)s;
+            y = par[y];
+        }
+        if (s == IN) vol_in += degree(g, v);
+    }
+    vol_in = block_sum<T>(vol_in, sh);
+    if (sh.bad) {  // (uniform)
+        if (tid == 0) report_error(rp.ctl, DEV_BADTREE, idx);
+        return 0;
+    }
+    const int small = 2 * vol_in <= g.two_m ? IN : OUT;
+    auto edge_count = [&](int x, int64_t first, int64_t step) {
+        int k = 0;
+        for (int64_t e = g.off[x] + first; e < g.off[x + 1]; e += step) {
             const int y = g.adj[e];
-            if (y > x && inside(y) != ix) ++k;
+            if (side[y] != small) {
+                ++k;
+                (void)afetch_add(&sp.grp[min(x, y) / WAVE], 1);
+            }
         }
         return k;
     };
-    const int nchunk = (n + WAVE - 1) / WAVE;
     int64_t cnt = 0;
-    for (int ch = threadIdx.x / WAVE; ch < nchunk; ch += T / WAVE) {
-        const int x = ch * WAVE + lane;
-        const int64_t k = x < n ? row_count(x, inside(x)) : 0;
-        cnt += k;
-        const int64_t all = wave_sum(k);
-        if (lane == 0) astore(&sp.grp[ch], (int32_t)all);
+    for (int x0 = tid - lane; x0 < n; x0 += T) {
+        const int x = x0 + lane;
+        const bool mine = x < n && side[x] == small;
+        const bool wide = mine && degree(g, x) > WAVE;  // a row for the whole wavefront
+        if (mine && !wide) cnt += edge_count(x, 0, 1);
+        for (uint64_t m = __ballot(wide); m != 0ull; m &= m - 1)
+            cnt += edge_count(x0 + __ffsll((unsigned long long)m) - 1, lane, WAVE);
     }
     const int64_t total = block_sum<T>(cnt, sh);
     if (!rp.relink) return total;
     if (total <= 0) {
-        report_error(rp.ctl, DEV_BADTREE, idx);
+        if (tid == 0) report_error(rp.ctl, DEV_BADTREE, idx);
         return 0;
     }
     __syncthreads();
-    if (threadIdx.x >= WAVE) return total;
+    if (tid >= WAVE) return total;
     const int64_t j = arrow_slot(rp.seed, ((uint64_t)ISM_CTR_HI << 32) | ISM_CTR_LO, rp.serial, (uint32_t)slot,
                                  (uint32_t)total);
     auto scan = [&](int64_t k) {
@@ -639,19 +641,24 @@ __device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const R
         base += __shfl(incl, WAVE - 1);
     }
     if (chunk < 0) {
-        report_error(rp.ctl, DEV_BADTREE, idx);
+        if (tid == 0) report_error(rp.ctl, DEV_BADTREE, idx);
         return total;
     }
+    // edge j among the rows' edges to larger endpoints
     const int x = chunk * WAVE + lane;
-    const bool ix = x < n && inside(x);
-    const int64_t k = x < n ? row_count(x, ix) : 0;
+    int64_t k = 0;
+    if (x < n)
+        for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
+            const int z = g.adj[e];
+            if (z > x && side[z] != side[x]) ++k;
+        }
     const int64_t incl = scan(k);
     if (k > 0 && base + incl - k <= j && j < base + incl) {
         int64_t r = j - (base + incl - k);
         int y = -1;
         for (int64_t e = g.off[x]; e < g.off[x + 1]; ++e) {
             const int z = g.adj[e];
-            if (z > x && inside(z) != ix) {
+            if (z > x && side[z] != side[x]) {
                 if (r == 0) { y = z; break; }
                 --r;
             }
@@ -659,14 +666,14 @@ __device__ int64_t crossing_edges(const GraphDev &g, const SlotPtrs &sp, const R
         if (y < 0) {
             report_error(rp.ctl, DEV_BADTREE, idx);
         } else {
-            const int xi = ix ? x : y, yo = ix ? y : x;
+            const bool ix = side[x] == IN;
             int32_t *out = rp.parents_mut + (size_t)slot * (size_t)n;
-            int32_t prev = yo, z = xi;
+            int32_t prev = ix ? y : x, z = ix ? x : y;
             for (int guard = 0; guard <= n; ++guard) {
-                const int32_t nz = rec_parent(sp.rec, z);
+                const int32_t nz = out[z];
                 out[z] = prev;
                 if (z == c) break;
-                if (nz < 0 || nz >= n) {  // c is an ancestor of xi: not reached
+                if (nz < 0 || nz >= n) {  // c is an ancestor of the inner endpoint: not reached
                     report_error(rp.ctl, DEV_BADTREE, idx);
                     break;
                 }
@@ -992,15 +999,14 @@ __device__ __forceinline__ int next_item(int32_t *ctl, TreeShared<T> &sh) {
     return __builtin_amdgcn_readfirstlane(idx);
 }
 
-// A tree of graph g (work item idx; its parents by parent_of(v), checked here)
-// through its record, its numbering and its value: f, the path current
-// (RUN_CURRENT) or the crossing edges (RUN_CROSS), into f_out[idx].
+// f of a tree of graph g (work item idx; its parents by parent_of(v), checked here)
+// into f_out[idx].  scratch: LDS, the sweep's list or nbits bits.
 template <int T, typename ParentOf>
 __device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<T> &sh, uint32_t *scratch,
                               int nbits, const RunParams &rp, int64_t fen_len, int idx,
-                              size_t row, ParentOf parent_of) {
+                              ParentOf parent_of) {
     const int tid = threadIdx.x;
-    if (rp.mode <= RUN_EVALUATE && rp.traversal != 2 && g.anc0 && g.n < PATHS_MAX_N) {
+    if (rp.traversal != 2 && g.anc0 && g.n < PATHS_MAX_N) {
         int64_t part = 0;
         const bool ok = g.anc_depth <= 4 ? f_paths<T, 4>(g, sp, sh.paths, scratch, nbits, parent_of, &part)
                                          : f_paths<T, 8>(g, sp, sh.paths, scratch, nbits, parent_of, &part);
@@ -1038,10 +1044,6 @@ __device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<
     int64_t f = 0;
     if (!ok) {
         // (the call fails; nothing is evaluated)
-    } else if (rp.mode == RUN_CROSS) {
-        f = crossing_edges<T>(g, sp, rp, (int32_t)row, idx, sh);
-    } else if (rp.mode == RUN_CURRENT) {
-        f = block_sum<T>(path_current<T>(sp, rp.path, rp.path_len), sh);
     } else if (rp.traversal == 2) {
         f = block_sum<T>(f_sweep<T>(g, sp, fen_len, reinterpret_cast<SweepItem *>(scratch), sh), sh);
     } else {
