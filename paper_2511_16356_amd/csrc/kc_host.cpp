@@ -103,16 +103,20 @@ void free_workspace(kc_graph *g) {
 
 void free_graph_arrays(kc_graph *g);
 
+void free_host_block(kc_graph *g) {
+    if (g->h_red) (void)hipHostFree(g->h_red);
+    g->h_red = g->d_host_red = nullptr;
+    g->h_progress = g->d_progress = nullptr;
+    g->progress_len = 0;
+}
+
 void free_all(kc_graph *g) {
     free_workspace(g);
     free_graph_arrays(g);
     dev_free(g->d_res_par); dev_free(g->d_res_f); dev_free(g->d_res_f_alt);
     g->d_res_par = nullptr; g->d_res_f = nullptr; g->d_res_f_alt = nullptr; g->res_count = 0;
     dev_free(g->d_f); dev_free(g->d_steps); dev_free(g->d_iters); dev_free(g->d_ctl); dev_free(g->d_red);
-    if (g->h_progress) (void)hipHostFree(g->h_progress);
-    g->h_progress = nullptr;
-    g->d_progress = nullptr;
-    g->progress_len = 0;
+    free_host_block(g);
 }
 
 // Walk start orders.  Wilson's algorithm may start its walks in any order
@@ -230,7 +234,8 @@ int kc_host::default_slots(const kc_graph *g, int mode) {
     return resident_slots(per_cu);
 }
 
-int kc_host::workspace_slots(const kc_graph *g) {
+int kc_host::workspace_slots(const kc_graph *g, int count) {
+    if (count <= resident_slots(1)) return count;  // every CU holds a workgroup of any of the kernels
     return std::max(default_slots(g), default_slots(g, kc::RUN_EVALUATE));
 }
 
@@ -315,12 +320,12 @@ namespace {
 kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
     const bool trav = rp.mode != kc::RUN_SAMPLE;
     const bool fen = trav && g->traversal == KC_TRAV_SWEEP;
-    int want = g->slots_opt > 0 ? g->slots_opt : workspace_slots(g);
+    int want = g->slots_opt > 0 ? g->slots_opt : workspace_slots(g, rp.count);
     want = std::min(want, rp.count);
     int slots = 0;
     kc_status st = ensure_workspace(g, want, trav, fen, stream, &slots);
     if (st != KC_OK) return st;
-    if (g->slots_opt <= 0) slots = std::min(slots, default_slots(g, rp.mode));
+    if (g->slots_opt <= 0 && slots > resident_slots(1)) slots = std::min(slots, default_slots(g, rp.mode));
     slots = balanced_slots(slots, rp.count);
     kc::SlotDev sd;
     sd.state = g->d_state;
@@ -333,13 +338,12 @@ kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
     sd.fen_len = fen ? g->two_m + 2 : 0;
     fill_run_options(g, rp);
     if (g->progress_len < slots) {
-        if (g->h_progress) (void)hipHostFree(g->h_progress);
-        g->h_progress = nullptr;
-        g->d_progress = nullptr;
-        g->progress_len = 0;
-        HIP_TRY(hipHostMalloc((void **)&g->h_progress, sizeof(int64_t) * (size_t)slots,
+        free_host_block(g);
+        HIP_TRY(hipHostMalloc((void **)&g->h_red, sizeof(kc::ReduceOut) + sizeof(int64_t) * (size_t)slots,
                               hipHostMallocMapped | hipHostMallocCoherent));
-        HIP_TRY(hipHostGetDevicePointer((void **)&g->d_progress, g->h_progress, 0));
+        HIP_TRY(hipHostGetDevicePointer((void **)&g->d_host_red, g->h_red, 0));
+        g->h_progress = reinterpret_cast<int64_t *>(g->h_red + 1);
+        g->d_progress = reinterpret_cast<int64_t *>(g->d_host_red + 1);
         g->progress_len = slots;
     }
     HIP_TRY(hipStreamSynchronize(stream));  // no earlier launch still writes the counters
@@ -607,10 +611,14 @@ void free_graph_arrays(kc_graph *g) {
     g->graph_bytes = 0;
 }
 
-kc_status rebuild_graph(kc_graph *g, int32_t root, hipStream_t stream) {
-    PreparedGraph pg;
-    const kc_status st = prepare_graph(g->h_off, g->h_adj, root, g->tau0_kind, &g->h_tau0, &pg);
-    if (st != KC_OK) return st;
+// (ready: the result of prepare_graph for the graph, root and rule g has now, or null)
+kc_status rebuild_graph(kc_graph *g, int32_t root, hipStream_t stream, PreparedGraph *ready = nullptr) {
+    PreparedGraph own;
+    PreparedGraph &pg = ready ? *ready : own;
+    if (!ready) {
+        const kc_status st = prepare_graph(g->h_off, g->h_adj, root, g->tau0_kind, &g->h_tau0, &pg);
+        if (st != KC_OK) return st;
+    }
     HIP_TRY(hipStreamSynchronize(stream));  // no running launch reads the old arrays
     free_graph_arrays(g);
     const int64_t n = (int64_t)g->h_off.size() - 1;
@@ -793,9 +801,9 @@ kc_status kc_set_tau0(kc_graph *g, int kind, const int32_t *parent, void *hip_st
     hipStream_t stream = (hipStream_t)hip_stream;
     std::vector<int32_t> given;
     if (kind == KC_TAU0_GIVEN) given.assign(parent, parent + g->n);
+    PreparedGraph ready;  // validate before anything changes
     {
-        PreparedGraph probe;  // validate before anything changes
-        const kc_status st = prepare_graph(g->h_off, g->h_adj, g->root, kind, &given, &probe);
+        const kc_status st = prepare_graph(g->h_off, g->h_adj, g->root, kind, &given, &ready);
         if (st != KC_OK) return st;
     }
     const int32_t old_kind = g->tau0_kind;
@@ -903,7 +911,7 @@ kc_status kc_reserve(kc_graph *g, int32_t count, void *hip_stream) {
     g_last_error.clear();
     if (!g) return fail(KC_ERR_INVALID, "NULL graph");
     if (count < 1) return fail(KC_ERR_INVALID, "count must be >= 1");
-    int want = g->slots_opt > 0 ? g->slots_opt : workspace_slots(g);
+    int want = g->slots_opt > 0 ? g->slots_opt : workspace_slots(g, count);
     want = std::min(want, count);
     int slots = 0;
     kc_status st = ensure_workspace(g, want, true, g->traversal == KC_TRAV_SWEEP, (hipStream_t)hip_stream, &slots);
@@ -954,10 +962,14 @@ void kc_host::finish_result(int64_t two_m, kc_result *res) {
 
 kc_status kc_host::finish_reduce(kc_graph *g, int32_t count, const int64_t *f, const int64_t *steps,
                                const int64_t *iters, kc_result *res, hipStream_t stream) {
-    HIP_TRY(kc::launch_reduce(f, steps, iters, count, g->d_red, stream));
+    // into the graph's pinned block once it has one (any launch but kc_estimate_static's
+    // makes it): a query is this kernel and one wait, where a copy back took as long again
+    // (26.7 against 18 us)
     kc::ReduceOut ro;
-    HIP_TRY(hipMemcpyAsync(&ro, g->d_red, sizeof(ro), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(kc::launch_reduce(f, steps, iters, count, g->h_red ? g->d_host_red : g->d_red, stream));
+    if (!g->h_red) HIP_TRY(hipMemcpyAsync(&ro, g->d_red, sizeof(ro), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
+    if (g->h_red) ro = *g->h_red;
     res->sum_f_lo = ro.sum_lo;
     res->sum_f_hi = ro.sum_hi;
     res->sum_f2_lo = ro.sq_lo;
@@ -1241,9 +1253,9 @@ static kc_status apply_deletions(kc_graph *g, const int32_t *u, const int32_t *v
     if (kind == KC_TAU0_GIVEN)
         for (const auto &e : del)
             if (g->h_tau0[(size_t)e.first] == e.second || g->h_tau0[(size_t)e.second] == e.first) kind = KC_TAU0_BFS;
+    PreparedGraph ready;  // G' must stay connected (section 2.1); nothing changes if not
     {
-        PreparedGraph probe;  // G' must stay connected (section 2.1); nothing changes if not
-        const kc_status st = prepare_graph(noff, nadj, g->root, kind, &g->h_tau0, &probe);
+        const kc_status st = prepare_graph(noff, nadj, g->root, kind, &g->h_tau0, &ready);
         if (st != KC_OK) return st;
     }
     if (g->maint == KC_MAINT_IMPROVED && g->res_count > 0) {
@@ -1370,9 +1382,9 @@ static kc_status apply_insertion(kc_graph *g, int32_t a, int32_t b, int32_t *res
     std::vector<int64_t> noff;
     std::vector<int32_t> nadj;
     csr_with_edge(g->h_off, g->h_adj, a, b, &noff, &nadj);
+    PreparedGraph ready;  // tau0 of G' must pass the overflow bound; nothing changes if not
     {
-        PreparedGraph probe;  // tau0 of G' must pass the overflow bound; nothing changes if not
-        const kc_status st = prepare_graph(noff, nadj, g->root, g->tau0_kind, &g->h_tau0, &probe);
+        const kc_status st = prepare_graph(noff, nadj, g->root, g->tau0_kind, &g->h_tau0, &ready);
         if (st != KC_OK) return st;
     }
     std::vector<int32_t> redo;
@@ -1497,9 +1509,9 @@ static kc_status ism_insertion(kc_graph *g, int32_t a, int32_t b, int32_t *chang
     std::vector<int64_t> noff;
     std::vector<int32_t> nadj;
     csr_with_edge(g->h_off, g->h_adj, a, b, &noff, &nadj);
+    PreparedGraph ready;
     {
-        PreparedGraph probe;
-        const kc_status st = prepare_graph(noff, nadj, g->root, g->tau0_kind, &g->h_tau0, &probe);
+        const kc_status st = prepare_graph(noff, nadj, g->root, g->tau0_kind, &g->h_tau0, &ready);
         if (st != KC_OK) return st;
     }
     const int32_t count = g->res_count;
@@ -1569,7 +1581,7 @@ static kc_status upload_csr_only(kc_graph *g, hipStream_t stream) {
 
 // One deletion by improved sample maintenance (Algorithm 3; Theorem 4.5); the
 // graph stays connected (checked by the caller for the whole run).  Only the
-// run's last edge rebuilds tau0 and the other per-graph arrays.
+// run's last edge replaces tau0 and the other per-graph arrays (last: theirs).
 static kc_status ism_deletion(kc_graph *g, int32_t a, int32_t b, int32_t *changed, hipStream_t stream, bool last) {
     const int32_t count = g->res_count;
     std::vector<int32_t> hit;

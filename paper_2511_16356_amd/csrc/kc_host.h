@@ -70,7 +70,9 @@ struct kc_graph {
     int64_t *d_f = nullptr, *d_steps = nullptr, *d_iters = nullptr;  // internal per-sample buffers
     int64_t fbuf_len = 0;
     int32_t *d_ctl = nullptr;
-    int64_t *h_progress = nullptr;  // pinned host array, one counter per slot
+    kc::ReduceOut *h_red = nullptr;  // pinned host block: a reduction's result, then the counters
+    kc::ReduceOut *d_host_red = nullptr;  // its device view
+    int64_t *h_progress = nullptr;  // one counter per slot
     int64_t *d_progress = nullptr;  // its device view
     int progress_len = 0;
     kc::ReduceOut *d_red = nullptr;
@@ -95,8 +97,9 @@ int64_t slot_bytes(const kc_graph *g, bool trav, bool fen);
 // Samples in flight when the graph's slots option is 0: resident workgroups of the kernel.
 int resident_slots(int per_cu);
 int default_slots(const kc_graph *g, int mode = kc::RUN_ESTIMATE);  // resident workgroups of the launch's kernel
-// Slots the workspace is sized for when the slots option is 0: the most any launch on g takes.
-int workspace_slots(const kc_graph *g);
+// Slots the workspace is sized for when the slots option is 0: the most any launch of up to
+// count samples on g takes.
+int workspace_slots(const kc_graph *g, int count);
 // How g's trees are sampled (kc::Route).
 int route_of(const kc_graph *g);
 int64_t workspace_budget(const kc_graph *g, size_t free_b);
