@@ -810,7 +810,7 @@ kc_status kc_set_tau0(kc_graph *g, int kind, const int32_t *parent, void *hip_st
     std::vector<int32_t> old_tau0 = g->h_tau0;
     g->tau0_kind = kind;
     g->h_tau0.swap(given);
-    kc_status st = rebuild_graph(g, g->root, stream);
+    kc_status st = rebuild_graph(g, g->root, stream, &ready);
     // resident trees are unchanged; their f is taken over the new tau0 (Theorem 3.4)
     const bool was_stale = g->res_f_stale;
     if (st == KC_OK && g->res_count > 0) {
@@ -1134,7 +1134,8 @@ kc_status kc_samples_get(kc_graph *g, int32_t *parents_out, int64_t *f_out, int6
     return KC_OK;
 }
 
-static kc_status ism_deletion(kc_graph *g, int32_t a, int32_t b, int32_t *changed, hipStream_t stream, bool last);
+static kc_status ism_deletion(kc_graph *g, int32_t a, int32_t b, int32_t *changed, hipStream_t stream,
+                              PreparedGraph *last);
 
 // Moves g to a new CSR and keeps the old one; undo() puts back the old CSR
 // and tau0 rule and rebuilds every per-graph array, so that an update that
@@ -1262,7 +1263,7 @@ static kc_status apply_deletions(kc_graph *g, const int32_t *u, const int32_t *v
         // Algorithm 3 takes one edge at a time; every intermediate graph contains
         // the final one, so it is connected too
         for (int32_t k = 0; k < count; ++k) {
-            const kc_status st = ism_deletion(g, u[k], v[k], resampled, stream, k == count - 1);
+            const kc_status st = ism_deletion(g, u[k], v[k], resampled, stream, k == count - 1 ? &ready : nullptr);
             if (st != KC_OK) return st;
         }
         return KC_OK;
@@ -1285,7 +1286,7 @@ static kc_status apply_deletions(kc_graph *g, const int32_t *u, const int32_t *v
         g->tau0_kind = kind;
         g->h_tau0.clear();
     }
-    kc_status st = rebuild_graph(g, g->root, stream);
+    kc_status st = rebuild_graph(g, g->root, stream, &ready);
     if (st != KC_OK) return sw.undo(st, stream);
     if (g->res_count > 0) {
         // fresh trees of G' for the replaced ones: the next unused sample indices, in slot order
@@ -1402,7 +1403,7 @@ static kc_status apply_insertion(kc_graph *g, int32_t a, int32_t b, int32_t *res
             if (update_uniform(g->res_seed, (uint32_t)t, (uint32_t)g->res_serial) < p) redo.push_back(t);
     }
     GraphSwitch sw(g, std::move(noff), std::move(nadj));
-    kc_status st = rebuild_graph(g, g->root, stream);
+    kc_status st = rebuild_graph(g, g->root, stream, &ready);
     if (st != KC_OK) return sw.undo(st, stream);
     if (g->res_count > 0) {
         const int32_t k = (int32_t)redo.size();
@@ -1544,7 +1545,7 @@ static kc_status ism_insertion(kc_graph *g, int32_t a, int32_t b, int32_t *chang
         return st;
     }
     GraphSwitch sw(g, std::move(noff), std::move(nadj));
-    st = rebuild_graph(g, g->root, stream);
+    st = rebuild_graph(g, g->root, stream, &ready);
     // d(tau_e): edges of G that join the two parts of tau_e - e (those of G' minus e itself)
     if (st == KC_OK) st = ism_cross(g, chosen, a, b, 0, &d_new, stream);
     if (st != KC_OK) {
@@ -1582,7 +1583,8 @@ static kc_status upload_csr_only(kc_graph *g, hipStream_t stream) {
 // One deletion by improved sample maintenance (Algorithm 3; Theorem 4.5); the
 // graph stays connected (checked by the caller for the whole run).  Only the
 // run's last edge replaces tau0 and the other per-graph arrays (last: theirs).
-static kc_status ism_deletion(kc_graph *g, int32_t a, int32_t b, int32_t *changed, hipStream_t stream, bool last) {
+static kc_status ism_deletion(kc_graph *g, int32_t a, int32_t b, int32_t *changed, hipStream_t stream,
+                              PreparedGraph *last) {
     const int32_t count = g->res_count;
     std::vector<int32_t> hit;
     {
@@ -1607,7 +1609,7 @@ static kc_status ism_deletion(kc_graph *g, int32_t a, int32_t b, int32_t *change
         g->tau0_kind = KC_TAU0_BFS;
         g->h_tau0.clear();
     }
-    kc_status st = last ? rebuild_graph(g, g->root, stream) : upload_csr_only(g, stream);
+    kc_status st = last ? rebuild_graph(g, g->root, stream, last) : upload_csr_only(g, stream);
     // cut-link in place; d(tau) = edges of G' that join the two parts of tau - e
     std::vector<int64_t> d_old, d_new;
     if (st == KC_OK) st = ism_cross(g, hit, a, b, 1, &d_old, stream);
