@@ -236,38 +236,54 @@ __device__ __forceinline__ int64_t sample_lds(const GraphDev &g, const FrontierW
             }
             next += take;
         } else {
-            // ---- the due walks
-            for (int b = 0; b < n; b += T) {
-                const int v = b + tid;
-                const uint32_t w = v < n ? load(v) : 0;
-                const bool due = (w & (L_FLAG | L_SET)) == L_FLAG;
-                const uint64_t m = __ballot(due);
-                const int at = take_shared(&sh.n_list, __popcll(m)) + rank_in(m);
-                if (due && at < D_LDS) {
-                    sh.due_v[at] = (uint16_t)v;
-                    sh.due_word[at] = w;
-                    words[v] = (uint32_t)at | L_FLAG | L_SET;
+            // ---- the due walks (four words per thread at a time: most hold none)
+            for (int b = 0; b < n; b += 4 * T) {
+                const int v0 = b + 4 * tid;
+                uint4 q = make_uint4(0, 0, 0, 0);
+                if (v0 < n) q = *reinterpret_cast<const uint4 *>(words + v0);  // (padded to 16 bytes)
+                const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+                uint32_t due = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (v0 + k < n && (w[k] & (L_FLAG | L_SET)) == L_FLAG) due |= 1u << k;
+                if (__ballot(due != 0) == 0ull) continue;
+                int c = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) c += __popcll(__ballot(due >> k & 1u));
+                int at = take_shared(&sh.n_list, c);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint64_t m = __ballot(due >> k & 1u);
+                    const int i = at + rank_in(m);
+                    if ((due >> k & 1u) && i < D_LDS) {
+                        sh.due_v[i] = (uint16_t)(v0 + k);
+                        sh.due_word[i] = w[k];
+                        words[v0 + k] = (uint32_t)i | L_FLAG | L_SET;
+                    }
+                    at += __popcll(m);
                 }
             }
             __syncthreads();
-            const int n_due = min(sh.n_list, D_LDS);  // (the others: next time)
+            const int n_list = sh.n_list, n_due = min(n_list, D_LDS);  // (the others: next time)
             if (n_due == 0) break;
-            for (int i = tid; i < n_due; i += T) {
-                int x = (int)(sh.due_word[i] & L_MASK), mark = -1, len = 1, link;
-                while (true) {
-                    const uint32_t wx = load(x);
-                    if (wx & L_SET) {
-                        link = wx & L_FLAG ? (int)(wx & L_MASK) : -1;
-                        break;
-                    }
-                    // (only where the table is too small: a cycle without a place)
-                    if (x == mark) { link = -2; break; }
-                    if ((len & (len - 1)) == 0) mark = x;
-                    x = (int)(wx & L_MASK);
-                    ++len;
+            for (int b = 0; b < n_due; b += T) {
+                const int i = b + tid;
+                int x = i < n_due ? (int)(sh.due_word[i] & L_MASK) : top, len = 1, mark = -1;
+                uint32_t wx, step = 1;
+                bool go;
+                do {  // (as above; Brent's marks only where the table is too small, so that a cycle
+                      // may have no place in it)
+                    wx = load(x);
+                    go = !(wx & L_SET) && x != mark;
+                    if (n_list > D_LDS && (step & (step - 1)) == 0) mark = go ? x : mark;
+                    x = go ? (int)(wx & L_MASK) : x;
+                    len += go ? 1 : 0;
+                    ++step;
+                } while (__builtin_amdgcn_ballot_w64(go) != 0ull);
+                if (i < n_due) {
+                    sh.due_next[i] = (int16_t)(!(wx & L_SET) ? -2 : (wx & L_FLAG ? (int)(wx & L_MASK) : -1));
+                    sh.due_len[i] = (uint16_t)len;
                 }
-                sh.due_next[i] = (int16_t)link;
-                sh.due_len[i] = (uint16_t)len;
             }
             __syncthreads();
             for (int i = tid; i < n_due; i += T) {
