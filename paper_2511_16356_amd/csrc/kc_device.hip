@@ -627,7 +627,7 @@ constexpr int CHAIN_BITS = 1 << 16;
 template <int CH>
 union KernelShared {
     SamplerShared<CH> samp;
-    SweepItem sweep[2 * WAVE];
+    SweepLds<WAVE> sweep;
     uint32_t bitmap[CHAIN_BITS / 32];
 };
 

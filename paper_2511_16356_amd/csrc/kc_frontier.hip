@@ -39,7 +39,7 @@ constexpr int LT = 256, GT = 512;
 constexpr int FT_WAVES = 4;  // wavefronts per SIMD the kernels are built to fit (128 VGPRs)
 // Trees the caller holds: as above (1,024 vertices and 2,000 trees: 1.7 against 2.6 ms
 // with 512; 481,994 vertices and 256 trees: 29.0 against 25.4 ms).
-inline int tree_threads(int64_t n) { return n > LDS_MAX_N ? GT : LT; }
+inline int tree_threads(int64_t n, int traversal) { return traversal != 2 && n > LDS_MAX_N ? GT : LT; }
 
 // Entries of the frontier, of the found cycles and of the due walks' table kept
 // in LDS; frontier and cycles beyond (early rounds only) go to the slot's block.
@@ -667,7 +667,7 @@ __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev s
 template <int T>
 size_t dyn_lds(int route, int64_t n) {
     const size_t words = route == ROUTE_LDS ? 4 * (size_t)n : 0;
-    return (std::max({words, (size_t)path_bits(n) / 8, sweep_lds<T>()}) + 15) / 16 * 16;
+    return (std::max({words, (size_t)path_bits(n) / 8, sizeof(SweepLds<T>)}) + 15) / 16 * 16;
 }
 
 template <typename K>
@@ -713,7 +713,7 @@ hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *
     return hipGetLastError();
 }
 hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
-    if (tree_threads(g.n) == GT)
+    if (tree_threads(g.n, rp.traversal) == GT)
         hipLaunchKernelGGL((tree_kernel<GT>), dim3(slots), dim3(GT), dyn_lds<GT>(ROUTE_GLOBAL, g.n), stream, g, s, rp);
     else
         hipLaunchKernelGGL((tree_kernel<LT>), dim3(slots), dim3(LT), dyn_lds<LT>(ROUTE_GLOBAL, g.n), stream, g, s, rp);
@@ -732,8 +732,8 @@ int frontier_batch_blocks_per_cu(const BatchArgs &a) {
     }
     return global ? resident(frontier_batch_kernel<GT>, GT, lds) : resident(frontier_batch_kernel<LT>, LT, lds);
 }
-int tree_blocks_per_cu(int64_t n) {
-    return tree_threads(n) == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n))
+int tree_blocks_per_cu(int64_t n, int traversal) {
+    return tree_threads(n, traversal) == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n))
                                   : resident(tree_kernel<LT>, LT, dyn_lds<LT>(ROUTE_GLOBAL, n));
 }
 

@@ -228,7 +228,7 @@ int kc_host::resident_slots(int per_cu) {
 int kc_host::default_slots(const kc_graph *g, int mode) {
     const int route = route_of(g);
     int per_cu = 0;
-    if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n);
+    if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n, g->traversal);
     else if (route == kc::ROUTE_CHAINS) per_cu = kc::persistent_blocks_per_cu(g->chains);
     else per_cu = kc::frontier_blocks_per_cu(route, g->n);
     return resident_slots(per_cu);

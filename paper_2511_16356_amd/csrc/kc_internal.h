@@ -34,10 +34,8 @@ struct GraphDev {
 //   tag words  uint64 [stride] at 0: tag/flag bits | first parked chain + 1 << 32
 //   arrow words uint64 [stride] at 8 stride: arrow target | draws << 32
 //   restart ring int32 [stride] at 16 stride
-// Once the tree's parents are copied into rec they are dead, and the tree
-// numbering reuses the block:
-//   ord  int4 [stride] at 0: finished vertices {v, parent, vol, offset}, leaves {v, parent, deg, 0}
-//   grp  int32 [stride + 1] at 16 stride: completion group boundaries
+// Once the tree's parents are copied into rec they are dead, and what evaluates the
+// tree reuses the block (kc_tree.h; the frontier sampler has its own layout of it).
 struct SlotDev {
     unsigned char *state; // [slots * state_bytes(stride)]
     int4 *queue;     // [slots*chains] sampler: ready tasks
@@ -165,7 +163,7 @@ hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *
 hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream);
 int frontier_blocks_per_cu(int route, int64_t n);  // resident workgroups per CU
 int frontier_batch_blocks_per_cu(const BatchArgs &a);
-int tree_blocks_per_cu(int64_t n);
+int tree_blocks_per_cu(int64_t n, int traversal);
 // The batch takes the frontier sampler when every job's route is one of its.
 inline bool batch_is_frontier(const BatchArgs &a) {
     for (int j = 0; j < a.k; ++j)

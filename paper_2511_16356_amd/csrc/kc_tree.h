@@ -121,18 +121,18 @@ __device__ __forceinline__ uint32_t arrow_slot(uint64_t seed, uint64_t s, uint32
 // The numbered tree: one 16-byte record per vertex, two 8-byte words, so that
 // every step of the numbering touches one line per vertex it visits:
 //   rec[2v]     pending children << 44 | volume while the volumes are summed
-//               (starting at deg(v)); tin(v) + vol(v) once the numbering is done
-//   rec[2v + 1] parent (low half, -1 at the root) | deg(v) (high half) until the
-//               top-down step, then parent | tin(v)
+//               (starting at deg(v)); then vol(v) | (tin(v) + 1) << 32, the high
+//               half 0 until tin is known
+//   rec[2v + 1] parent (low half, -1 at the root) | once the vertex is finished,
+//               its offset in the parent's interval << 32
 struct SlotPtrs {
     unsigned char *state;  // the sampler's block, 20 bytes per vertex
     size_t stride;
     int4 *queue;
     int32_t *cstart;
     uint64_t *rec;
-    int4 *ord;             // finished vertices {v, parent, vol, offset in the parent's interval} in
-                           // completion order; the leaves {v, parent, deg, 0} wait at its end
-    int32_t *grp;
+    int32_t *leaf;         // the tree's leaves
+    int32_t *grp;          // per 64 vertices: counts of crossing edges
     int64_t *fen;
 };
 
@@ -145,15 +145,11 @@ struct TNum {
     int32_t par;
 };
 __device__ __forceinline__ TNum rec_num(const uint64_t *rec, int v) {
-    const uint64_t w = aload(&rec[2 * (size_t)v]), h = aload(&rec[2 * (size_t)v + 1]);
-    TNum t;
-    t.tin = (uint32_t)(h >> 32);
-    t.vol = (uint32_t)(w - (h >> 32));
-    t.par = (int32_t)(uint32_t)h;
-    return t;
+    const uint64_t w = aload(&rec[2 * (size_t)v]);
+    return {(uint32_t)(w >> 32) - 1, (uint32_t)w, rec_parent(rec, v)};
 }
 __device__ __forceinline__ uint32_t rec_tin(const uint64_t *rec, int v) {
-    return (uint32_t)(aload(&rec[2 * (size_t)v + 1]) >> 32);
+    return (uint32_t)(aload(&rec[2 * (size_t)v]) >> 32) - 1;
 }
 
 // Vertices each lane keeps in flight in the tree numbering: the memory
@@ -170,17 +166,29 @@ __device__ __forceinline__ uint32_t degree(const GraphDev &g, int v) {
     return (uint32_t)(g.off[v + 1] - g.off[v]);
 }
 
-// Fenwick tree over positions 0..2m storing a difference array.
-__device__ __forceinline__ void fen_point_add(int64_t *fen, int64_t len, int64_t pos, int64_t val) {
-    if (pos < 0) pos = 0;
-    for (int64_t i = pos + 1; i < len; i += i & (-i)) afetch_add(&fen[i], val);
+// Fenwick tree over positions 0..2m storing a difference array.  The nodes at
+// multiples of 2^shift are kept in LDS (at most FEN_HI of them): what is left of an
+// update or a sum in memory lies in one block of 2^shift words, where the whole
+// tree there took about ten lines of its own per point (1,024 trees of a road-like
+// graph of 44,780 vertices: 22.4 ms, 19.8 with the split).
+template <int T>
+constexpr int FEN_HI = T == WAVE ? 1024 : 2048;  // (one wavefront: the list and these fit the chain table's LDS)
+struct Fenwick {
+    int64_t *low, *hi;
+    int32_t len, shift;
+};
+__device__ __forceinline__ void fen_point_add(const Fenwick &t, uint32_t pos, int64_t val) {
+    uint32_t i = pos + 1;
+    const uint32_t len = (uint32_t)t.len, mask = (1u << t.shift) - 1;
+    for (; i < len && (i & mask) != 0; i += i & (0u - i)) afetch_add(&t.low[i], val);
+    for (uint32_t h = i >> t.shift; i < len && h <= (len - 1) >> t.shift; h += h & (0u - h)) afetch_add(&t.hi[h], val);
 }
-__device__ __forceinline__ void fen_range_add(int64_t *fen, int64_t len, int64_t lo, int64_t hi,
-                                              int64_t val) {
+__device__ __forceinline__ void fen_range_add(const Fenwick &t, uint32_t lo, uint32_t hi, int64_t val) {
     if (val == 0 || hi <= lo) return;
-    fen_point_add(fen, len, lo, val);
-    fen_point_add(fen, len, hi, -val);
+    fen_point_add(t, lo, val);
+    fen_point_add(t, hi, -val);
 }
+
 // The two contributions attached to tau0 vertex x (Theorem 3.4), as
 // ranges of tin with a weight, active for every u in Sub(tau0, x):
 //   forward : p(x) = p0(x)          -> +(2m - vol(x)) on Sub(tau, x)
@@ -211,8 +219,8 @@ struct PathShared {
 // Scratch of the tree code in LDS.
 template <int T>
 struct TreeShared {
-    int32_t count[4], take[4];  // rotating counters of the bottom-up rounds
-    int32_t leaves, bad, item;
+    int32_t count[2];           // the sweep's lists
+    int32_t leaves, taken, left, bad, item;
     PathShared paths;
     int64_t red[T / WAVE];
 };
@@ -239,27 +247,26 @@ __device__ __forceinline__ int take_shared(int32_t *counter, int n) {
 }
 
 // Volumes and the volume-weighted preorder of the tree whose parents are in
-// rec (rec[2v] = deg(v), rec[2v+1] = parent | deg(v) << 32 already).  Returns
-// false if the parents do not form a tree rooted at r.
+// rec (rec[2v] = deg(v), rec[2v+1] = parent already).  Returns false if the
+// parents do not form a tree rooted at r.
 //
-// Bottom-up: each lane carries up to NB finished vertices; a carrier pushes
-// its vertex's volume into the parent's word with one atomic, and the last
-// child to arrive carries the parent on in the next round.  The volume part
-// the atomic returns is the parent's degree plus the volumes of the siblings
-// that arrived before: the vertex's offset in its parent's interval.  Every
-// round's finished vertices form a completion group.  Top-down: the groups in
-// reverse order (a parent always finishes in a later group than its
-// children); a vertex's tin is its parent's tin plus its offset.
+// Bottom-up: each lane carries up to NB finished vertices; a carrier pushes its
+// vertex's volume into the parent's word with one atomic, and the last child to
+// arrive carries the parent on.  The volume part the atomic returns is the
+// parent's degree plus the volumes of the siblings that arrived before: the
+// vertex's offset in its parent's interval.  Top-down, tin is the sum of the
+// offsets along the path to the root: a vertex climbs to one whose tin is known
+// and writes those of the vertices it passed; a spread of seeds climbs first.
 //
-// A round's counters rotate over four words: the one a round fills is read
-// after that round's barrier and cleared by thread 0 after the next one, two
-// barriers before it is filled again.
+// Neither half has rounds, so a deep tree (1,200 levels on a road-like graph of
+// 44,780 vertices) costs its longest chain's dependent atomics and climbs, not
+// two barriers per level: 6.8M cycles a tree with completion groups, top-down in
+// reverse.
 template <int T>
 __device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared<T> &sh) {
     const int tid = threadIdx.x;
     const int n = g.n;
-    if (tid < 4) sh.count[tid] = sh.take[tid] = 0;
-    if (tid == 0) sh.leaves = 0;
+    if (tid == 0) sh.leaves = sh.taken = sh.left = 0;
     // one PEND_ONE per child in the parent's word
     for (int b = 0; b < n; b += T * NBS) {
         int32_t p[NBS];
@@ -273,14 +280,12 @@ __device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared
             if (p[k] >= 0) afetch_add(&sp.rec[2 * (size_t)p[k]], PEND_ONE);
     }
     __syncthreads();
-    // leaves {v, parent, deg, 0}: leaf number j at ord[n - 1 - j]
     for (int b = 0; b < n; b += T * NBS) {
-        uint64_t w[NBS], h[NBS];
+        uint64_t w[NBS];
 #pragma unroll
         for (int k = 0; k < NBS; ++k) {
             const int v = b + k * T + tid;
             w[k] = v < n ? aload(&sp.rec[2 * (size_t)v]) : PEND_ONE;  // past the end: not a leaf
-            h[k] = v < n ? aload(&sp.rec[2 * (size_t)v + 1]) : 0;
         }
         int c = 0;
 #pragma unroll
@@ -290,54 +295,50 @@ __device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared
         for (int k = 0; k < NBS; ++k) {
             const bool leaf = (w[k] >> 44) == 0;
             const uint64_t m = __ballot(leaf);
-            if (leaf)
-                sp.ord[n - 1 - (at + rank_in(m))] = make_int4(b + k * T + tid, (int32_t)(uint32_t)h[k],
-                                                              (int)(w[k] & VOL_MASK), 0);
+            if (leaf) sp.leaf[at + rank_in(m)] = b + k * T + tid;
             at += __popcll(m);
         }
     }
     __syncthreads();
     const int L = sh.leaves;
-    // bottom-up.  Leaves are taken from the low end of their block, ord[n-L ..]:
-    // the finished entries of all rounds so far never reach a leaf that is still
-    // to be taken, since nord + (leaves not yet taken) <= n; within a round every
-    // leaf is read before the first entry is written.
     int cv[NB], cp[NB];
     uint64_t cval[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) { cv[k] = -1; cp[k] = -1; cval[k] = 0; }
-    int li = 0, nord = 0, ngrp = 0;
+    int64_t done = 0;
+    bool more = true;
     while (true) {
-        const int r = ngrp & 3;
-        if (li < L) {  // (uniform)
+        if (more) {
             int c = 0;
 #pragma unroll
             for (int k = 0; k < NB; ++k) c += __popcll(__ballot(cv[k] < 0));
-            int at = li + take_shared(&sh.take[r], c);
+            int at = c > 0 ? take_shared(&sh.taken, c) : 0;
+            if (c > 0) more = at + c < L;
 #pragma unroll
             for (int k = 0; k < NB; ++k) {
-                const uint64_t freem = __ballot(cv[k] < 0);
-                const int j = at + rank_in(freem);
+                const uint64_t m = __ballot(cv[k] < 0);
+                const int j = at + rank_in(m);
                 if (cv[k] < 0 && j < L) {
-                    const int4 e = sp.ord[n - L + j];
-                    cv[k] = e.x;
-                    cp[k] = e.y;
-                    cval[k] = (uint64_t)(uint32_t)e.z;
+                    cv[k] = sp.leaf[j];
+                    cval[k] = (uint64_t)degree(g, cv[k]);
+                    cp[k] = rec_parent(sp.rec, cv[k]);
                 }
-                at += __popcll(freem);
+                at += __popcll(m);
             }
-            if constexpr (T > WAVE) __syncthreads();
         }
-        int c = 0;
+        uint64_t busy = 0;
 #pragma unroll
-        for (int k = 0; k < NB; ++k) c += __popcll(__ballot(cv[k] >= 0));
-        int at = nord + take_shared(&sh.count[r], c);
+        for (int k = 0; k < NB; ++k) busy |= __ballot(cv[k] >= 0);
+        if (busy == 0ull) break;  // (then no leaf is left either)
         // the parent's own parent, the next vertex if this child is the last, comes
         // from the record line the atomic uses
         uint64_t old[NB];
         int32_t up[NB];
+        bool any[NB];  // (the wavefront has such a carrier: most of a deep tree's steps have few)
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
+            any[k] = __ballot(cv[k] >= 0) != 0ull;
+            if (!any[k]) continue;
             old[k] = 0;
             up[k] = -1;
             if (cv[k] >= 0 && cp[k] >= 0) {
@@ -347,66 +348,85 @@ __device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared
         }
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-            const uint64_t bm = __ballot(cv[k] >= 0);
-            const int i = at + rank_in(bm);
-            if (cv[k] >= 0 && i < n)
-                sp.ord[i] = make_int4(cv[k], cp[k], (int)cval[k], (int)(uint32_t)(old[k] & VOL_MASK));
-            at += __popcll(bm);
-        }
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            const bool last = cv[k] >= 0 && cp[k] >= 0 && (old[k] >> 44) == 1;
+            if (!any[k] || cv[k] < 0) continue;
+            const bool top = cp[k] < 0;
+            astore(&sp.rec[2 * (size_t)cv[k]], cval[k] | (uint64_t)(top ? 1u : 0u) << 32);
+            astore(&sp.rec[2 * (size_t)cv[k] + 1], (uint64_t)(uint32_t)cp[k] | (old[k] & VOL_MASK) << 32);
+            ++done;
+            const bool last = !top && (old[k] >> 44) == 1;
+            if (last) cval[k] = (old[k] & VOL_MASK) + cval[k];
             cv[k] = last ? cp[k] : -1;
             cp[k] = up[k];
-            if (last) cval[k] = (old[k] & VOL_MASK) + cval[k];
         }
-        __syncthreads();
-        const int done = sh.count[r];
-        if (li < L) li = min(L, li + sh.take[r]);
-        if (tid == 0) {
-            sh.count[(r + 3) & 3] = sh.take[(r + 3) & 3] = 0;
-            if (ngrp <= n) astore(&sp.grp[ngrp], nord);
-        }
-        nord += done;
-        if (done == 0 || nord > n) break;  // nothing left; more entries than vertices: not a tree
-        ngrp++;
     }
+    if (block_sum<T>(done, sh) != n) return false;
     __syncthreads();
-    if (nord != n) return false;
-    // top-down; the group boundaries are read 64 at a time
-    const int lane = tid & (WAVE - 1);
-    for (int g0 = ngrp - 1; g0 >= 0; g0 -= WAVE) {
-        const int bnd = g0 - lane >= 0 ? aload(&sp.grp[g0 - lane]) : 0;
-        const int nb = min(WAVE, g0 + 1);
-        int hi = aload(&sp.grp[g0 + 1]);
-        for (int t = 0; t < nb; ++t) {
-            const int lo = __shfl(bnd, t);
-            for (int i0 = lo; i0 < hi; i0 += T * NB) {
-                int4 e[NB];
+    // top-down
+    constexpr int SEED = 4096, SHORT = 8;
+    const int4 *rec4 = reinterpret_cast<const int4 *>(sp.rec);  // vol, tin + 1, parent, offset
+    auto climb = [&](auto wu, auto is_short, int at, int count, auto vertex) __attribute__((always_inline)) {
+        constexpr int WU = decltype(wu)::value;
+        constexpr bool CUT = decltype(is_short)::value;
+        int v[WU], x[WU];
+        uint32_t sum[WU], vol[WU], off[WU], up[WU], len[WU];
+        int4 r[WU];
+        bool go[WU];
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const int i = i0 + k * T + tid;
-                    e[k] = i < hi ? sp.ord[i] : make_int4(-1, -1, 0, 0);
-                }
-                // tin = the parent's tin (written by its own group) + the offset the
-                // bottom-up atomic returned
-                uint64_t tin[NB];
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    tin[k] = 0;
-                    if (e[k].x >= 0 && e[k].y >= 0) tin[k] = (uint64_t)rec_tin(sp.rec, e[k].y) + (uint32_t)e[k].w;
-                }
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    if (e[k].x < 0) continue;
-                    astore(&sp.rec[2 * (size_t)e[k].x], tin[k] + (uint64_t)(uint32_t)e[k].z);
-                    astore(&sp.rec[2 * (size_t)e[k].x + 1], (uint64_t)(uint32_t)e[k].y | (tin[k] << 32));
-                }
-            }
-            __syncthreads();  // the next group reads the intervals of this one
-            hi = lo;
+        for (int k = 0; k < WU; ++k) {
+            const int i = at + k * T;
+            v[k] = i < count ? vertex(i) : -1;
+            x[k] = v[k] >= 0 ? v[k] : g.root;
+            sum[k] = len[k] = vol[k] = off[k] = up[k] = 0;
         }
-    }
+        int step = 0;
+        uint64_t any;
+        do {
+            any = 0;
+#pragma unroll
+            for (int k = 0; k < WU; ++k) r[k] = rec4[x[k]];
+#pragma unroll
+            for (int k = 0; k < WU; ++k) {
+                if (step == 0) {
+                    vol[k] = (uint32_t)r[k].x;
+                    off[k] = (uint32_t)r[k].w;
+                    up[k] = (uint32_t)r[k].z;
+                }
+                go[k] = r[k].y == 0;
+                sum[k] += go[k] ? (uint32_t)r[k].w : 0u;
+                x[k] = go[k] ? r[k].z : x[k];
+                len[k] += go[k] ? 1u : 0u;
+                any |= __builtin_amdgcn_ballot_w64(go[k]);
+            }
+        } while ((!CUT || step < SHORT) && ++step && any != 0ull);
+#pragma unroll
+        for (int k = 0; k < WU; ++k) {
+            if (v[k] < 0 || len[k] == 0) continue;
+            if (go[k]) {
+                sp.leaf[afetch_add(&sh.left, 1)] = v[k];  // (the leaves are used up)
+                continue;
+            }
+            uint32_t tin1 = sum[k] + (uint32_t)r[k].y;  // tin + 1
+            astore(&sp.rec[2 * (size_t)v[k]], (uint64_t)vol[k] | (uint64_t)tin1 << 32);
+            tin1 -= off[k];
+            for (int y = (int)up[k]; y != x[k];) {
+                const int4 q = rec4[y];
+                astore(&sp.rec[2 * (size_t)y], (uint64_t)(uint32_t)q.x | (uint64_t)tin1 << 32);
+                tin1 -= (uint32_t)q.w;
+                y = q.z;
+            }
+        }
+    };
+    constexpr auto one = std::integral_constant<int, 1>{};
+    constexpr auto four = std::integral_constant<int, 4>{};
+    const int seeds = min(n, SEED);
+    for (int at = tid; at - tid < seeds; at += T)
+        climb(one, std::false_type{}, at, seeds, [&](int i) { return (int)((int64_t)i * n / seeds); });
+    for (int at = tid; at - tid < n; at += 4 * T) climb(four, std::true_type{}, at, n, [](int i) { return i; });
+    __syncthreads();
+    const int left = sh.left;
+    for (int at = tid; at - tid < left; at += T)
+        climb(one, std::false_type{}, at, left, [&](int i) { return sp.leaf[i]; });
+    __syncthreads();
     return true;
 }
 
@@ -462,36 +482,51 @@ struct SweepItem {
     int64_t w;
 };
 template <int T>
-constexpr size_t sweep_lds() { return 2 * T * sizeof(SweepItem); }
+struct SweepLds {
+    SweepItem list[2 * T];
+    int64_t hi[FEN_HI<T>];
+};
 
 template <int T>
-__device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_len, SweepItem *list,
+__device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_len, SweepLds<T> &lds,
                            TreeShared<T> &sh) {
     constexpr int WAVES = T / WAVE;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const int n = g.n;
     int64_t acc = 0;
     int blk = 0;
+    SweepItem *list = lds.list;
+    Fenwick fen{sp.fen, lds.hi, (int32_t)fen_len, 0};
     int levels = 1;
     while ((1ll << levels) < fen_len) ++levels;
+    while ((fen_len - 1) >> fen.shift >= FEN_HI<T>) ++fen.shift;
+    for (int i = tid; i < FEN_HI<T>; i += T) fen.hi[i] = 0;
     if (tid < 2) sh.count[tid] = 0;
     __syncthreads();
     int turn = 0;  // of the two list counters
+    // the step's own vertices, and the closing subtrees of its first list, are read a step ahead
+    const int first = tid - WAVE;  // this thread's place among those
+    int e0 = g.eoff[0], e1 = g.eoff[1];
+    int u_next = lane < n ? g.pre0[lane] : g.root;
+    int x_next = first >= 0 && e0 + first < e1 ? g.elist[e0 + first] : -1;
     for (int P0 = 0; P0 < n; P0 += WAVE, ++blk) {
         const int p = P0 + lane;
         const bool valid = p < n;
-        const int u = valid ? g.pre0[p] : g.root;
+        const int u = u_next, c0 = e0, c1 = e1;
+        int x = wave == 0 ? (valid ? u : -1) : x_next;
+        if (P0 + WAVE < n) {
+            e0 = e1;
+            e1 = g.eoff[blk + 2];
+            u_next = p + WAVE < n ? g.pre0[p + WAVE] : g.root;
+            x_next = first >= 0 && e0 + first < e1 ? g.elist[e0 + first] : -1;
+        }
         const uint32_t tu = rec_tin(sp.rec, u);
         int64_t S = 0;
-        const int e0 = g.eoff[blk], e1 = g.eoff[blk + 1];
         // the first list: the step's own vertices (wavefront 0) and closing subtrees
         // (the others); then further closing subtrees
-        for (int c = e0, own = 1; own != 0 || c < e1;) {
-            const int k = own ? c + tid - WAVE : c + tid;
-            const bool mine = own && wave == 0, closing = !mine && k < e1;
-            int x = -1;
-            if (mine) x = valid ? u : -1;
-            else if (closing) x = g.elist[k];
+        for (int c = c0, own = 1; own != 0 || c < c1;) {
+            const bool mine = own && wave == 0;
+            if (!own) x = c + tid < c1 ? g.elist[c + tid] : -1;
             Items it{0u, 0u, 0u, 0u, 0, 0};
             int o = -1;
             if (x >= 0) {
@@ -500,11 +535,11 @@ __device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_le
             }
             if (own && valid) {
                 // this wavefront's levels of the prefix sum at tu
-                const int64_t i = min((int64_t)tu + 1, fen_len - 1);
+                const uint32_t i = min(tu + 1, (uint32_t)fen_len - 1);
                 for (int b = wave; b < levels; b += WAVES)
-                    if (i >> b & 1) S += aload(&sp.fen[i >> b << b]);
+                    if (i >> b & 1) S += b < fen.shift ? aload(&fen.low[i >> b << b]) : fen.hi[i >> b << (b - fen.shift)];
             }
-            const int32_t from = mine ? p : o + 1, to = mine ? o : n;
+            const int32_t from = mine ? p : o + 1, to = mine ? o : INT32_MAX;
             const bool f1 = it.fw != 0, r1 = it.rw != 0;
             const uint64_t fm = __ballot(f1), rm = __ballot(r1);
             const int at = take_shared(&sh.count[turn], __popcll(fm) + __popcll(rm));
@@ -514,12 +549,10 @@ __device__ int64_t f_sweep(const GraphDev &g, const SlotPtrs &sp, int64_t fen_le
             const int cnt = sh.count[turn];
             turn ^= 1;
             if (tid == 0) sh.count[turn] = 0;
-            // the tree as it stands after the step (every prefix sum has been read)
-            if (closing || (mine && o >= P0 + WAVE)) {
-                const int64_t sgn = mine ? 1 : -1;
-                fen_range_add(sp.fen, fen_len, it.flo, it.fhi, sgn * it.fw);
-                fen_range_add(sp.fen, fen_len, it.rlo, it.rhi, sgn * it.rw);
-            }
+            // the tree as it stands after the step (every prefix sum has been read): what
+            // stays open is added, what closed (and was added before) taken out
+            for (int j = tid; j < cnt; j += T)
+                if (list[j].to >= P0 + WAVE) fen_range_add(fen, list[j].lo, list[j].hi, list[j].w);
             for (int j = wave; j < cnt; j += WAVES) {
                 const SweepItem e = list[j];
                 if (e.from <= p && p <= e.to && e.lo <= tu && tu < e.hi) S += e.w;
@@ -971,8 +1004,8 @@ __device__ __forceinline__ SlotPtrs slot_ptrs(const SlotDev &sd, size_t stride) 
     sp.cstart = sd.cstart + b * (size_t)sd.chains;
     sp.rec = sd.rec ? reinterpret_cast<uint64_t *>(sd.rec) + 2 * b * stride : nullptr;
     // the numbering's arrays reuse the sampler's block (dead once the parents are in rec)
-    sp.ord = sd.rec ? reinterpret_cast<int4 *>(st) : nullptr;
-    sp.grp = sd.rec ? reinterpret_cast<int32_t *>(st + 16 * stride) : nullptr;
+    sp.leaf = reinterpret_cast<int32_t *>(st);
+    sp.grp = reinterpret_cast<int32_t *>(st + 16 * stride);
     sp.fen = sd.fen ? sd.fen + b * (size_t)sd.fen_len : nullptr;
     return sp;
 }
@@ -1018,7 +1051,7 @@ __device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<
         return;
     }
     if (tid == 0) sh.bad = 0;
-    // parent and degree into each vertex's tree record; its volume word starts at deg(v)
+    // the parent into each vertex's tree record; its volume word starts at deg(v)
     bool bad = false;
     for (int b = 0; b < g.n; b += T * NBS) {
         int32_t p[NBS];
@@ -1032,9 +1065,8 @@ __device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<
             const int v = b + k * T + tid;
             if (v >= g.n) continue;
             if (v != g.root && (p[k] < 0 || p[k] >= g.n || p[k] == v)) { bad = true; p[k] = g.root; }
-            const uint64_t d = degree(g, v);
-            astore(&sp.rec[2 * (size_t)v], d);
-            astore(&sp.rec[2 * (size_t)v + 1], (uint64_t)(uint32_t)p[k] | (d << 32));
+            astore(&sp.rec[2 * (size_t)v], (uint64_t)degree(g, v));
+            astore(&sp.rec[2 * (size_t)v + 1], (uint64_t)(uint32_t)p[k]);
         }
     }
     __syncthreads();
@@ -1045,7 +1077,7 @@ __device__ void evaluate_tree(const GraphDev &g, const SlotPtrs &sp, TreeShared<
     if (!ok) {
         // (the call fails; nothing is evaluated)
     } else if (rp.traversal == 2) {
-        f = block_sum<T>(f_sweep<T>(g, sp, fen_len, reinterpret_cast<SweepItem *>(scratch), sh), sh);
+        f = block_sum<T>(f_sweep<T>(g, sp, fen_len, *reinterpret_cast<SweepLds<T> *>(scratch), sh), sh);
     } else {
         f = block_sum<T>(f_walk<T>(g, sp), sh);
     }
