@@ -631,6 +631,19 @@ union KernelShared {
     uint32_t bitmap[CHAIN_BITS / 32];
 };
 
+// The evaluation of a chain sampler's tree: a function of its own, so that its
+// registers do not weigh on the sampler's.  Inlined, a tree took 12 to 15% longer
+// (road network of 44,780 vertices, 512 trees: 6,940 ms against 6,120 ms; grid of
+// 102,400, 8 trees: 538 ms against 478 ms).
+template <int CH>
+__device__ __attribute__((noinline)) void evaluate_chain_tree(const GraphDev &g, const SlotPtrs &sp,
+                                                              TreeShared<WAVE> &tree, KernelShared<CH> &lds,
+                                                              const RunParams &rp, int64_t fen_len, int idx) {
+    const uint64_t *arrow = sampler_ws(sp).arrow;
+    evaluate_tree<WAVE>(g, sp, tree, lds.bitmap, min(CHAIN_BITS, path_bits(g.n)), rp, fen_len, idx,
+                        [&](int v) { return (int32_t)(uint32_t)aload(&arrow[v]); });
+}
+
 // One sample s (work item idx) of graph g through the whole path in the
 // calling workgroup: the tree, then (except in RUN_SAMPLE) its numbering and
 // f.  Returns false when the workgroup must stop (an error was recorded).
@@ -653,8 +666,7 @@ __device__ bool process_one(const GraphDev &g, const SlotPtrs &sp, KernelShared<
             if (co) co[v] = (uint32_t)(ar >> 32);
         }
     } else {
-        evaluate_tree<WAVE>(g, sp, tree, lds.bitmap, min(CHAIN_BITS, path_bits(g.n)), rp, fen_len, idx,
-                            [&](int v) { return (int32_t)(uint32_t)aload(&ws.arrow[v]); });
+        evaluate_chain_tree<CH>(g, sp, tree, lds, rp, fen_len, idx);
     }
     if (rp.steps_out && lane == 0) rp.steps_out[idx] = steps;
     if (rp.iters_out && lane == 0) rp.iters_out[idx] = iters;
