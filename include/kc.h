@@ -89,6 +89,9 @@ enum {
 
 /* Options for kc_set_option. */
 enum {
+    /* WALKERS, START_ORDER, CHAINS and LEAN_LOOKS steer the chain sampler (graphs of more than
+       32,767 vertices with long walks); the frontier sampler, which the others take, has no
+       use for them.  Results depend on none of them. */
     KC_OPT_WALKERS = 1,    /* cooperating walkers per sample, 1..64 (default 64) */
     KC_OPT_SLOTS = 2,      /* samples in flight per launch (0 = sized from free HBM) */
     KC_OPT_TRAVERSAL = 3,  /* KC_TRAV_* */

@@ -1,33 +1,26 @@
-// kc_device.hip -- gfx950 kernels of the Kemeny-constant estimator.
+// kc_device.hip -- the chain sampler, and the kernels around the samplers: edge
+// updates of resident trees, exact sums, fills and counters.
 //
-// One wavefront (64 lanes, one workgroup) owns one sample at a time and runs
-// its whole hot path in a persistent loop:
+// Uniform spanning trees by Wilson's algorithm (paper section 2.2 and Algorithm
+// 1), organised as cooperative cycle popping.  The k-th draw at vertex v of
+// sample s always uses the same Philox4x32-10 arrow, so the tree and the
+// per-vertex draw counts are the unique cycle-popping outcome of those arrow
+// stacks, whatever order the pops happen in.  Two samplers find it:
 //
-//   1. Uniform spanning tree by Wilson's algorithm (paper section 2.2 and
-//      Algorithm 1), organised as cooperative cycle popping: up to 64 lanes
-//      drive loop-erased walks ("chains") of the same sample at once; a chain
-//      whose arrow lands on another chain's path is parked in an LDS table
-//      and its lane moves on.  The k-th draw at vertex v of sample s always
-//      uses the same Philox4x32-10 arrow, so the tree and the per-vertex draw
-//      counts are the unique cycle-popping outcome of those arrow stacks,
-//      whatever order the pops happen in.
-//   2. Subtree volumes vol(v) of the sampled tree (Algorithm 1, the loop that
-//      fills vol[]) by bottom-up carriers with one 64-bit atomic per vertex,
-//      and a volume-weighted preorder numbering tin(v) of the tree (top-down,
-//      replaying the bottom-up completion groups in reverse).  A vertex u lies
-//      in Sub(tau, v) iff tin(v) <= tin(u) < tin(v) + vol(v).
-//   3. f(tau) of Theorem 3.3 via Theorem 3.4: every tree edge (v, p(v)) that
-//      is also a tau0 edge contributes +-(2m - vol(v)) to every u in the
-//      intersection of a tau subtree and a tau0 subtree.  Two evaluations:
-//        walk  -- per u, walk u's tau0 ancestors (depth0 steps);
-//        sweep -- visit tau0 in preorder, 64 positions per step, keeping the
-//                 active tau0 ancestors' contributions as range updates in a
-//                 Fenwick tree indexed by tin (O(log m) per update/query).
-//   4. Exact reduction: sum f and sum f^2 in 128-bit integers.
+//   the frontier sampler (kc_frontier.hip), one workgroup per sample, for graphs
+//   whose words fit LDS and for larger ones with short walks;
+//   the chain sampler (here), one wavefront per sample, for large sparse graphs:
+//   up to 64 lanes drive loop-erased walks ("chains") of the same sample at once;
+//   a chain whose arrow lands on another chain's path is parked in an LDS table
+//   and its lane moves on.
+//
+// Every kernel takes sample after sample from a counter and evaluates f of each
+// tree where it was sampled (kc_tree.h); sum f and sum f^2 are exact, in 128-bit
+// integers.
 //
 // Cross-lane communication through global memory uses workgroup-scope
 // relaxed atomics (L2-coherent on gfx950) ordered by workgroup fences; every
-// lane of a sample is in the same wavefront.
+// lane of a sample of the chain sampler is in the same wavefront.
 
 #include <algorithm>
 

@@ -135,6 +135,10 @@ static_assert(LDS_MAX_N <= (int64_t)L_MASK, "vertices fit a word's fields");
 // whose walks were cut get places in a table.  Each walks to the next of them
 // (every cycle holds one, and no walk goes further than that), and the cycles
 // are those of the table's links.
+//
+// Trees of the chain sampler (a wavefront each, its words in L2) and these: the
+// 32 x 32 grid, 2,000 trees 50.9 -> 10.9 ms, one tree 3.8 -> 0.86 ms; a road-like
+// graph of 8,609 vertices, 256 trees 519 -> 198 ms.
 // Returns the total number of draws, or -1 (error recorded in ctl).
 template <int T>
 __device__ __forceinline__ int64_t sample_lds(const GraphDev &g, const FrontierWS &ws, uint32_t *words,
@@ -340,6 +344,11 @@ constexpr uint32_t G_MASK = (1u << 30) - 1, G_SET = 1u << 30, G_FLAG = 1u << 31;
 // One sample's tree, its words in the slot's block.  The first round walks from
 // every vertex (there the smallest index on a cycle finds it, without flags),
 // the later ones from the frontier.
+//
+// Bound by the random lines of the words and graph records: about two per draw
+// where the chain sampler has a claim, an arrow and a record.  A power-law graph of
+// 481,994 vertices, 2,048 trees 174 -> 91 ms, one tree 65 -> 6.5 ms; a dense one of
+// 150,001 vertices, 2,560 trees 90 -> 30 ms.
 template <int T>
 __device__ __forceinline__ int64_t sample_global(const GraphDev &g, const FrontierWS &ws, FrontierShared &sh,
                                                  TreeShared<T> &tree, uint64_t seed, uint64_t s, int64_t iter_cap,

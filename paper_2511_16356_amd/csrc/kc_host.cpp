@@ -210,9 +210,16 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 
 }  // namespace
 
-// The frontier sampler takes every graph whose words fit a CU's LDS.  Of the
-// larger ones it takes those with short walks: a shallow reference tree (the
-// traversal's own rule) and a mean degree of at least 8.
+// The frontier sampler takes every graph whose words fit a CU's LDS: a step of a
+// walk is an LDS read there, and an L2 round trip in the chain sampler (2,000 trees
+// of the 32 x 32 grid: 10.9 against 50.9 ms; 256 of a road-like graph of 8,609
+// vertices: 198 against 519 ms).  Of the larger graphs it takes those with short
+// walks, a shallow reference tree (the traversal's own rule) and a mean degree of at
+// least 8: there a round pops thousands of cycles (2,048 trees of a power-law graph
+// of 481,994 vertices: 91 against 174 ms; 2,560 of a dense one of 150,001: 30 against
+// 90 ms).  On the others a round lasts as long as its longest walk through L2, while
+// chains wait for none (grid of 102,400, 8 trees: 1,654 against 478 ms for the chain
+// sampler; 512 trees: 5,690 against 1,596 ms).
 int kc_host::route_of(const kc_graph *g) {
     if (g->n <= kc::LDS_MAX_N) return kc::ROUTE_LDS;
     return g->two_m >= 8 * g->n && g->depth0 <= 12 ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;

@@ -28,21 +28,21 @@ struct GraphDev {
     int32_t anc_depth;    //       levels in anc0 (4 or 8), 0 without the table
 };
 
-// Per-slot workspace: one slot = one sample in flight = one wavefront.
+// Per-slot workspace: one slot = one sample in flight = one workgroup.
 //
-// A slot's state block (state_bytes(stride) bytes) holds the sampler's arrays:
+// A slot's state block (state_bytes(stride) bytes) holds the chain sampler's arrays:
 //   tag words  uint64 [stride] at 0: tag/flag bits | first parked chain + 1 << 32
 //   arrow words uint64 [stride] at 8 stride: arrow target | draws << 32
 //   restart ring int32 [stride] at 16 stride
-// Once the tree's parents are copied into rec they are dead, and what evaluates the
-// tree reuses the block (kc_tree.h; the frontier sampler has its own layout of it).
+// The frontier sampler has its own layout of it.  Once the tree's parents are copied
+// into rec they are dead, and what evaluates the tree reuses the block (kc_tree.h).
 struct SlotDev {
     unsigned char *state; // [slots * state_bytes(stride)]
-    int4 *queue;     // [slots*chains] sampler: ready tasks
-    int32_t *cstart; // [slots*chains] sampler: chain start vertices
+    int4 *queue;     // [slots*chains] chain sampler: ready tasks
+    int32_t *cstart; // [slots*chains] chain sampler: chain start vertices
     int64_t chains;  // per-slot stride of queue and cstart
-    int4 *rec;       // [slots*stride] the numbered tree, 16 bytes per vertex: numbering word, then
-                     // parent | deg, later parent | tin; null without the traversal
+    int4 *rec;       // [slots*stride] the tree being evaluated, 16 bytes per vertex (kc_tree.h);
+                     // null without the traversal
     int64_t *fen;    // [slots*fen_len] Fenwick tree (sweep traversal only)
     int64_t fen_len; // per-slot length of fen: 2m + 2 (0 if not allocated)
     int64_t stride;  // vertices per slot (a batch: its largest graph's n)
@@ -65,7 +65,8 @@ struct BatchJob {
 // the frontier sampler (kc_frontier.hip) with its words in LDS or in the slot's
 // state block.
 enum Route { ROUTE_CHAINS = 0, ROUTE_LDS = 1, ROUTE_GLOBAL = 2 };
-constexpr int64_t LDS_MAX_N = (1 << 15) - 1;  // a word holds two vertices and two flags
+// A word holds two vertices and two flags, and the words of one sample fit a CU's LDS.
+constexpr int64_t LDS_MAX_N = (1 << 15) - 1;
 // Bits of the map of tau0 vertices that the evaluation on a shallow tau0 keeps in
 // LDS: a power of two, one bit per vertex up to 2^19.
 __host__ __device__ inline int path_bits(int64_t n) {
