@@ -766,7 +766,7 @@ def main():
                         "; %d tree samples per step (one persistent launch%s), Philox seed %d" %
                         (B, "" if args.direct else ", replayed from a captured HIP graph", args.seed),
             "samples_per_step": B,
-            "parallelism": "1 GPU, one wavefront per sample in flight",
+            "parallelism": "1 GPU, one workgroup per sample in flight",
             "chains_per_sample": G.info["chains"],
         },
         "kappa": pooled.kappa,
