@@ -219,7 +219,10 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 // of 481,994 vertices: 91 against 174 ms; 2,560 of a dense one of 150,001: 30 against
 // 90 ms).  On the others a round lasts as long as its longest walk through L2, while
 // chains wait for none (grid of 102,400, 8 trees: 1,654 against 478 ms for the chain
-// sampler; 512 trees: 5,690 against 1,596 ms).
+// sampler; 512 trees: 5,690 against 1,596 ms).  A road-like graph of 44,780 would
+// gain (512 trees: 3,199 against 6,145 ms), a grid thinned to the same degree lose
+// (40,000 vertices, 8 trees: 1,128 against 583 ms); nothing known of a graph before
+// its walks tells the two apart, so both stay with the chains.
 int kc_host::route_of(const kc_graph *g) {
     if (g->n <= kc::LDS_MAX_N) return kc::ROUTE_LDS;
     return g->two_m >= 8 * g->n && g->depth0 <= 12 ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
