@@ -351,7 +351,9 @@ kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
         free_host_block(g);
         HIP_TRY(hipHostMalloc((void **)&g->h_red, sizeof(kc::ReduceOut) + sizeof(int64_t) * (size_t)slots,
                               hipHostMallocMapped | hipHostMallocCoherent));
-        HIP_TRY(hipHostGetDevicePointer((void **)&g->d_host_red, g->h_red, 0));
+        const hipError_t e = hipHostGetDevicePointer((void **)&g->d_host_red, g->h_red, 0);
+        if (e != hipSuccess) free_host_block(g);  // a block without a device view is not kept: reductions write to it
+        HIP_TRY(e);
         g->h_progress = reinterpret_cast<int64_t *>(g->h_red + 1);
         g->d_progress = reinterpret_cast<int64_t *>(g->d_host_red + 1);
         g->progress_len = slots;

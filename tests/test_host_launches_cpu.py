@@ -1,0 +1,84 @@
+"""What the library's host code launches, on the CPU: the built library over a stand-in
+runtime (hip_stub.cpp) that writes the launches down and runs none of them.  Each test is a
+program of its own, so that the stand-in never meets the real runtime's state."""
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, sys
+stub = ctypes.CDLL(%(stub)r, ctypes.RTLD_GLOBAL)
+for f in ("stub_name", "stub_out"):
+    getattr(stub, f).restype = ctypes.c_char_p if f == "stub_name" else ctypes.c_void_p
+stub.stub_lds.restype = ctypes.c_size_t
+stub.stub_set.argtypes = [ctypes.c_size_t, ctypes.c_int]
+sys.path.insert(0, %(root)r)
+import numpy as np
+import graphgen as gen
+import paper_2511_16356_amd as kc
+lib = kc.library()
+def graph(g, root=-1):
+    off, idx = np.ascontiguousarray(g.offsets, np.int64), np.ascontiguousarray(g.indices, np.int32)
+    h = ctypes.c_void_p()
+    st = lib.kc_graph_create(g.n, off.ctypes.data, 1, idx.ctypes.data, root, None, ctypes.byref(h))
+    assert st == 0, lib.kc_last_error()
+    return h
+def launches(clear=True):
+    out = [dict(name=stub.stub_name(i).decode(), grid=stub.stub_grid(i), block=stub.stub_block(i), lds=stub.stub_lds(i),
+                out=stub.stub_out(i)) for i in range(stub.stub_launches())]
+    if clear: stub.stub_clear()
+    return out
+def estimate(h, count):
+    stub.stub_clear()
+    st = lib.kc_estimate(h, 1, 0, count, ctypes.byref(kc._Result()), None, None, None)
+    return st, launches()
+def sampler(ls):
+    return [l for l in ls if "persistent_kernel" in l["name"] or "frontier" in l["name"] or "batch_kernel" in l["name"]][0]
+def kind(ls):
+    l = sampler(ls)
+    return "chains" if "frontier" not in l["name"] else "lds" if l["block"] == 256 else "global"
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    import paper_2511_16356_amd as kc
+    if not os.path.exists(kc.LIB_PATH):
+        from paper_2511_16356_amd import build_lib
+        build_lib.build()
+    import graphgen
+    graphgen.build()
+    so = str(tmp_path_factory.mktemp("stub") / "libhip_stub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_stub.cpp")], check=True)
+
+    def go(body):
+        code = PRELUDE % {"stub": so, "root": ROOT} + textwrap.dedent(body)
+        r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-3000:]
+        return json.loads(r.stdout.strip().splitlines()[-1])
+    return go
+
+
+def test_a_result_block_without_a_device_view_is_not_used(run):
+    """The pinned block is replaced when a launch has more slots than it holds counters; if its
+    device view cannot be had, the call fails, and later reductions must not write through null."""
+    r = run("""
+        h = graph(gen.grid(8, 8))
+        assert lib.kc_samples_init(h, 1, 16, None) == 0
+        stub.stub_fail(b"hipHostGetDevicePointer")
+        st, _ = estimate(h, 400)
+        stub.stub_clear()
+        q = lib.kc_samples_query(h, ctypes.byref(kc._Result()), None)
+        out = [l["out"] for l in launches() if "reduce_kernel" in l["name"]]
+        st2, _ = estimate(h, 400)
+        print(json.dumps(dict(st=st, q=q, out=out, st2=st2)))
+    """)
+    assert r["st"] != 0 and r["q"] == 0 and r["st2"] == 0
+    assert len(r["out"]) == 1 and r["out"][0]
