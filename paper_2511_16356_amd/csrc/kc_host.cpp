@@ -214,18 +214,32 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 // walk is an LDS read there, and an L2 round trip in the chain sampler (2,000 trees
 // of the 32 x 32 grid: 10.9 against 50.9 ms; 256 of a road-like graph of 8,609
 // vertices: 198 against 519 ms).  Of the larger graphs it takes those with short
-// walks, a shallow reference tree (the traversal's own rule) and a mean degree of at
-// least 8: there a round pops thousands of cycles (2,048 trees of a power-law graph
+// walks: there a round pops thousands of cycles (2,048 trees of a power-law graph
 // of 481,994 vertices: 91 against 174 ms; 2,560 of a dense one of 150,001: 30 against
 // 90 ms).  On the others a round lasts as long as its longest walk through L2, while
 // chains wait for none (grid of 102,400, 8 trees: 1,654 against 478 ms for the chain
-// sampler; 512 trees: 5,690 against 1,596 ms).  A road-like graph of 44,780 would
-// gain (512 trees: 3,199 against 6,145 ms), a grid thinned to the same degree lose
-// (40,000 vertices, 8 trees: 1,128 against 583 ms); nothing known of a graph before
-// its walks tells the two apart, so both stay with the chains.
+// sampler; 512 trees: 5,690 against 1,596 ms).
+//
+// Walks are short where they soon meet the root: no vertex far from it (the depth of
+// a breadth-first search, whatever the reference tree), a mean degree of at least 8,
+// and a root that holds at least 16 / n of all edge ends, so that a walk returns to it
+// every 2m / deg(root) <= n / 16 steps.  Power laws (exponent 2 to 3, largest degree
+// 300 to 2,000, 33,000 to 300,000 vertices) and preferential attachment return every
+// n / 170 to n / 27 steps: 1.3 to 10 times the chains' speed at 1 to 2,560 trees.  Random
+// graphs of degree 8 to 76 and two of them joined by one edge return every 0.35 n to
+// 0.7 n steps: 0.28 to 1.3 times at 64 trees and more (100,000 vertices of degree 20,
+// 2,560 trees: 1,160 ms against 348 ms for the chains; two halves of 50,000, 512 trees:
+// 11.1 against 6.5 s).
+//
+// A road-like graph of 44,780 would gain (512 trees: 3,199 against 6,145 ms), a grid
+// thinned to the same degree lose (40,000 vertices, 8 trees: 1,128 against 583 ms);
+// nothing known of a graph before its walks tells the two apart, so both stay with the
+// chains.
 int kc_host::route_of(const kc_graph *g) {
     if (g->n <= kc::LDS_MAX_N) return kc::ROUTE_LDS;
-    return g->two_m >= 8 * g->n && g->depth0 <= 12 ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
+    const int64_t root_degree = g->h_off[(size_t)g->root + 1] - g->h_off[(size_t)g->root];
+    const bool short_walks = g->two_m >= 8 * g->n && g->bfs_depth <= 12 && 16 * g->two_m <= g->n * root_degree;
+    return short_walks ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
 }
 
 // One slot per resident workgroup of the launch's kernel (per_cu of them on a CU).
@@ -458,6 +472,7 @@ kc_status prepare_graph(const std::vector<int64_t> &off, const std::vector<int32
     }
     if ((int64_t)order.size() != n)
         return fail(KC_ERR_DISCONNECTED, "only %zu of %lld vertices reachable from the root", order.size(), (long long)n);
+    pg->bfs_depth = dist[(size_t)order.back()];
     std::vector<int32_t> &p0 = pg->p0;
     p0.assign((size_t)n, -1);
     int32_t depth0 = 0;
@@ -638,6 +653,7 @@ kc_status rebuild_graph(kc_graph *g, int32_t root, hipStream_t stream, PreparedG
     g->two_m = g->h_off[(size_t)n];
     g->root = pg.root;
     g->depth0 = pg.depth0;
+    g->bfs_depth = pg.bfs_depth;
     g->nblk = pg.nblk;
     g->max_degree = 0;
     for (int64_t v = 0; v < n; ++v)

@@ -13,6 +13,7 @@
 
 struct PreparedGraph {
     int32_t root = -1, depth0 = 0, nblk = 0, anc_depth = 0;
+    int32_t bfs_depth = 0;  // of the breadth-first search from the root, whatever tau0
     std::vector<int32_t> order, p0, pre0, out0, eoff, elist, vrec, anc0;
     std::vector<uint32_t> int0;
 };
@@ -20,6 +21,7 @@ struct PreparedGraph {
 struct kc_graph {
     int64_t n = 0, two_m = 0;
     int32_t root = -1, depth0 = 0, max_degree = 0;
+    int32_t bfs_depth = 0;  // largest distance from the root
     int32_t traversal = KC_TRAV_WALK;
     int32_t walkers = 64;
     int32_t chains = 1024;

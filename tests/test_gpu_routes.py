@@ -1,0 +1,83 @@
+"""Every way a graph's trees are sampled, bit for bit against the CPU oracle (exact
+integers: no tolerance), on graphs the dispatch sends there.
+
+The rounds a call reports (sampler_iterations) tell the samplers apart: with one walker
+the chain sampler takes many times the rounds, the frontier sampler as many as before.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kc():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2511_16356_amd as kc
+    kc.library()
+    return kc
+
+
+def random_graph(gen, n, deg, hub=0, seed=1):
+    """Mean degree deg on a ring; with hub, vertex 0 is joined to that many others."""
+    rng = np.random.default_rng(seed)
+    k = n * (deg - 2) // 2
+    u = np.concatenate([np.arange(n), rng.integers(0, n, k), np.zeros(hub, np.int64)])
+    v = np.concatenate([(np.arange(n) + 1) % n, rng.integers(0, n, k), np.arange(1, 1 + hub)])
+    return gen.from_edges("random", n, u[u != v], v[u != v])
+
+
+def samples_match(G, oracle_lib, P, seed, first, count):
+    par, cnt, steps = oracle_lib.sample(P, seed=seed, s0=first, count=count, threads=8)
+    got = G.sample_trees(seed, first, count)
+    assert np.array_equal(got[0].cpu().numpy(), par)
+    assert np.array_equal(got[1].cpu().numpy().astype(np.uint32), cnt)
+    assert np.array_equal(got[2].cpu().numpy(), steps)
+    f, _ = oracle_lib.estimate_f(P, seed=seed, s0=first, count=count, threads=8)
+    est, gf, gs = G.estimate(seed, first, count, per_sample=True)
+    assert np.array_equal(gf.cpu().numpy(), f) and np.array_equal(gs.cpu().numpy(), steps)
+    return est
+
+
+def on_chains(kc, G, seed, first, count):
+    rounds = []
+    for walkers in (64, 1):
+        G.set_option(kc.KC_OPT_WALKERS, walkers)
+        rounds.append(G.estimate(seed, first, count).sampler_iterations)
+    G.set_option(kc.KC_OPT_WALKERS, 64)
+    return rounds[1] > 4 * rounds[0]
+
+
+def test_large_lean_graph_with_a_deep_reference_tree(kc, oracle_lib, gen):
+    """The frontier sampler with its words in memory, tau0 breadth-first (path sums) and
+    depth-first (the sweep, a workgroup of that sampler's threads)."""
+    g = random_graph(gen, 33001, 10, hub=2500)
+    P = oracle_lib.prepare_graph(g)
+    with kc.Graph.from_graph(g) as G:
+        samples_match(G, oracle_lib, P, 21, 5, 4)
+        G.set_tau0(kc.KC_TAU0_DFS)
+        assert G.info["depth0"] > 1000 and G.info["traversal"] == kc.KC_TRAV_SWEEP
+        Q = oracle_lib.with_tau0(P, oracle_lib.dfs_tree(g.offsets, g.indices, P.root))
+        samples_match(G, oracle_lib, Q, 21, 5, 4)
+        assert not on_chains(kc, G, 21, 5, 4)
+
+
+def test_batch_of_words_in_lds_and_in_memory(kc, oracle_lib, gen):
+    gs = [gen.grid(32, 32), random_graph(gen, 33000, 10, hub=2500), gen.chung_lu(3000, 2.2, 10.0, 270.0, seed=1)]
+    counts = [9, 3, 7]
+    Gs = [kc.Graph.from_graph(g) for g in gs]
+    with kc.Batch(Gs, [4, 5, 6], [0, 10, 20], counts) as batch:
+        for launch in range(3):
+            batch.launch()
+            ests, done = batch.results()
+            assert done == launch + 1
+            for j, (g, first) in enumerate(zip(gs, (0, 10, 20))):
+                P = oracle_lib.prepare_graph(g)
+                f, _ = oracle_lib.estimate_f(P, seed=4 + j, s0=first + launch * counts[j], count=counts[j], threads=8)
+                assert np.array_equal(batch.f(j).cpu().numpy(), f)
+                K, se, s1, _ = oracle_lib.reduce_estimate(f, g.two_m)
+                assert ests[j].kappa == K and ests[j].sum_f == s1
+    for G in Gs:
+        G.close()

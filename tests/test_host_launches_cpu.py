@@ -82,3 +82,42 @@ def test_a_result_block_without_a_device_view_is_not_used(run):
     """)
     assert r["st"] != 0 and r["q"] == 0 and r["st2"] == 0
     assert len(r["out"]) == 1 and r["out"][0]
+
+
+ROUTE_GRAPHS = """
+def random_graph(n, deg, seed=1):
+    rng = np.random.default_rng(seed)
+    k = n * (deg - 2) // 2
+    u = np.concatenate([np.arange(n), rng.integers(0, n, k)])
+    v = np.concatenate([(np.arange(n) + 1) % n, rng.integers(0, n, k)])
+    return gen.from_edges("random", n, u[u != v], v[u != v])
+def hubs(n, deg, hub=2000, seed=1):  # the same with a vertex that `hub` others are joined to
+    g = random_graph(n, deg, seed)
+    e = np.array([(x, y) for x, y in g.edges()])
+    return gen.from_edges("hubs", n, np.concatenate([e[:, 0], np.zeros(hub, int)]), np.concatenate([e[:, 1], np.arange(2, 2 + hub)]))
+"""
+
+
+def test_route_follows_the_graph_not_tau0(run):
+    """Above the LDS sizes the frontier sampler takes a lean graph whose root holds many edge ends,
+    with any reference tree; random graphs without such a root (long walks) and sparse ones go to
+    the chains."""
+    r = run(ROUTE_GRAPHS + """
+        out = {}
+        h = graph(hubs(33000, 10))
+        out["hubs"] = kind(estimate(h, 64)[1])
+        assert lib.kc_set_tau0(h, kc.KC_TAU0_DFS, None, None) == 0
+        info = kc._Info(); lib.kc_graph_get_info(h, ctypes.byref(info))
+        out["depth"] = info.depth0
+        out["hubs dfs"] = kind(estimate(h, 64)[1])
+        assert lib.kc_set_tau0(h, kc.KC_TAU0_BFS, None, None) == 0
+        out["hubs bfs"] = kind(estimate(h, 64)[1])
+        out["leaf root"] = kind(estimate(graph(hubs(33000, 10), root=30000), 64)[1])
+        out["random"] = kind(estimate(graph(random_graph(33000, 12)), 64)[1])
+        out["grid"] = kind(estimate(graph(gen.grid(200, 200)), 64)[1])
+        out["small"] = kind(estimate(graph(random_graph(2000, 12)), 64)[1])
+        print(json.dumps(out))
+    """.replace("\n        ", "\n"))
+    assert r.pop("depth") > 100
+    assert r == {"hubs": "global", "hubs dfs": "global", "hubs bfs": "global", "leaf root": "chains", "random": "chains",
+                 "grid": "chains", "small": "lds"}
