@@ -104,8 +104,6 @@ kc_status kc_batch_create(kc_graph *const *graphs, int32_t k, const uint64_t *se
     // workgroups), within its memory budget for slots sized for the largest graph
     const size_t n = (size_t)max_n, ch = (size_t)kc::sampler_chains();
     const int64_t per_slot = kc::state_bytes(max_n) + (int64_t)(20 * ch + 16 * n + 8 * (size_t)max_fen);
-    int want = graphs[0]->slots_opt > 0 ? graphs[0]->slots_opt : resident_slots(blocks_per_cu(a, b->chains));
-    want = (int)std::min<int64_t>(want, total);
     size_t free_b = 0, total_b = 0;
     hipError_t e = hipMemGetInfo(&free_b, &total_b);
     if (e != hipSuccess) {
@@ -113,7 +111,13 @@ kc_status kc_batch_create(kc_graph *const *graphs, int32_t k, const uint64_t *se
         return fail(KC_ERR_DEVICE, "hipMemGetInfo: %s", hipGetErrorString(e));
     }
     const int64_t budget = workspace_budget(graphs[0], free_b);
-    int slots = (int)std::min<int64_t>(want, budget / per_slot);
+    // one kernel samples every job: the chains' by the number of samples only if all would take it
+    const int fit = (int)std::min<int64_t>(graphs[0]->slots_opt > 0 ? graphs[0]->slots_opt : 1 << 20, budget / per_slot);
+    bool chains = true;
+    for (int32_t j = 0; j < k; ++j) chains = chains && route_of(graphs[j], total, fit) == kc::ROUTE_CHAINS;
+    for (int32_t j = 0; chains && j < k; ++j) a.job[j].route = kc::ROUTE_CHAINS;
+    const int want = graphs[0]->slots_opt > 0 ? graphs[0]->slots_opt : resident_slots(blocks_per_cu(a, b->chains));
+    int slots = (int)std::min<int64_t>(std::min<int64_t>(want, total), fit);
     slots = balanced_slots(slots, total);
     if (slots < 1) {
         batch_free(b);

@@ -235,11 +235,27 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 // thinned to the same degree lose (40,000 vertices, 8 trees: 1,128 against 583 ms);
 // nothing known of a graph before its walks tells the two apart, so both stay with the
 // chains.
-int kc_host::route_of(const kc_graph *g) {
-    if (g->n <= kc::LDS_MAX_N) return kc::ROUTE_LDS;
+//
+// Words in LDS leave a CU one workgroup from 17,900 vertices on and two from 11,200
+// (256 and 512 trees in flight), where the chains have 2,560: with many samples they
+// catch up.  Trees of one workgroup per CU, LDS against chains: grids of 18,225 / 24,025 /
+// 32,400 vertices 265 / 333 / 425 against 318 / 412 / 495 ms for 1,024 trees, 410 / 579 / 823
+// against 336 / 446 / 567 for 2,560; of the other sparse graphs and random graphs those of
+// 20,000 to 32,000 vertices cross at 2,560 to 5,120 (road-like of 32,314: 2.83 against 2.56 s for
+// 2,560, 5.2 against 3.4 for 5,120; mean degree 4: 73 against 74 ms, then 141 against 115).
+// Two per CU: grids of 12,100 to 16,900 cross at 6,000 to 8,000 (16,900: 431 against 452 ms for
+// 5,120, 769 against 667 for 10,240), other graphs do not up to 8,192 (mean degree 4, 14,000
+// vertices: 57 against 77 ms).  Hence the limits below, in full waves of trees; the chains need
+// most of their slots for it (2,048 of 2,560).
+int kc_host::route_of(const kc_graph *g, int64_t count, int slots) {
     const int64_t root_degree = g->h_off[(size_t)g->root + 1] - g->h_off[(size_t)g->root];
-    const bool short_walks = g->two_m >= 8 * g->n && g->bfs_depth <= 12 && 16 * g->two_m <= g->n * root_degree;
-    return short_walks ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
+    const bool meets_root = g->bfs_depth <= 12 && 16 * g->two_m <= g->n * root_degree;
+    if (g->n > kc::LDS_MAX_N) return meets_root && g->two_m >= 8 * g->n ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
+    if (meets_root || slots < std::min<int64_t>(count, 2048) || count <= 7 * resident_slots(1)) return kc::ROUTE_LDS;
+    const bool lattice = 2 * g->two_m >= 7 * g->n && g->bfs_depth > 12;
+    const int per_cu = kc::frontier_blocks_per_cu(kc::ROUTE_LDS, g->n);
+    const int waves = per_cu == 1 ? (lattice ? 7 : 12) : per_cu == 2 && lattice ? 14 : 0;
+    return waves > 0 && count > (int64_t)waves * resident_slots(per_cu) ? kc::ROUTE_CHAINS : kc::ROUTE_LDS;
 }
 
 // One slot per resident workgroup of the launch's kernel (per_cu of them on a CU).
@@ -249,8 +265,7 @@ int kc_host::resident_slots(int per_cu) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 1024;
     return cus > 0 && per_cu > 0 ? cus * per_cu : 1024;
 }
-int kc_host::default_slots(const kc_graph *g, int mode) {
-    const int route = route_of(g);
+int kc_host::default_slots(const kc_graph *g, int mode, int route) {
     int per_cu = 0;
     if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n, g->traversal);
     else if (route == kc::ROUTE_CHAINS) per_cu = kc::persistent_blocks_per_cu(g->chains);
@@ -260,7 +275,8 @@ int kc_host::default_slots(const kc_graph *g, int mode) {
 
 int kc_host::workspace_slots(const kc_graph *g, int count) {
     if (count <= resident_slots(1)) return count;  // every CU holds a workgroup of any of the kernels
-    return std::max(default_slots(g), default_slots(g, kc::RUN_EVALUATE));
+    const int route = route_of(g, count);
+    return std::max(default_slots(g, kc::RUN_ESTIMATE, route), default_slots(g, kc::RUN_EVALUATE, route));
 }
 
 // Workspace bytes a launch may allocate: the graph's budget option, else 80%
@@ -349,7 +365,8 @@ kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
     int slots = 0;
     kc_status st = ensure_workspace(g, want, trav, fen, stream, &slots);
     if (st != KC_OK) return st;
-    if (g->slots_opt <= 0 && slots > resident_slots(1)) slots = std::min(slots, default_slots(g, rp.mode));
+    const int route = route_of(g, rp.count, slots);
+    if (g->slots_opt <= 0 && slots > resident_slots(1)) slots = std::min(slots, default_slots(g, rp.mode, route));
     slots = balanced_slots(slots, rp.count);
     kc::SlotDev sd;
     sd.state = g->d_state;
@@ -361,6 +378,7 @@ kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
     sd.fen = fen ? g->d_fen : nullptr;
     sd.fen_len = fen ? g->two_m + 2 : 0;
     fill_run_options(g, rp);
+    rp.route = route;
     if (g->progress_len < slots) {
         free_host_block(g);
         HIP_TRY(hipHostMalloc((void **)&g->h_red, sizeof(kc::ReduceOut) + sizeof(int64_t) * (size_t)slots,

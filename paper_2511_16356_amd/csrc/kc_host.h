@@ -98,12 +98,12 @@ kc_status fail(kc_status st, const char *fmt, ...);
 int64_t slot_bytes(const kc_graph *g, bool trav, bool fen);
 // Samples in flight when the graph's slots option is 0: resident workgroups of the kernel.
 int resident_slots(int per_cu);
-int default_slots(const kc_graph *g, int mode = kc::RUN_ESTIMATE);  // resident workgroups of the launch's kernel
+int default_slots(const kc_graph *g, int mode, int route);  // resident workgroups of the launch's kernel
 // Slots the workspace is sized for when the slots option is 0: the most any launch of up to
 // count samples on g takes.
 int workspace_slots(const kc_graph *g, int count);
-// How g's trees are sampled (kc::Route).
-int route_of(const kc_graph *g);
+// How a launch of count samples with up to `slots` in flight samples g's trees (kc::Route).
+int route_of(const kc_graph *g, int64_t count = 1, int slots = 1 << 20);
 int64_t workspace_budget(const kc_graph *g, size_t free_b);
 // Slots that split `count` samples into equal waves (at most `slots`).
 int balanced_slots(int slots, int64_t count);

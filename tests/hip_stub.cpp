@@ -88,7 +88,12 @@ int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipGetDevicePropertiesR0600(void *, int) { return 1; }
 int hipFuncSetAttribute(const void *f, int, int v) { lds_limit[f] = (size_t)v; return 0; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = per_cu; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int, size_t) {
+    // the one-wavefront kernels of the chain sampler are bound by their table's LDS
+    const std::string &k = names()[f];
+    *n = k.find("frontier") != std::string::npos || k.find("tree_kernel") != std::string::npos ? per_cu : 10;
+    return 0;
+}
 int hipMemGetInfo(size_t *f, size_t *t) { *f = free_bytes; *t = free_bytes; return 0; }
 int hipMalloc(void **p, size_t n) {
     if (fails("hipMalloc")) return 2;

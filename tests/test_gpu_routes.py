@@ -81,3 +81,29 @@ def test_batch_of_words_in_lds_and_in_memory(kc, oracle_lib, gen):
                 assert ests[j].kappa == K and ests[j].sum_f == s1
     for G in Gs:
         G.close()
+
+
+def test_many_samples_on_the_chains_equal_few_in_lds(kc, gen):
+    """A grid that leaves one workgroup per CU: above 1,792 samples a call takes the chains, its
+    parts do not; a workspace without slots for the chains keeps LDS.  The sums and each f agree."""
+    count = 2000
+    with kc.Graph.from_graph(gen.grid(135, 135)) as G:
+        whole, f, steps = G.estimate(17, 900, count, per_sample=True)
+        assert on_chains(kc, G, 17, 900, 1793) and not on_chains(kc, G, 17, 900, 8)
+        parts = [G.estimate(17, 900 + a, 500, per_sample=True) for a in range(0, count, 500)]
+        for i, (_, pf, ps) in enumerate(parts):
+            assert (pf == f[500 * i:500 * i + 500]).all() and (ps == steps[500 * i:500 * i + 500]).all()
+        pooled = G.combine([p[0] for p in parts])
+        assert (pooled.sum_f, pooled.sum_f2, pooled.total_steps) == (whole.sum_f, whole.sum_f2, whole.total_steps)
+        par, cnt, _ = G.sample_trees(17, 900, 1800)
+        few, fewcnt, _ = G.sample_trees(17, 1400, 40)
+        assert (par[500:540] == few).all() and (cnt[500:540] == fewcnt).all()
+        with kc.Batch([G], [17], [900], [count]) as batch:
+            for launch in range(2):
+                batch.launch()
+                est, _ = batch.results()
+                if launch == 0:
+                    assert est[0].sum_f == whole.sum_f and (batch.f(0) == f).all()
+        G.set_option(kc.KC_OPT_SLOTS, 300)
+        assert not on_chains(kc, G, 17, 900, 1793)
+        assert G.estimate(17, 900, count).sum_f == whole.sum_f

@@ -121,3 +121,49 @@ def test_route_follows_the_graph_not_tau0(run):
     assert r.pop("depth") > 100
     assert r == {"hubs": "global", "hubs dfs": "global", "hubs bfs": "global", "leaf root": "chains", "random": "chains",
                  "grid": "chains", "small": "lds"}
+
+
+@pytest.mark.parametrize("per_cu,count,expect", [(1, 1792, "lds"), (1, 1793, "chains"), (2, 7168, "lds"), (2, 7169, "chains"),
+                                                 (3, 100000, "lds")])
+def test_many_samples_of_a_lattice_take_the_chains(run, per_cu, count, expect):
+    """Words in LDS let few trees be in flight; the limits are whole waves of them."""
+    r = run("""
+        stub.stub_set(64 << 30, %d)
+        h = graph(gen.grid(135, 135))
+        ls = estimate(h, %d)[1]
+        print(json.dumps(dict(kind=kind(ls), slots=sampler(ls)["grid"])))
+    """ % (per_cu, count))
+    assert r["kind"] == expect
+    most = min(count, 2560 if expect == "chains" else 256 * per_cu)
+    assert most // 2 < r["slots"] <= most
+
+
+def test_many_samples_with_few_slots_or_a_short_way_to_the_root_stay_in_lds(run):
+    r = run(ROUTE_GRAPHS + """
+stub.stub_set(64 << 30, 1)
+out = {}
+h = graph(gen.grid(135, 135))
+lib.kc_set_option(h, kc.KC_OPT_SLOTS, 2000)
+out["slots"] = kind(estimate(h, 5000)[1])
+lib.kc_set_option(h, kc.KC_OPT_SLOTS, 0)
+info = kc._Info(); lib.kc_graph_get_info(h, ctypes.byref(info))
+lib.kc_set_option(h, kc.KC_OPT_MEM_BUDGET, 500 * info.sample_bytes)
+ls = estimate(h, 5000)[1]
+out["budget"] = [kind(ls), sampler(ls)["grid"] <= 256]
+lib.kc_set_option(h, kc.KC_OPT_MEM_BUDGET, 0)
+lib.kc_trim(h, None)
+out["none"] = kind(estimate(h, 5000)[1])
+out["star"] = kind(estimate(graph(gen.star(20000)), 20000)[1])
+out["random"] = [kind(estimate(graph(random_graph(20000, 8)), c)[1]) for c in (3072, 3073)]
+def batch(*jobs):
+    hs = (ctypes.c_void_p * len(jobs))(*[graph(g).value for g, _ in jobs])
+    sd, fi = np.zeros(len(jobs), np.uint64), np.zeros(len(jobs), np.int64)
+    co, b = np.array([c for _, c in jobs], np.int32), ctypes.c_void_p()
+    stub.stub_clear()
+    assert lib.kc_batch_create(hs, len(jobs), sd.ctypes.data, fi.ctypes.data, co.ctypes.data, None, ctypes.byref(b)) == 0
+    return kind(launches())
+out["batch"] = [batch((gen.grid(135, 135), 2000)), batch((gen.grid(135, 135), 1500)), batch((gen.grid(135, 135), 2000), (gen.grid(8, 8), 10))]
+print(json.dumps(out))
+""")
+    assert r == {"slots": "lds", "budget": ["lds", True], "none": "chains", "star": "lds", "random": ["lds", "chains"],
+                 "batch": ["chains", "lds", "lds"]}
