@@ -706,20 +706,33 @@ hipError_t launch_frontier(const GraphDev &g, const SlotDev &s, const RunParams 
     hipLaunchKernelGGL((frontier_kernel<LT, ROUTE_LDS>), dim3(slots), dim3(LT), lds, stream, g, s, rp);
     return hipGetLastError();
 }
-// A batch's workgroups have the threads its largest graph takes.
+// A batch's workgroups have the threads its largest graph takes, and the most dynamic LDS of
+// its jobs with that many threads (grids of 1,024 take 28 KB with 256; the 40 KB of 512 threads
+// left a CU three of those workgroups where it holds four).
+static bool batch_is_global(const BatchArgs &a) {
+    for (int j = 0; j < a.k; ++j)
+        if (a.job[j].route == ROUTE_GLOBAL) return true;
+    return false;
+}
+template <int T>
+static size_t batch_lds(const BatchArgs &a) {
+    size_t lds = 0;
+    for (int j = 0; j < a.k; ++j) lds = std::max(lds, dyn_lds<T>(a.job[j].route, a.job[j].g.n));
+    return lds;
+}
+template <int T>
+static hipError_t launch_batch_of(const BatchArgs &a, const SlotDev &s, int32_t *ctl, const int64_t *launch, int slots,
+                                  hipStream_t stream) {
+    const size_t lds = batch_lds<T>(a);
+    const hipError_t e = allow_lds(frontier_batch_kernel<T>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((frontier_batch_kernel<T>), dim3(slots), dim3(T), lds, stream, a, s, ctl, launch);
+    return hipGetLastError();
+}
 hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *ctl, const int64_t *launch,
                                  int slots, hipStream_t stream) {
-    size_t lds = 0;
-    bool global = false;
-    for (int j = 0; j < a.k; ++j) {
-        lds = std::max(lds, dyn_lds<GT>(a.job[j].route, a.job[j].g.n));
-        global = global || a.job[j].route == ROUTE_GLOBAL;
-    }
-    const hipError_t e = global ? allow_lds(frontier_batch_kernel<GT>, lds) : allow_lds(frontier_batch_kernel<LT>, lds);
-    if (e != hipSuccess) return e;
-    if (global) hipLaunchKernelGGL((frontier_batch_kernel<GT>), dim3(slots), dim3(GT), lds, stream, a, s, ctl, launch);
-    else hipLaunchKernelGGL((frontier_batch_kernel<LT>), dim3(slots), dim3(LT), lds, stream, a, s, ctl, launch);
-    return hipGetLastError();
+    return batch_is_global(a) ? launch_batch_of<GT>(a, s, ctl, launch, slots, stream)
+                              : launch_batch_of<LT>(a, s, ctl, launch, slots, stream);
 }
 hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
     if (tree_threads(g.n, rp.traversal) == GT)
@@ -733,13 +746,8 @@ int frontier_blocks_per_cu(int route, int64_t n) {
                                  : resident(frontier_kernel<LT, ROUTE_LDS>, LT, dyn_lds<LT>(route, n));
 }
 int frontier_batch_blocks_per_cu(const BatchArgs &a) {
-    size_t lds = 0;
-    bool global = false;
-    for (int j = 0; j < a.k; ++j) {
-        lds = std::max(lds, dyn_lds<GT>(a.job[j].route, a.job[j].g.n));
-        global = global || a.job[j].route == ROUTE_GLOBAL;
-    }
-    return global ? resident(frontier_batch_kernel<GT>, GT, lds) : resident(frontier_batch_kernel<LT>, LT, lds);
+    return batch_is_global(a) ? resident(frontier_batch_kernel<GT>, GT, batch_lds<GT>(a))
+                              : resident(frontier_batch_kernel<LT>, LT, batch_lds<LT>(a));
 }
 int tree_blocks_per_cu(int64_t n, int traversal) {
     return tree_threads(n, traversal) == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n))

@@ -107,3 +107,18 @@ def test_many_samples_on_the_chains_equal_few_in_lds(kc, gen):
         G.set_option(kc.KC_OPT_SLOTS, 300)
         assert not on_chains(kc, G, 17, 900, 1793)
         assert G.estimate(17, 900, count).sum_f == whole.sum_f
+
+
+def test_captured_batch_with_more_than_64_kb_of_words(kc, oracle_lib, gen):
+    gs = [gen.grid(150, 200), gen.grid(12, 12)]
+    Gs = [kc.Graph.from_graph(g) for g in gs]
+    with kc.Batch(Gs, [8, 9], [3, 1000], [2, 30]) as batch:
+        for launch in range(2):
+            batch.launch()
+            batch.results()
+            for j, (g, first, c) in enumerate(zip(gs, (3, 1000), (2, 30))):
+                P = oracle_lib.prepare_graph(g)
+                f, _ = oracle_lib.estimate_f(P, seed=8 + j, s0=first + launch * c, count=c, threads=8)
+                assert np.array_equal(batch.f(j).cpu().numpy(), f)
+    for G in Gs:
+        G.close()

@@ -167,3 +167,28 @@ print(json.dumps(out))
 """)
     assert r == {"slots": "lds", "budget": ["lds", True], "none": "chains", "star": "lds", "random": ["lds", "chains"],
                  "batch": ["chains", "lds", "lds"]}
+
+
+BATCH = """
+def batch(*jobs):
+    hs = (ctypes.c_void_p * len(jobs))(*[graph(g).value for g, _ in jobs])
+    sd, fi = np.zeros(len(jobs), np.uint64), np.zeros(len(jobs), np.int64)
+    co, b = np.array([c for _, c in jobs], np.int32), ctypes.c_void_p()
+    stub.stub_clear()
+    assert lib.kc_batch_create(hs, len(jobs), sd.ctypes.data, fi.ctypes.data, co.ctypes.data, None, ctypes.byref(b)) == 0
+    return launches()
+"""
+
+
+def test_a_batch_asks_for_the_lds_of_its_own_threads(run):
+    """No more than a launch over its largest graph alone."""
+    r = run(ROUTE_GRAPHS + BATCH + """
+out = []
+for gs in ([gen.grid(32, 32), gen.grid(16, 16)], [gen.grid(32, 32), hubs(33000, 10)], [gen.grid(150, 200), gen.grid(8, 8)]):
+    one = [sampler(estimate(graph(g), 10)[1]) for g in gs]
+    b = sampler(batch(*[(g, 10) for g in gs]))
+    out.append([b["block"], b["lds"], max(l["block"] for l in one), max(l["lds"] for l in one)])
+print(json.dumps(out))
+""")
+    for block, lds, block1, lds1 in r:
+        assert block == block1 and lds == lds1
