@@ -672,11 +672,15 @@ __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev s
 }
 
 // Dynamic LDS of a workgroup of T threads: the words of the tree being sampled; in
-// their place, once its parents are read, the map or the list of its evaluation.
+// their place, once its parents are read, what the traversal of its evaluation takes:
+// the sweep's list and nodes, or the path sums' map (64 KB above 2^18 vertices, where the
+// sweep takes 28: 1,024 trees of a road-like graph of 315,215 vertices take 146 ms at two
+// workgroups per CU, 119 at four).
 template <int T>
-size_t dyn_lds(int route, int64_t n) {
+size_t dyn_lds(int route, int64_t n, int traversal) {
     const size_t words = route == ROUTE_LDS ? 4 * (size_t)n : 0;
-    return (std::max({words, (size_t)path_bits(n) / 8, sizeof(SweepLds<T>)}) + 15) / 16 * 16;
+    const size_t eval = traversal == 2 ? sizeof(SweepLds<T>) : (size_t)path_bits(n) / 8;
+    return (std::max(words, eval) + 15) / 16 * 16;
 }
 
 template <typename K>
@@ -696,11 +700,11 @@ hipError_t allow_lds(K kernel, size_t lds) {
 
 hipError_t launch_frontier(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
     if (rp.route == ROUTE_GLOBAL) {
-        const size_t lds = dyn_lds<GT>(rp.route, g.n);
+        const size_t lds = dyn_lds<GT>(rp.route, g.n, rp.traversal);
         hipLaunchKernelGGL((frontier_kernel<GT, ROUTE_GLOBAL>), dim3(slots), dim3(GT), lds, stream, g, s, rp);
         return hipGetLastError();
     }
-    const size_t lds = dyn_lds<LT>(rp.route, g.n);
+    const size_t lds = dyn_lds<LT>(rp.route, g.n, rp.traversal);
     const hipError_t e = allow_lds(frontier_kernel<LT, ROUTE_LDS>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((frontier_kernel<LT, ROUTE_LDS>), dim3(slots), dim3(LT), lds, stream, g, s, rp);
@@ -717,7 +721,7 @@ static bool batch_is_global(const BatchArgs &a) {
 template <int T>
 static size_t batch_lds(const BatchArgs &a) {
     size_t lds = 0;
-    for (int j = 0; j < a.k; ++j) lds = std::max(lds, dyn_lds<T>(a.job[j].route, a.job[j].g.n));
+    for (int j = 0; j < a.k; ++j) lds = std::max(lds, dyn_lds<T>(a.job[j].route, a.job[j].g.n, a.job[j].traversal));
     return lds;
 }
 template <int T>
@@ -735,23 +739,24 @@ hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *
                               : launch_batch_of<LT>(a, s, ctl, launch, slots, stream);
 }
 hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
-    if (tree_threads(g.n, rp.traversal) == GT)
-        hipLaunchKernelGGL((tree_kernel<GT>), dim3(slots), dim3(GT), dyn_lds<GT>(ROUTE_GLOBAL, g.n), stream, g, s, rp);
+    const int t = rp.traversal;
+    if (tree_threads(g.n, t) == GT)
+        hipLaunchKernelGGL((tree_kernel<GT>), dim3(slots), dim3(GT), dyn_lds<GT>(ROUTE_GLOBAL, g.n, t), stream, g, s, rp);
     else
-        hipLaunchKernelGGL((tree_kernel<LT>), dim3(slots), dim3(LT), dyn_lds<LT>(ROUTE_GLOBAL, g.n), stream, g, s, rp);
+        hipLaunchKernelGGL((tree_kernel<LT>), dim3(slots), dim3(LT), dyn_lds<LT>(ROUTE_GLOBAL, g.n, t), stream, g, s, rp);
     return hipGetLastError();
 }
-int frontier_blocks_per_cu(int route, int64_t n) {
-    return route == ROUTE_GLOBAL ? resident(frontier_kernel<GT, ROUTE_GLOBAL>, GT, dyn_lds<GT>(route, n))
-                                 : resident(frontier_kernel<LT, ROUTE_LDS>, LT, dyn_lds<LT>(route, n));
+int frontier_blocks_per_cu(int route, int64_t n, int traversal) {
+    return route == ROUTE_GLOBAL ? resident(frontier_kernel<GT, ROUTE_GLOBAL>, GT, dyn_lds<GT>(route, n, traversal))
+                                 : resident(frontier_kernel<LT, ROUTE_LDS>, LT, dyn_lds<LT>(route, n, traversal));
 }
 int frontier_batch_blocks_per_cu(const BatchArgs &a) {
     return batch_is_global(a) ? resident(frontier_batch_kernel<GT>, GT, batch_lds<GT>(a))
                               : resident(frontier_batch_kernel<LT>, LT, batch_lds<LT>(a));
 }
 int tree_blocks_per_cu(int64_t n, int traversal) {
-    return tree_threads(n, traversal) == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n))
-                                  : resident(tree_kernel<LT>, LT, dyn_lds<LT>(ROUTE_GLOBAL, n));
+    return tree_threads(n, traversal) == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n, traversal))
+                                  : resident(tree_kernel<LT>, LT, dyn_lds<LT>(ROUTE_GLOBAL, n, traversal));
 }
 
 }  // namespace kc

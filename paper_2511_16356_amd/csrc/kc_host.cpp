@@ -253,7 +253,7 @@ int kc_host::route_of(const kc_graph *g, int64_t count, int slots) {
     if (g->n > kc::LDS_MAX_N) return meets_root && g->two_m >= 8 * g->n ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
     if (meets_root || slots < std::min<int64_t>(count, 2048) || count <= 7 * resident_slots(1)) return kc::ROUTE_LDS;
     const bool lattice = 2 * g->two_m >= 7 * g->n && g->bfs_depth > 12;
-    const int per_cu = kc::frontier_blocks_per_cu(kc::ROUTE_LDS, g->n);
+    const int per_cu = kc::frontier_blocks_per_cu(kc::ROUTE_LDS, g->n, g->traversal);
     const int waves = per_cu == 1 ? (lattice ? 7 : 12) : per_cu == 2 && lattice ? 14 : 0;
     return waves > 0 && count > (int64_t)waves * resident_slots(per_cu) ? kc::ROUTE_CHAINS : kc::ROUTE_LDS;
 }
@@ -269,7 +269,7 @@ int kc_host::default_slots(const kc_graph *g, int mode, int route) {
     int per_cu = 0;
     if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n, g->traversal);
     else if (route == kc::ROUTE_CHAINS) per_cu = kc::persistent_blocks_per_cu(g->chains);
-    else per_cu = kc::frontier_blocks_per_cu(route, g->n);
+    else per_cu = kc::frontier_blocks_per_cu(route, g->n, g->traversal);
     return resident_slots(per_cu);
 }
 

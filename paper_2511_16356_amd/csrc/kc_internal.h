@@ -162,7 +162,7 @@ hipError_t launch_frontier(const GraphDev &g, const SlotDev &s, const RunParams 
 hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *ctl, const int64_t *launch,
                                  int slots, hipStream_t stream);
 hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream);
-int frontier_blocks_per_cu(int route, int64_t n);  // resident workgroups per CU
+int frontier_blocks_per_cu(int route, int64_t n, int traversal);  // resident workgroups per CU
 int frontier_batch_blocks_per_cu(const BatchArgs &a);
 int tree_blocks_per_cu(int64_t n, int traversal);
 // The batch takes the frontier sampler when every job's route is one of its.

@@ -181,7 +181,7 @@ def batch(*jobs):
 
 
 def test_a_batch_asks_for_the_lds_of_its_own_threads(run):
-    """No more than a launch over its largest graph alone."""
+    """No more than a launch over its largest graph alone, but for a sweep by more threads."""
     r = run(ROUTE_GRAPHS + BATCH + """
 out = []
 for gs in ([gen.grid(32, 32), gen.grid(16, 16)], [gen.grid(32, 32), hubs(33000, 10)], [gen.grid(150, 200), gen.grid(8, 8)]):
@@ -190,5 +190,29 @@ for gs in ([gen.grid(32, 32), gen.grid(16, 16)], [gen.grid(32, 32), hubs(33000, 
     out.append([b["block"], b["lds"], max(l["block"] for l in one), max(l["lds"] for l in one)])
 print(json.dumps(out))
 """)
-    for block, lds, block1, lds1 in r:
-        assert block == block1 and lds == lds1
+    (b0, l0, *one0), (b1, l1, *one1), (b2, l2, *one2) = r
+    assert [b0, l0] == one0 and [b2, l2] == one2
+    assert b1 == one1[0] == 512 and l1 == 2 * 512 * 24 + 2048 * 8
+
+
+def test_a_launch_asks_for_the_lds_its_traversal_takes(run):
+    """The sweep's 1,024 or 512 items of 24 bytes and 2,048 nodes of 8, the path sums' bit per
+    vertex (at most 2^19), or the words if those are more."""
+    r = run("""
+        def evaluate(h, n):
+            par, f = np.zeros(n, np.int32), np.zeros(1, np.int64)
+            stub.stub_clear()
+            assert lib.kc_evaluate_trees(h, par.ctypes.data, 1, f.ctypes.data, None) == 0
+            return launches()
+        def lds(ls):
+            return [[l["block"], l["lds"]] for l in ls if "tree_kernel" in l["name"] or "frontier" in l["name"]]
+        out = []
+        for g in (gen.cycle(300000), gen.star(300000), gen.star(600000), gen.grid(20, 20), gen.star(400), gen.grid(100, 150)):
+            h = graph(g)
+            out += lds(evaluate(h, g.n))
+            if g.n < 32768: out += lds(estimate(h, 4)[1])
+        print(json.dumps(out))
+    """)
+    sweep = 2 * 256 * 24 + 2048 * 8
+    assert r == [[256, sweep], [512, 1 << 16], [512, 1 << 16], [256, sweep], [256, sweep], [256, 64], [256, 1600],
+                 [256, sweep], [256, 60000]]
