@@ -38,8 +38,17 @@ namespace {
 constexpr int LT = 256, GT = 512;
 constexpr int FT_WAVES = 4;  // wavefronts per SIMD the kernels are built to fit (128 VGPRs)
 // Trees the caller holds: as above (1,024 vertices and 2,000 trees: 1.7 against 2.6 ms
-// with 512; 481,994 vertices and 256 trees: 29.0 against 25.4 ms).
-inline int tree_threads(int64_t n, int traversal) { return traversal != 2 && n > LDS_MAX_N ? GT : LT; }
+// with 512; 481,994 vertices and 256 trees: 29.0 against 25.4 ms).  Small trees, in more
+// slots than 256 threads each let be in flight (four on a CU), are evaluated by one
+// wavefront each: their phases are too short for the barriers (20,000 trees, 256 threads
+// against 64: grid of 1,024 10.1 / 6.7 ms, of 64 1.38 / 0.63 ms, power-law graph of 497
+// vertices 1.46 / 0.54 ms; 4,096 trees of a grid of 4,096 7.4 / 6.9 ms; from there on, and
+// with fewer slots, 256 are as fast or faster: road-like graph of 5,749, 1,024 trees 2.25 /
+// 2.99 ms).
+int tree_threads(int64_t n, int traversal, int mode, int64_t slots) {
+    if (traversal != 2 && n > LDS_MAX_N) return GT;
+    return mode == RUN_EVALUATE && slots > 1024 && n <= (traversal == 2 ? 4096 : 512) ? WAVE : LT;
+}
 
 // Entries of the frontier, of the found cycles and of the due walks' table kept
 // in LDS; frontier and cycles beyond (early rounds only) go to the slot's block.
@@ -650,8 +659,14 @@ __global__ void __launch_bounds__(T, FT_WAVES) tree_kernel(GraphDev g, SlotDev s
     const SlotPtrs sp = slot_ptrs(sd, (size_t)g.n);
     int64_t done = 0;
     while (true) {
-        const int idx = next_item<T>(rp.ctl, tree);
-        if (idx >= rp.count) break;
+        // trees that are short and alike, one wavefront's or a workgroup for each: fixed shares,
+        // without the counter's 45 ns per tree (1,024 trees of a grid of 64: 0.14 -> 0.11 ms; of
+        // a grid of 1,024 it pays to start them one after the other: 0.70, 0.72 ms)
+        const bool shares = T == WAVE || ((int)gridDim.x >= rp.count && g.n <= 512);
+        const int64_t item = shares ? blockIdx.x + done * gridDim.x : next_item<T>(rp.ctl, tree);
+        if (item >= rp.count) break;
+        const int idx = (int)item;
+        if (shares) __syncthreads();  // the LDS of the tree before is free
         const size_t row = rp.rows ? (size_t)rp.rows[idx] : (size_t)idx;
         const int32_t *par = rp.parents_in + row * (size_t)g.n;
         if (rp.mode == RUN_CROSS) {
@@ -738,13 +753,18 @@ hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *
     return batch_is_global(a) ? launch_batch_of<GT>(a, s, ctl, launch, slots, stream)
                               : launch_batch_of<LT>(a, s, ctl, launch, slots, stream);
 }
-hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
-    const int t = rp.traversal;
-    if (tree_threads(g.n, t) == GT)
-        hipLaunchKernelGGL((tree_kernel<GT>), dim3(slots), dim3(GT), dyn_lds<GT>(ROUTE_GLOBAL, g.n, t), stream, g, s, rp);
-    else
-        hipLaunchKernelGGL((tree_kernel<LT>), dim3(slots), dim3(LT), dyn_lds<LT>(ROUTE_GLOBAL, g.n, t), stream, g, s, rp);
+template <int T>
+static hipError_t launch_trees_of(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots,
+                                  hipStream_t stream) {
+    hipLaunchKernelGGL((tree_kernel<T>), dim3(slots), dim3(T), dyn_lds<T>(ROUTE_GLOBAL, g.n, rp.traversal), stream, g,
+                       s, rp);
     return hipGetLastError();
+}
+hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
+    const int threads = tree_threads(g.n, rp.traversal, rp.mode, slots);
+    return threads == GT ? launch_trees_of<GT>(g, s, rp, slots, stream)
+         : threads == LT ? launch_trees_of<LT>(g, s, rp, slots, stream)
+                         : launch_trees_of<WAVE>(g, s, rp, slots, stream);
 }
 int frontier_blocks_per_cu(int route, int64_t n, int traversal) {
     return route == ROUTE_GLOBAL ? resident(frontier_kernel<GT, ROUTE_GLOBAL>, GT, dyn_lds<GT>(route, n, traversal))
@@ -754,9 +774,11 @@ int frontier_batch_blocks_per_cu(const BatchArgs &a) {
     return batch_is_global(a) ? resident(frontier_batch_kernel<GT>, GT, batch_lds<GT>(a))
                               : resident(frontier_batch_kernel<LT>, LT, batch_lds<LT>(a));
 }
-int tree_blocks_per_cu(int64_t n, int traversal) {
-    return tree_threads(n, traversal) == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n, traversal))
-                                  : resident(tree_kernel<LT>, LT, dyn_lds<LT>(ROUTE_GLOBAL, n, traversal));
+int tree_blocks_per_cu(int64_t n, int traversal, int mode, int64_t slots) {
+    const int threads = tree_threads(n, traversal, mode, slots);
+    return threads == GT ? resident(tree_kernel<GT>, GT, dyn_lds<GT>(ROUTE_GLOBAL, n, traversal))
+         : threads == LT ? resident(tree_kernel<LT>, LT, dyn_lds<LT>(ROUTE_GLOBAL, n, traversal))
+                         : resident(tree_kernel<WAVE>, WAVE, dyn_lds<WAVE>(ROUTE_GLOBAL, n, traversal));
 }
 
 }  // namespace kc

@@ -265,9 +265,9 @@ int kc_host::resident_slots(int per_cu) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 1024;
     return cus > 0 && per_cu > 0 ? cus * per_cu : 1024;
 }
-int kc_host::default_slots(const kc_graph *g, int mode, int route) {
+int kc_host::default_slots(const kc_graph *g, int mode, int route, int64_t count) {
     int per_cu = 0;
-    if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n, g->traversal);
+    if (mode != kc::RUN_SAMPLE && mode != kc::RUN_ESTIMATE) per_cu = kc::tree_blocks_per_cu(g->n, g->traversal, mode, count);
     else if (route == kc::ROUTE_CHAINS) per_cu = kc::persistent_blocks_per_cu(g->chains);
     else per_cu = kc::frontier_blocks_per_cu(route, g->n, g->traversal);
     return resident_slots(per_cu);
@@ -276,7 +276,8 @@ int kc_host::default_slots(const kc_graph *g, int mode, int route) {
 int kc_host::workspace_slots(const kc_graph *g, int count) {
     if (count <= resident_slots(1)) return count;  // every CU holds a workgroup of any of the kernels
     const int route = route_of(g, count);
-    return std::max(default_slots(g, kc::RUN_ESTIMATE, route), default_slots(g, kc::RUN_EVALUATE, route));
+    return std::max(default_slots(g, kc::RUN_ESTIMATE, route, count),
+                    default_slots(g, kc::RUN_EVALUATE, route, count));
 }
 
 // Workspace bytes a launch may allocate: the graph's budget option, else 80%
@@ -366,7 +367,7 @@ kc_status run_persistent(kc_graph *g, kc::RunParams rp, hipStream_t stream) {
     kc_status st = ensure_workspace(g, want, trav, fen, stream, &slots);
     if (st != KC_OK) return st;
     const int route = route_of(g, rp.count, slots);
-    if (g->slots_opt <= 0 && slots > resident_slots(1)) slots = std::min(slots, default_slots(g, rp.mode, route));
+    if (g->slots_opt <= 0 && slots > resident_slots(1)) slots = std::min(slots, default_slots(g, rp.mode, route, slots));
     slots = balanced_slots(slots, rp.count);
     kc::SlotDev sd;
     sd.state = g->d_state;

@@ -98,7 +98,8 @@ kc_status fail(kc_status st, const char *fmt, ...);
 int64_t slot_bytes(const kc_graph *g, bool trav, bool fen);
 // Samples in flight when the graph's slots option is 0: resident workgroups of the kernel.
 int resident_slots(int per_cu);
-int default_slots(const kc_graph *g, int mode, int route);  // resident workgroups of the launch's kernel
+// (count: trees the launch takes)
+int default_slots(const kc_graph *g, int mode, int route, int64_t count);
 // Slots the workspace is sized for when the slots option is 0: the most any launch of up to
 // count samples on g takes.
 int workspace_slots(const kc_graph *g, int count);

@@ -164,7 +164,7 @@ hipError_t launch_frontier_batch(const BatchArgs &a, const SlotDev &s, int32_t *
 hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream);
 int frontier_blocks_per_cu(int route, int64_t n, int traversal);  // resident workgroups per CU
 int frontier_batch_blocks_per_cu(const BatchArgs &a);
-int tree_blocks_per_cu(int64_t n, int traversal);
+int tree_blocks_per_cu(int64_t n, int traversal, int mode, int64_t slots);  // of a launch with that many slots
 // The batch takes the frontier sampler when every job's route is one of its.
 inline bool batch_is_frontier(const BatchArgs &a) {
     for (int j = 0; j < a.k; ++j)

@@ -87,7 +87,7 @@ extern "C" kc_status kc_estimate_static(kc_graph *g, uint64_t seed, int64_t firs
                r256(16 * s * n) + (fen ? r256(8 * s * (size_t)(g->two_m + 2)) : 0);
     };
     const size_t room = STATIC_SCRATCH_BYTES - r256(c.used);
-    int slots = g->slots_opt > 0 ? g->slots_opt : default_slots(g, kc::RUN_ESTIMATE, route_of(g));
+    int slots = g->slots_opt > 0 ? g->slots_opt : default_slots(g, kc::RUN_ESTIMATE, route_of(g), count);
     slots = std::min(slots, count);
     while (slots > 0 && need((size_t)slots) > room) slots = (int)std::min<size_t>(slots - 1, room / need(1));
     if (slots < 1)

@@ -111,7 +111,7 @@ extern "C" kc_status kc_autotune(kc_graph *g, int32_t count, const char *cache_p
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     const int64_t budget = workspace_budget(g, free_b);
     const int64_t fit = budget / std::max<int64_t>(1, slot_bytes(g, true, g->traversal == KC_TRAV_SWEEP));
-    const int full = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(default_slots(g, kc::RUN_ESTIMATE, route_of(g, count)), count), fit));
+    const int full = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(default_slots(g, kc::RUN_ESTIMATE, route_of(g, count), count), count), fit));
     // trial estimates: one wave of samples in flight (at least 64), on sample ids far
     // from any the caller uses (2^40 upward)
     kc_result res{};

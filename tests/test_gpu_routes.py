@@ -122,3 +122,48 @@ def test_captured_batch_with_more_than_64_kb_of_words(kc, oracle_lib, gen):
                 assert np.array_equal(batch.f(j).cpu().numpy(), f)
     for G in Gs:
         G.close()
+
+
+@pytest.mark.parametrize("kind,size,count", [
+    ("path", 2, 1100), ("path", 63, 5000), ("path", 65, 1025), ("cycle", 65, 9000), ("star", 255, 5000), ("star", 512, 1025),
+    ("star", 513, 1025), ("complete", 129, 1500), ("grid", (32, 32), 5000), ("grid", (64, 64), 1025), ("grid", (17, 241), 1025),
+    ("cycle", 4096, 1025)])
+def test_many_small_trees(kc, oracle_lib, gen, kind, size, count):
+    """Evaluations in more than 1,024 slots: one wavefront per tree up to 4,096 vertices (sweep) or
+    512 (path sums), each with a fixed share of the trees; then a call with a parent array that is
+    no tree, and the trees again."""
+    import torch
+    g = gen.grid(*size) if kind == "grid" else {"path": gen.path, "cycle": gen.cycle, "star": gen.star,
+                                                 "complete": gen.complete}[kind](size)
+    P = oracle_lib.prepare_graph(g)
+    rng = np.random.default_rng(g.n)
+    if kind == "cycle":  # a tree is a path: cut at a random edge
+        trees = []
+        for cut in rng.integers(0, g.n, 7):
+            par = np.full(g.n, -1, np.int32)
+            for step in (1, -1):
+                v = P.root
+                while (v if step == 1 else (v - 1) % g.n) != cut:
+                    par[(v + step) % g.n] = v
+                    v = (v + step) % g.n
+            trees.append(par)
+        trees = np.array(trees, np.int32)
+    else:
+        trees = oracle_lib.sample(P, seed=2, s0=0, count=7, threads=8)[0]
+    ref = np.array([oracle_lib.f_of_tree(P, t) for t in trees], np.int64)
+    pick = rng.integers(0, len(trees), count)
+    par = torch.from_numpy(trees[pick]).cuda()
+    with kc.Graph.from_graph(g) as G:
+        if g.n <= 600:
+            G.set_option(kc.KC_OPT_TRAVERSAL, kc.KC_TRAV_SWEEP)
+            assert np.array_equal(G.evaluate_trees(par).cpu().numpy(), ref[pick])
+            G.set_option(kc.KC_OPT_TRAVERSAL, kc.KC_TRAV_AUTO)
+        assert np.array_equal(G.evaluate_trees(par).cpu().numpy(), ref[pick])
+        bad = par.clone()
+        bad[count // 2, (P.root + 1) % g.n] = (P.root + 1) % g.n
+        with pytest.raises(kc.KcError) as ei:
+            G.evaluate_trees(bad)
+        assert ei.value.status == 1
+        assert np.array_equal(G.evaluate_trees(par).cpu().numpy(), ref[pick])
+        G.set_option(kc.KC_OPT_SLOTS, 3)
+        assert np.array_equal(G.evaluate_trees(par[:40]).cpu().numpy(), ref[pick[:40]])
