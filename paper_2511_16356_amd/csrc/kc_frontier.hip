@@ -704,11 +704,13 @@ int resident(K kernel, int threads, size_t lds) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, kernel, threads, lds) != hipSuccess) return 0;
     return blocks;
 }
+// Dynamic LDS above 64 KB is a limit of the kernel, shared by every thread of the process: it
+// is set to the most any graph takes, so that no call lowers it between another's two steps.
 template <typename K>
 hipError_t allow_lds(K kernel, size_t lds) {
+    constexpr int most = (4 * (int)LDS_MAX_N + 15) / 16 * 16;
     if (lds <= (64u << 10)) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds);
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, most);
 }
 
 }  // namespace

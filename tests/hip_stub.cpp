@@ -49,6 +49,11 @@ const char *stub_name(int i) { return launches[(size_t)i].name.c_str(); }
 int stub_grid(int i) { return (int)launches[(size_t)i].grid; }
 int stub_block(int i) { return (int)launches[(size_t)i].block; }
 size_t stub_lds(int i) { return launches[(size_t)i].lds; }
+size_t stub_limit(const char *kernel) {  // the dynamic LDS it may take (of one whose name holds this)
+    for (const auto &l : lds_limit)
+        if (names()[l.first].find(kernel) != std::string::npos) return l.second;
+    return 0;
+}
 void *stub_out(int i) { return launches[(size_t)i].out; }
 
 // ---- the runtime (0: hipSuccess, 1: hipErrorInvalidValue)

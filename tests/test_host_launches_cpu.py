@@ -216,3 +216,21 @@ def test_a_launch_asks_for_the_lds_its_traversal_takes(run):
     sweep = 2 * 256 * 24 + 2048 * 8
     assert r == [[256, sweep], [512, 1 << 16], [512, 1 << 16], [256, sweep], [256, sweep], [256, 64], [256, 1600],
                  [256, sweep], [256, 60000]]
+
+
+def test_no_call_lowers_the_lds_limit_of_another(run):
+    """The limit belongs to the kernel: one thread may set it and launch while another sets it for a
+    smaller graph.  After any call it covers the largest graph's words."""
+    r = run(BATCH + """
+stub.stub_limit.restype = ctypes.c_size_t
+out = []
+for g in (gen.grid(150, 200), gen.grid(130, 140), gen.grid(10, 10)):
+    st, ls = estimate(graph(g), 4)
+    assert st == 0
+    out.append(["frontier_kernel", stub.stub_limit(b"frontier_kernel")])
+for g in (gen.grid(150, 200), gen.grid(130, 140)):
+    batch((g, 3))
+    out.append(["frontier_batch_kernel", stub.stub_limit(b"frontier_batch_kernel")])
+print(json.dumps(out))
+""")
+    assert all(limit >= 4 * 32767 for _, limit in r)
