@@ -328,11 +328,11 @@ typedef struct {
  * Choose g's launch options for estimates of `count` samples by timing short
  * trial estimates (one wave of samples in flight, at least 64, on sample ids
  * from 2^40 upward): starting from the current options, one option at a
- * time (traversal for tau0 depth <= 64, chain-table size,
- * 3/4 and 1/2 of the samples in flight, walkers 32/64), a change kept only for
+ * time (traversal for tau0 depth <= 64, 3/4 and 1/2 of the samples in flight
+ * and, where the chain sampler runs, its table's size and walkers 32/64), a change kept only for
  * a gain above 2%.  The choice is applied to g (kc_set_option) and appended to
  * cache_path (HOST string or NULL: no cache) as one JSON line keyed by device
- * architecture, n, 2m, max degree, tau0 depth and count; a later call with the
+ * architecture, n, 2m, max degree, tau0 depth, count and sampler; a later call with the
  * same key applies the cached choice without trials.  No option changes any
  * result (trees, f and estimates are bit-identical).
  *   out : HOST pointer

@@ -1,11 +1,12 @@
 // kc_tune.cpp -- kc_autotune: chooses a graph's launch options (samples in
-// flight, chain-table size, walkers per sample, traversal) by timing short estimates, and keeps the choice in a cache file.
+// flight, traversal and, for the chain sampler, its table's size and the walkers per
+// sample) by timing short estimates, and keeps the choice in a cache file.
 // None of these options changes any tree, f or estimate: the tree of sample s
 // is the cycle-popping outcome of its arrows (section 2.2) whatever the launch
 // shape, and f is Theorem 3.4's sum whatever the traversal.
 //
 // Cache: one JSON object per line,
-//   {"key": "<arch>|n=..|two_m=..|dmax=..|depth0=..|count=..", "chains": C, "slots": S,
+//   {"key": "<arch>|n=..|two_m=..|dmax=..|depth0=..|count=..[|frontier=..]", "chains": C, "slots": S,
 //    "walkers": W, "traversal": T, "samples_per_s": R}
 // The last line with the graph's key wins.
 
@@ -27,14 +28,17 @@ struct Choice {
     int32_t chains, slots, walkers, traversal;
 };
 
-std::string cache_key(const kc_graph *g, int32_t count) {
+// (The frontier sampler's keys name it: slots chosen for the one-wavefront slots of the chain
+// sampler, which once took every graph, do not fit its workgroups.)
+std::string cache_key(const kc_graph *g, int32_t count, int route) {
     int dev = 0;
     hipDeviceProp_t prop{};
     std::string arch = "unknown";
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) arch = prop.gcnArchName;
     char buf[256];
-    std::snprintf(buf, sizeof(buf), "%s|n=%lld|two_m=%lld|dmax=%d|depth0=%d|count=%d", arch.c_str(), (long long)g->n,
-                  (long long)g->two_m, g->max_degree, g->depth0, count);
+    std::snprintf(buf, sizeof(buf), "%s|n=%lld|two_m=%lld|dmax=%d|depth0=%d|count=%d%s", arch.c_str(), (long long)g->n,
+                  (long long)g->two_m, g->max_degree, g->depth0, count,
+                  route == kc::ROUTE_CHAINS ? "" : route == kc::ROUTE_LDS ? "|frontier=lds" : "|frontier=memory");
     return buf;
 }
 
@@ -90,7 +94,8 @@ extern "C" kc_status kc_autotune(kc_graph *g, int32_t count, const char *cache_p
     if (!g || !out) return fail(KC_ERR_INVALID, "NULL argument");
     if (count < 1) return fail(KC_ERR_INVALID, "count must be >= 1");
     std::memset(out, 0, sizeof(*out));
-    const std::string key = cache_key(g, count);
+    const int route = route_of(g, count);
+    const std::string key = cache_key(g, count, route);
     Choice best{};
     if (cache_lookup(cache_path, key, &best)) {
         const kc_status st = apply(g, best);
@@ -111,7 +116,7 @@ extern "C" kc_status kc_autotune(kc_graph *g, int32_t count, const char *cache_p
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     const int64_t budget = workspace_budget(g, free_b);
     const int64_t fit = budget / std::max<int64_t>(1, slot_bytes(g, true, g->traversal == KC_TRAV_SWEEP));
-    const int full = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(default_slots(g, kc::RUN_ESTIMATE, route_of(g, count), count), count), fit));
+    const int full = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(default_slots(g, kc::RUN_ESTIMATE, route, count), count), fit));
     // trial estimates: one wave of samples in flight (at least 64), on sample ids far
     // from any the caller uses (2^40 upward)
     kc_result res{};
@@ -148,10 +153,11 @@ extern "C" kc_status kc_autotune(kc_graph *g, int32_t count, const char *cache_p
         changes.push_back([](Choice &c) { c.traversal = KC_TRAV_WALK; });
         changes.push_back([](Choice &c) { c.traversal = KC_TRAV_SWEEP; });
     }
-    changes.push_back([](Choice &c) { c.chains = c.chains == 1024 ? 2048 : 1024; });
+    const bool chains = route == kc::ROUTE_CHAINS;  // the frontier sampler has neither chains nor walkers
+    if (chains) changes.push_back([](Choice &c) { c.chains = c.chains == 1024 ? 2048 : 1024; });
     changes.push_back([full](Choice &c) { c.slots = std::max(1, full * 3 / 4); });
     changes.push_back([full](Choice &c) { c.slots = std::max(1, full / 2); });
-    changes.push_back([](Choice &c) { c.walkers = c.walkers == 64 ? 32 : 64; });
+    if (chains) changes.push_back([](Choice &c) { c.walkers = c.walkers == 64 ? 32 : 64; });
     for (const Change &change : changes) {
         Choice cand = best;
         change(cand);

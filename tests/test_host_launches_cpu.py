@@ -234,3 +234,28 @@ for g in (gen.grid(150, 200), gen.grid(130, 140)):
 print(json.dumps(out))
 """)
     assert all(limit >= 4 * 32767 for _, limit in r)
+
+
+def test_autotune_tries_what_the_sampler_has(run, tmp_path):
+    """Chains and walkers are tried for the chain sampler alone, and a choice kept for it (a key
+    without the sampler's name) is not applied to a graph that another sampler takes."""
+    r = run("""
+        def tune(h, path):
+            t = kc._Tune()
+            assert lib.kc_autotune(h, 100, path, ctypes.byref(t), None) == 0, lib.kc_last_error()
+            return t
+        out = []
+        for name, g in (("lds", gen.grid(60, 60)), ("chains", gen.grid(182, 182))):
+            h = graph(g)
+            info = kc._Info(); lib.kc_graph_get_info(h, ctypes.byref(info))
+            path = %r + name
+            key = "unknown|n=%%d|two_m=%%d|dmax=%%d|depth0=%%d|count=100" %% (info.n, info.two_m, info.max_degree, info.depth0)
+            first = tune(h, path.encode())
+            again = tune(h, path.encode())
+            with open(path + ".old", "w") as fh:
+                fh.write(json.dumps({"key": key, "chains": 2048, "slots": 77, "walkers": 32, "traversal": 0}) + "\\n")
+            old = tune(h, (path + ".old").encode())
+            out.append([name, first.trials, again.from_cache, old.from_cache, old.slots == 77])
+        print(json.dumps(out))
+    """ % str(tmp_path / "tune-"))
+    assert r == [["lds", 3, 1, 0, False], ["chains", 5, 1, 1, True]]
