@@ -167,3 +167,100 @@ def test_many_small_trees(kc, oracle_lib, gen, kind, size, count):
         assert np.array_equal(G.evaluate_trees(par).cpu().numpy(), ref[pick])
         G.set_option(kc.KC_OPT_SLOTS, 3)
         assert np.array_equal(G.evaluate_trees(par[:40]).cpu().numpy(), ref[pick[:40]])
+
+
+CHAIN_GRAPHS = {
+    "random": lambda gen: random_graph(gen, 33001, 8),     # lean looks by default
+    "grid": lambda gen: gen.grid(182, 182),                # long walks, no lean looks
+}
+
+
+@pytest.fixture(scope="module")
+def chain_reference(oracle_lib, gen):
+    ref = {}
+    for name, make in CHAIN_GRAPHS.items():
+        g = make(gen)
+        P = oracle_lib.prepare_graph(g)
+        first = (1 << 40) + 3 if name == "random" else 12
+        trees = oracle_lib.sample(P, seed=23, s0=first, count=4, threads=8)
+        ref[name] = (g, first, trees, oracle_lib.estimate_f(P, seed=23, s0=first, count=4, threads=8)[0])
+    return ref
+
+
+@pytest.mark.parametrize("options", [
+    {"WALKERS": 1}, {"WALKERS": 7, "SLOTS": 3}, {"WALKERS": 63, "SLOTS": 1}, {"START_ORDER": 0}, {"START_ORDER": 1},
+    {"START_ORDER": 2}, {"CHAINS": 2048}, {"CHAINS": 2048, "WALKERS": 5, "START_ORDER": 1}, {"LEAN_LOOKS": 1},
+    {"LEAN_LOOKS": 2}, {"LEAN_LOOKS": 2, "CHAINS": 2048}, {"LEAN_LOOKS": 1, "CHAINS": 2048, "SLOTS": 2}],
+    ids=lambda o: "-".join("%s%d" % (k.lower(), v) for k, v in o.items()))
+@pytest.mark.parametrize("name", sorted(CHAIN_GRAPHS))
+def test_chain_sampler_options_change_nothing(kc, chain_reference, name, options):
+    """Walkers, start order, table size, lean looks and slots on graphs the chain sampler takes."""
+    g, first, (par, cnt, steps), f = chain_reference[name]
+    print("chains", name, options, flush=True)
+    with kc.Graph.from_graph(g) as G:
+        if options == {"START_ORDER": 2}:
+            # the chain sampler is in effect: with fewer walkers it takes more rounds
+            few = []
+            for walkers in (64, 4):
+                G.set_option(kc.KC_OPT_WALKERS, walkers)
+                few.append(G.estimate(23, first, 4).sampler_iterations)
+            G.set_option(kc.KC_OPT_WALKERS, 64)
+            assert few[1] > 2 * few[0]
+        for key, value in options.items():
+            G.set_option(getattr(kc, "KC_OPT_" + key), value)
+        got = G.sample_trees(23, first, 4)
+        assert np.array_equal(got[0].cpu().numpy(), par)
+        assert np.array_equal(got[1].cpu().numpy().astype(np.uint32), cnt)
+        assert np.array_equal(got[2].cpu().numpy(), steps)
+        _, gf, gs = G.estimate(23, first, 4, per_sample=True)
+        assert np.array_equal(gf.cpu().numpy(), f) and np.array_equal(gs.cpu().numpy(), steps)
+
+
+@pytest.mark.parametrize("n,deg", [(70001, 10), (66000, 6)])
+def test_path_sums_by_one_wavefront_with_more_vertices_than_bits(kc, oracle_lib, gen, n, deg):
+    """A chain-sampled tree on a shallow tau0: its map of tau0 vertices has 65,536 bits."""
+    g = random_graph(gen, n, deg)
+    P = oracle_lib.prepare_graph(g)
+    with kc.Graph.from_graph(g) as G:
+        if deg == 10:
+            assert 4 < G.info["depth0"] <= 8
+        samples_match(G, oracle_lib, P, 3, 70, 4)
+
+
+@pytest.mark.parametrize("other", ["grid", "social"])
+def test_batch_with_a_job_of_the_chain_sampler(kc, oracle_lib, gen, other):
+    """Every job of such a batch takes the chains (with lean looks if all of them would)."""
+    gs = [random_graph(gen, 33001, 10), gen.grid(12, 12) if other == "grid" else gen.chung_lu(2000, 2.2, 10.0, 200.0, seed=1)]
+    Gs = [kc.Graph.from_graph(g) for g in gs]
+    with kc.Batch(Gs, [8, 9], [3, 1000], [2, 30]) as batch:
+        for launch in range(3):
+            batch.launch()
+            ests, done = batch.results()
+            assert done == launch + 1
+            for j, (g, first, c) in enumerate(zip(gs, (3, 1000), (2, 30))):
+                P = oracle_lib.prepare_graph(g)
+                f, _ = oracle_lib.estimate_f(P, seed=8 + j, s0=first + launch * c, count=c, threads=8)
+                assert np.array_equal(batch.f(j).cpu().numpy(), f)
+                assert ests[j].sum_f == int(f.astype(object).sum())
+    for G in Gs:
+        G.close()
+
+
+@pytest.mark.parametrize("hub", [0, 2500])
+def test_trees_through_an_inserted_edge(kc, oracle_lib, gen, hub):
+    """Basic maintenance draws replacements from two roots: on the chains (no hub) and by the
+    frontier sampler with its words in memory."""
+    g = random_graph(gen, 33001, 8, hub=hub)
+    S = oracle_lib.samples_init(g.offsets, g.indices, seed=6, count=8)
+    replaced = 0
+    with kc.Graph.from_graph(g) as G:
+        G.samples_init(6, 8)
+        for serial, (u, v) in enumerate(gen.insertion_batch(g, 4, np.random.default_rng(1))):
+            g = gen.add_edges(g, [(u, v)])
+            S, k, _ = oracle_lib.bsm_insert(S, g.offsets, g.indices, u, v, serial)
+            replaced += k
+            assert G.apply_updates([u], [v], [1]) == k
+            par, f, ids = G.samples_get()
+            assert np.array_equal(par.cpu().numpy(), S.parents) and np.array_equal(ids, S.ids)
+            assert np.array_equal(f.cpu().numpy(), S.f)
+    assert replaced > 0
