@@ -27,7 +27,7 @@ def late_deletions(oracle_lib, gen, g, W, want):
             if p < 4200 or (par == v).any():  # v a leaf: its crossing edges are those of its row
                 continue
             row = g.indices[g.offsets[v]:g.offsets[v + 1]]
-            if len(row) < 2 or row.min() < 4096:
+            if len(row) < 2 or row.min() < 4096 or p not in row:
                 continue
             h = gen.remove_edges(g, [(v, p)])
             if not gen.is_connected(h):
