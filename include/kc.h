@@ -95,7 +95,8 @@ enum {
     KC_OPT_WALKERS = 1,    /* cooperating walkers per sample, 1..64 (default 64) */
     KC_OPT_SLOTS = 2,      /* samples in flight per launch (0 = sized from free HBM) */
     KC_OPT_TRAVERSAL = 3,  /* KC_TRAV_* */
-    KC_OPT_STEP_LIMIT = 4, /* per-sample cap on sampler rounds (0 = default 1024 n + 2^22) */
+    KC_OPT_STEP_LIMIT = 4, /* per-sample cap on sampler rounds (0 = default 1024 n + 2^22); two
+                              rounds of the frontier sampler count as one */
     KC_OPT_MEM_BUDGET = 5, /* bytes of device workspace the library may allocate (0 = 80% of free) */
     KC_OPT_START_ORDER = 6, /* order in which walks are started (results do not depend on it):
                               0 = BFS order from the root, 1 = reverse BFS order,

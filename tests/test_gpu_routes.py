@@ -264,3 +264,20 @@ def test_trees_through_an_inserted_edge(kc, oracle_lib, gen, hub):
             assert np.array_equal(par.cpu().numpy(), S.parents) and np.array_equal(ids, S.ids)
             assert np.array_equal(f.cpu().numpy(), S.f)
     assert replaced > 0
+
+
+@pytest.mark.parametrize("name", ["path", "caterpillar", "grid"])
+def test_step_limit_counts_two_frontier_rounds_as_one(kc, gen, name):
+    """Where walks are longest bulk pops take up to 9% more rounds than the chains, for which
+    limits were chosen: a limit a third below a sample's rounds holds, one far below does not."""
+    i = np.arange(200)
+    g = {"path": lambda: gen.path(300), "grid": lambda: gen.grid(32, 32),
+         "caterpillar": lambda: gen.from_edges("cat", 400, np.concatenate([i[:-1], i]), np.concatenate([i[1:], i + 200]))}[name]()
+    with kc.Graph.from_graph(g) as G:
+        whole = G.estimate(3, 5, 1)
+        G.set_option(kc.KC_OPT_STEP_LIMIT, max(1, whole.sampler_iterations * 2 // 3))
+        assert G.estimate(3, 5, 1).sum_f == whole.sum_f
+        G.set_option(kc.KC_OPT_STEP_LIMIT, max(1, whole.sampler_iterations // 3))
+        with pytest.raises(kc.KcError) as ei:
+            G.estimate(3, 5, 1)
+        assert ei.value.status == 6
