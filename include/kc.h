@@ -90,8 +90,9 @@ enum {
 /* Options for kc_set_option. */
 enum {
     /* WALKERS, START_ORDER, CHAINS and LEAN_LOOKS steer the chain sampler (graphs of more than
-       32,767 vertices with long walks); the frontier sampler, which the others take, has no
-       use for them.  Results depend on none of them. */
+       32,767 vertices with long walks, and thousands of samples of sparse ones above 11,000);
+       the frontier sampler, which the others take, has no use for them.  Results depend on
+       none of them. */
     KC_OPT_WALKERS = 1,    /* cooperating walkers per sample, 1..64 (default 64) */
     KC_OPT_SLOTS = 2,      /* samples in flight per launch (0 = sized from free HBM) */
     KC_OPT_TRAVERSAL = 3,  /* KC_TRAV_* */
@@ -281,8 +282,11 @@ kc_status kc_estimate_static(kc_graph *g, uint64_t seed, int64_t first_sample, i
  * Launch options (step limit, walkers, traversal) are each
  * graph's; the chain-table size, samples in flight and memory budget are the
  * first graph's; lean looks (KC_OPT_LEAN_LOOKS) are taken only when every
- * graph of the batch takes them (results do not depend on either).  The batch owns its workspace (slots sized for the largest
- * graph) and copies of the graphs' device array pointers: the graphs must
+ * graph of the batch takes them (results do not depend on either).  One kernel
+ * samples all jobs: a graph that only the chain sampler takes (see the options)
+ * puts every graph of its batch on that sampler, which is 3 to 5 times slower for
+ * small ones; keep such graphs in a batch of their own where that matters.  The
+ * batch owns its workspace (slots sized for the largest graph) and copies of the graphs' device array pointers: the graphs must
  * outlive the batch and must not be updated (kc_apply_updates, kc_set_tau0)
  * while it exists.
  */

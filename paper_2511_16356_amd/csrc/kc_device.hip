@@ -9,10 +9,13 @@
 //
 //   the frontier sampler (kc_frontier.hip), one workgroup per sample, for graphs
 //   whose words fit LDS and for larger ones with short walks;
-//   the chain sampler (here), one wavefront per sample, for large sparse graphs:
-//   up to 64 lanes drive loop-erased walks ("chains") of the same sample at once;
-//   a chain whose arrow lands on another chain's path is parked in an LDS table
-//   and its lane moves on.
+//   the chain sampler (here), one wavefront per sample, for large graphs with long
+//   walks, and for calls with many samples of a graph that leaves few workgroups of
+//   the other in flight: up to 64 lanes drive loop-erased walks ("chains") of the
+//   same sample at once; a chain whose arrow lands on another chain's path is parked
+//   in an LDS table and its lane moves on.
+//
+// Which one a call takes is kc_host::route_of.
 //
 // Every kernel takes sample after sample from a counter and evaluates f of each
 // tree where it was sampled (kc_tree.h); sum f and sum f^2 are exact, in 128-bit

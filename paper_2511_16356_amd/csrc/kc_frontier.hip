@@ -18,8 +18,10 @@
 // On graphs with short walks that leaves a few dozen rounds per tree, which
 // stream the arrows and touch no per-vertex state beyond one word and the draw
 // count; on small graphs the arrows are held in LDS, where a step of a walk is
-// one LDS read (large sparse graphs keep the chain sampler of kc_device.hip:
-// there the longest walk of each round would be paid in L2 round trips).
+// one LDS read (large graphs with long walks keep the chain sampler of
+// kc_device.hip: there the longest walk of each round would be paid in L2 round
+// trips; so do calls with many samples where the words leave a CU one or two
+// workgroups.  kc_host::route_of has the rule and both sides' times).
 
 #include <algorithm>
 #include <type_traits>

@@ -143,7 +143,7 @@ std::vector<int32_t> start_order_of(const std::vector<int32_t> &bfs, int kind) {
 }  // namespace
 
 int64_t kc_host::slot_bytes(const kc_graph *g, bool trav, bool fen) {
-    // sampler state (reused by the numbering's ord and grp), tasks and chain starts
+    // sampler state (reused by the tree's evaluation), tasks and chain starts
     int64_t b = kc::state_bytes(g->n) + 20 * (int64_t)kc::sampler_chains();
     if (trav) b += 16 * g->n;  // rec
     if (fen) b += 8 * (g->two_m + 2);

@@ -48,8 +48,8 @@ struct SlotDev {
     int64_t stride;  // vertices per slot (a batch: its largest graph's n)
 };
 
-// Bytes of one slot's state block: 20 bytes per vertex, the 4 of grp's last
-// entry, rounded up to 256 so that every slot's block starts 256-aligned.
+// Bytes of one slot's state block: 20 bytes per vertex and 4 more, rounded up to 256
+// so that every slot's block starts 256-aligned.
 __host__ __device__ inline int64_t state_bytes(int64_t stride) { return (20 * stride + 4 + 255) / 256 * 256; }
 
 // One graph's share of a batch launch (batch_kernel).

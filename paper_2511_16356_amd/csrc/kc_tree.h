@@ -38,10 +38,6 @@ __device__ __forceinline__ T afetch_or(T *p, T v) {
     return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 template <typename T>
-__device__ __forceinline__ T afetch_and(T *p, T v) {
-    return __hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
 __device__ __forceinline__ T afetch_xor(T *p, T v) {
     return __hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -848,7 +844,7 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
         extra[u] = 0;
     }
     // ---- the path sums.  A few thousand vertices climb as far as it takes, which writes the
-    // trunk of the tree; the others climb WALK steps at most, and those not done, once more
+    // trunk of the tree; the others climb SHORT steps at most, and those not done, once more
     constexpr int SEED = 4096, SHORT = 8;
     auto rec4 = [&](int v) __attribute__((always_inline)) { return rec_both(rec, v); };
     int64_t acc = 0;
