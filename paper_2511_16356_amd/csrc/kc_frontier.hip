@@ -578,8 +578,10 @@ __device__ __forceinline__ int64_t sample_global(const GraphDev &g, const Fronti
 extern __shared__ __align__(16) uint32_t dyn_words[];
 
 // One sample through the whole path, as process_one of the chain sampler.
-// (ROUTES: the routes compiled in, one bit each; a launch over one graph has one.)
-template <int T, int ROUTES>
+// (ROUTES: the routes compiled in, one bit each; a launch over one graph has one.
+// TREES: the trees go to the caller, else they are evaluated here; kernels of their own,
+// so that the evaluation's registers do not weigh on a launch that has none.)
+template <int T, int ROUTES, bool TREES>
 __device__ __forceinline__ bool process_frontier(const GraphDev &g, const SlotPtrs &sp, FrontierLds<T> &lds,
                                                  uint32_t *dyn, const RunParams &rp, int route, int64_t fen_len,
                                                  int idx, uint64_t s) {
@@ -596,7 +598,7 @@ __device__ __forceinline__ bool process_frontier(const GraphDev &g, const SlotPt
     auto parent_of = [&](int v) __attribute__((always_inline)) {
         return (int32_t)(in_lds ? dyn[v] & L_MASK : aload(&ws.word[v]) & G_MASK);
     };
-    if (rp.mode == RUN_SAMPLE) {
+    if constexpr (TREES) {
         const size_t n = (size_t)g.n;
         int32_t *po = rp.parents_out + (size_t)idx * n;
         uint32_t *co = rp.cnt_out ? rp.cnt_out + (size_t)idx * n : nullptr;
@@ -616,7 +618,7 @@ __device__ __forceinline__ bool process_frontier(const GraphDev &g, const SlotPt
 }
 
 // As persistent_kernel and batch_kernel of the chain sampler.
-template <int T, int ROUTE>
+template <int T, int ROUTE, bool TREES>
 __global__ void __launch_bounds__(T, FT_WAVES) frontier_kernel(GraphDev g, SlotDev sd, RunParams rp) {
     __shared__ FrontierLds<T> lds;
     const SlotPtrs sp = slot_ptrs(sd, (size_t)g.n);
@@ -624,8 +626,8 @@ __global__ void __launch_bounds__(T, FT_WAVES) frontier_kernel(GraphDev g, SlotD
     while (true) {
         const int idx = next_item<T>(rp.ctl, lds.tree);
         if (idx >= rp.count) break;
-        if (!process_frontier<T, 1 << ROUTE>(g, sp, lds, dyn_words, rp, ROUTE, sd.fen_len, idx,
-                                             (uint64_t)(rp.first + idx)))
+        if (!process_frontier<T, 1 << ROUTE, TREES>(g, sp, lds, dyn_words, rp, ROUTE, sd.fen_len, idx,
+                                                    (uint64_t)(rp.first + idx)))
             break;
         ++done;
         if (rp.progress && threadIdx.x == 0)
@@ -655,7 +657,9 @@ __global__ void __launch_bounds__(T, FT_WAVES) frontier_batch_kernel(BatchArgs a
         rp.steps_out = a.steps;
         rp.iters_out = a.iters;
         const uint64_t s = (uint64_t)(job.first + L * (int64_t)(a.base[j + 1] - a.base[j]) + (idx - a.base[j]));
-        if (!process_frontier<T, 1 << ROUTE_LDS | 1 << ROUTE_GLOBAL>(job.g, sp, lds, dyn_words, rp, job.route, job.g.two_m + 2, idx, s)) break;
+        if (!process_frontier<T, 1 << ROUTE_LDS | 1 << ROUTE_GLOBAL, false>(job.g, sp, lds, dyn_words, rp, job.route,
+                                                                            job.g.two_m + 2, idx, s))
+            break;
     }
 }
 
@@ -722,17 +726,22 @@ hipError_t allow_lds(K kernel, size_t lds) {
 
 }  // namespace
 
-hipError_t launch_frontier(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
-    if (rp.route == ROUTE_GLOBAL) {
-        const size_t lds = dyn_lds<GT>(rp.route, g.n, rp.traversal);
-        hipLaunchKernelGGL((frontier_kernel<GT, ROUTE_GLOBAL>), dim3(slots), dim3(GT), lds, stream, g, s, rp);
-        return hipGetLastError();
-    }
-    const size_t lds = dyn_lds<LT>(rp.route, g.n, rp.traversal);
-    const hipError_t e = allow_lds(frontier_kernel<LT, ROUTE_LDS>, lds);
+template <int T, int ROUTE, bool TREES>
+static hipError_t launch_frontier_of(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots,
+                                     hipStream_t stream) {
+    const size_t lds = dyn_lds<T>(ROUTE, g.n, rp.traversal);
+    const hipError_t e = allow_lds(frontier_kernel<T, ROUTE, TREES>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((frontier_kernel<LT, ROUTE_LDS>), dim3(slots), dim3(LT), lds, stream, g, s, rp);
+    hipLaunchKernelGGL((frontier_kernel<T, ROUTE, TREES>), dim3(slots), dim3(T), lds, stream, g, s, rp);
     return hipGetLastError();
+}
+hipError_t launch_frontier(const GraphDev &g, const SlotDev &s, const RunParams &rp, int slots, hipStream_t stream) {
+    const bool trees = rp.mode == RUN_SAMPLE;
+    if (rp.route == ROUTE_GLOBAL)
+        return trees ? launch_frontier_of<GT, ROUTE_GLOBAL, true>(g, s, rp, slots, stream)
+                     : launch_frontier_of<GT, ROUTE_GLOBAL, false>(g, s, rp, slots, stream);
+    return trees ? launch_frontier_of<LT, ROUTE_LDS, true>(g, s, rp, slots, stream)
+                 : launch_frontier_of<LT, ROUTE_LDS, false>(g, s, rp, slots, stream);
 }
 // A batch's workgroups have the threads its largest graph takes, and the most dynamic LDS of
 // its jobs with that many threads (grids of 1,024 take 28 KB with 256; the 40 KB of 512 threads
@@ -776,8 +785,8 @@ hipError_t launch_tree(const GraphDev &g, const SlotDev &s, const RunParams &rp,
                          : launch_trees_of<WAVE>(g, s, rp, slots, stream);
 }
 int frontier_blocks_per_cu(int route, int64_t n, int traversal) {
-    return route == ROUTE_GLOBAL ? resident(frontier_kernel<GT, ROUTE_GLOBAL>, GT, dyn_lds<GT>(route, n, traversal))
-                                 : resident(frontier_kernel<LT, ROUTE_LDS>, LT, dyn_lds<LT>(route, n, traversal));
+    return route == ROUTE_GLOBAL ? resident(frontier_kernel<GT, ROUTE_GLOBAL, false>, GT, dyn_lds<GT>(route, n, traversal))
+                                 : resident(frontier_kernel<LT, ROUTE_LDS, false>, LT, dyn_lds<LT>(route, n, traversal));
 }
 int frontier_batch_blocks_per_cu(const BatchArgs &a) {
     return batch_is_global(a) ? resident(frontier_batch_kernel<GT>, GT, batch_lds<GT>(a))
