@@ -225,7 +225,9 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 // and a root that holds at least 16 / n of all edge ends, so that a walk returns to it
 // every 2m / deg(root) <= n / 16 steps.  Power laws (exponent 2 to 3, largest degree
 // 300 to 2,000, 33,000 to 300,000 vertices) and preferential attachment return every
-// n / 170 to n / 27 steps: 1.3 to 10 times the chains' speed at 1 to 2,560 trees.  Random
+// n / 170 to n / 27 steps: 1.3 to 10 times the chains' speed at 1 to 2,560 trees.  A random
+// graph of 40,000 with one vertex of larger degree, a return every n / 7.5, n / 14, n / 34 steps:
+// 0.81, 1.0 and 1.33 times with 2,560 trees; of 100,000, every n / 17: 1.14 times.  Random
 // graphs of degree 8 to 76 and two of them joined by one edge return every 0.35 n to
 // 0.7 n steps: 0.28 to 1.3 times at 64 trees and more (100,000 vertices of degree 20,
 // 2,560 trees: 1,160 ms against 348 ms for the chains; two halves of 50,000, 512 trees:

@@ -4,8 +4,8 @@
 //
 // The tree code runs in a workgroup of T threads (64: one wavefront) that owns
 // one tree.  Threads exchange data through global memory by workgroup-scope
-// relaxed atomics (L2-coherent on gfx950), ordered by the workgroup barriers; one
-// 16-byte load of a record still being completed is explained where it stands.
+// relaxed atomics (L2-coherent on gfx950), ordered by the workgroup barriers; for
+// the 16-byte loads of records still being completed see pin().
 #pragma once
 
 #include <type_traits>
@@ -136,14 +136,15 @@ struct SlotPtrs {
 __device__ __forceinline__ int32_t rec_parent(const uint64_t *rec, int v) {
     return (int32_t)(uint32_t)aload(&rec[2 * (size_t)v + 1]);
 }
-// Both words of a record that other threads may be completing, each by one 8-byte store from
-// "unknown" to the only value it can have: a word is read unknown or complete, and an old
-// one only makes a climb longer.  (f_paths: 512 trees of a power-law graph of 289,721 vertices
-// 13.9 ms with one 16-byte load, 13.0 with the two.)
-__device__ __forceinline__ int4 rec_both(const uint64_t *rec, int v) {
-    const uint64_t a = aload(&rec[2 * (size_t)v]), b = aload(&rec[2 * (size_t)v + 1]);
-    return make_int4((int)(uint32_t)a, (int)(a >> 32), (int)(uint32_t)b, (int)(b >> 32));
-}
+// A record that other threads may be completing is read by one 16-byte load, then pinned:
+// the compiler may not load parts of it again or apart, so that what is tested is what is
+// used.  Each of its two words is written by one 8-byte store, from "unknown" to the only
+// value it can have, and a half of an aligned 16-byte load is read whole: a word is unknown
+// or complete, and an old one only makes a climb longer.  Evaluating 512 trees of a power-law
+// graph of 289,721 vertices took 14.1 ms with unpinned loads, 13.2 with an atomic load for each
+// word, 12.6 so; 1,024 of a road-like graph of 44,780 17.4, 18.4 and 17.4.
+__device__ __forceinline__ void pin(int4 &q) { asm("" : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w)); }
+
 // The numbering of a vertex once it is complete: tin, vol and tree parent.
 struct TNum {
     uint32_t tin, vol;
@@ -369,12 +370,7 @@ __device__ bool tree_numbering(const GraphDev &g, const SlotPtrs &sp, TreeShared
     __syncthreads();
     // top-down
     constexpr int SEED = 4096, SHORT = 8;
-    // vol, tin + 1, parent, offset: of these tin is still being written, in one 8-byte store with
-    // vol, which does not change.  One 16-byte load, each half of it whole; the pin below keeps it
-    // one, so that what is tested is what is used.  (1,024 trees of a road-like graph of 44,780
-    // vertices: 17.4 ms, 18.4 with a load for each word)
-    const int4 *rec4 = reinterpret_cast<const int4 *>(sp.rec);
-    auto pin = [](int4 &q) __attribute__((always_inline)) { asm("" : "+v"(q.x), "+v"(q.y), "+v"(q.z), "+v"(q.w)); };
+    const int4 *rec4 = reinterpret_cast<const int4 *>(sp.rec);  // vol, tin + 1, parent, offset
     auto climb = [&](auto wu, auto is_short, int at, int count, auto vertex) __attribute__((always_inline)) {
         constexpr int WU = decltype(wu)::value;
         constexpr bool CUT = decltype(is_short)::value;
@@ -846,7 +842,7 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
     // ---- the path sums.  A few thousand vertices climb as far as it takes, which writes the
     // trunk of the tree; the others climb SHORT steps at most, and those not done, once more
     constexpr int SEED = 4096, SHORT = 8;
-    auto rec4 = [&](int v) __attribute__((always_inline)) { return rec_both(rec, v); };
+    const int4 *rec4 = reinterpret_cast<const int4 *>(rec);
     int64_t acc = 0;
     auto climb = [&](auto wu, auto is_short, int at, int count, auto vertex) __attribute__((always_inline)) {
         constexpr int WU = decltype(wu)::value;
@@ -871,9 +867,10 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
         do {
             any = 0;
 #pragma unroll
-            for (int k = 0; k < WU; ++k) r[k] = rec4(x[k]);
+            for (int k = 0; k < WU; ++k) r[k] = rec4[x[k]];
 #pragma unroll
             for (int k = 0; k < WU; ++k) {
+                pin(r[k]);
                 const uint32_t node = (uint32_t)r[k].x;
                 const uint32_t c = node & P_FWD ? (uint32_t)r[k].y : 0u;
                 if (step == 0) {
@@ -911,15 +908,18 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
                 bool look = l == (uint32_t)v[k];
                 for (int y = (int)up[k]; y != x[k];) {
                     if (look) {
-                        int4 q = rec4(y);
+                        int4 q = rec4[y];
+                        pin(q);
                         for (int a = y; (l = (uint32_t)a, !((uint32_t)q.x & P_MARK));) {
                             if ((uint32_t)q.w != P_NONE) { l = (uint32_t)q.z; break; }
                             a = (int)((uint32_t)q.x & P_PAR);
-                            q = rec4(a);
+                            q = rec4[a];
+                            pin(q);
                         }
                         look = false;
                     }
-                    const int4 q = rec4(y);
+                    int4 q = rec4[y];
+                    pin(q);
                     astore(&rec[2 * (size_t)y + 1], (uint64_t)rest << 32 | l);
                     rest -= (uint32_t)q.x & P_FWD ? (uint32_t)q.y : 0u;
                     look = l == (uint32_t)y;
@@ -940,7 +940,7 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
     __syncthreads();
     if (sh.bad) return false;  // (uniform)
     if (n_mark > 0) {
-        // ---- the vertices with a tau0 ancestor in the map
+        // ---- the vertices with a tau0 ancestor in the map (the records are complete)
         for (int b = 0; b < n; b += T) {
             const int u = b + tid;
             bool hit = false;
@@ -962,7 +962,7 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
         const int n_user = sh.n_user;
         for (int i = tid; i < n_user; i += T) {
             const int u = user[i];
-            const int4 ru = rec4(u);
+            const int4 ru = rec4[u];
             const int64_t d = (int64_t)(uint32_t)ru.y;
             // the vertices whose terms u has, if they are tau ancestors of u
             uint32_t plus[D], minus[D];
@@ -972,7 +972,7 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
             for (int l = 0; l < D; ++l) z[l] = g.anc0[(size_t)l * n + u];
             uint32_t node[D];
 #pragma unroll
-            for (int l = 0; l < D; ++l) node[l] = z[l] >= 0 ? (uint32_t)rec4(z[l]).x : 0u;
+            for (int l = 0; l < D; ++l) node[l] = z[l] >= 0 ? (uint32_t)rec4[z[l]].x : 0u;
 #pragma unroll
             for (int l = 0; l < D; ++l) {
                 plus[l] = z[l] >= 0 && (node[l] & P_FWD) ? (uint32_t)z[l] : P_NONE;
@@ -1001,7 +1001,7 @@ __device__ bool f_paths(const GraphDev &g, const SlotPtrs &sp, PathShared &sh, u
             }
             __syncthreads();
             for (int w = tid; w < n; w += T) {
-                const int4 r = rec4(w);
+                const int4 r = rec4[w];
                 if ((uint32_t)r.z != P_NONE) acc -= (int64_t)(uint32_t)r.y * extra_sum[r.z];
             }
         }
