@@ -91,7 +91,6 @@ kc_status kc_batch_create(kc_graph *const *graphs, int32_t k, const uint64_t *se
         kc::RunParams rp{};
         fill_run_options(g, rp);
         kc::BatchJob &job = a.job[j];
-        job.g = graph_dev(g);
         job.seed = seeds[j];
         job.first = firsts[j];
         job.iter_cap = rp.iter_cap;
@@ -116,6 +115,9 @@ kc_status kc_batch_create(kc_graph *const *graphs, int32_t k, const uint64_t *se
     bool chains = true;
     for (int32_t j = 0; j < k; ++j) chains = chains && route_of(graphs[j], total, fit) == kc::ROUTE_CHAINS;
     for (int32_t j = 0; chains && j < k; ++j) a.job[j].route = kc::ROUTE_CHAINS;
+    chains = !kc::batch_is_frontier(a);
+    for (int32_t j = 0; j < k; ++j)
+        a.job[j].g = graph_dev(graphs[j], kc::RUN_ESTIMATE, chains ? (int)kc::ROUTE_CHAINS : (int)a.job[j].route);
     const int want = graphs[0]->slots_opt > 0 ? graphs[0]->slots_opt : resident_slots(blocks_per_cu(a, b->chains));
     int slots = (int)std::min<int64_t>(std::min<int64_t>(want, total), fit);
     slots = balanced_slots(slots, total);

@@ -221,17 +221,18 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 // sampler; 512 trees: 5,690 against 1,596 ms).
 //
 // Walks are short where they soon meet the root: no vertex far from it (the depth of
-// a breadth-first search, whatever the reference tree), a mean degree of at least 8,
-// and a root that holds at least 16 / n of all edge ends, so that a walk returns to it
-// every 2m / deg(root) <= n / 16 steps.  Power laws (exponent 2 to 3, largest degree
+// a breadth-first search, whatever the reference tree) and the root holds at least
+// 16 / n of all edge ends, so that a walk returns to it every 2m / deg(root) <= n / 16
+// steps, whatever the mean degree (4.4, exponent 2.2, 67,111 vertices, 512 trees: 20 -> 9.6
+// ms; preferential attachment of degree 6, 100,000 vertices: 29 -> 18 ms).  Power laws (exponent 2 to 3, largest degree
 // 300 to 2,000, 33,000 to 300,000 vertices) and preferential attachment return every
 // n / 170 to n / 27 steps: 1.3 to 10 times the chains' speed at 1 to 2,560 trees.  A random
-// graph of 40,000 with one vertex of larger degree, a return every n / 7.5, n / 14, n / 34 steps:
-// 0.81, 1.0 and 1.33 times with 2,560 trees; of 100,000, every n / 17: 1.14 times.  Random
-// graphs of degree 8 to 76 and two of them joined by one edge return every 0.35 n to
-// 0.7 n steps: 0.28 to 1.3 times at 64 trees and more (100,000 vertices of degree 20,
-// 2,560 trees: 1,160 ms against 348 ms for the chains; two halves of 50,000, 512 trees:
-// 11.1 against 6.5 s).
+// graph with one vertex of larger degree, chains against this with 2,560 trees: of 40,000
+// vertices 74 / 97 ms (a return every n / 7.5 steps), 62 / 66 (n / 14), 56 / 43 (n / 34); of
+// 100,000 151 / 204 (n / 17), 147 / 153 (n / 34), 145 / 117 (n / 84), with one tree 32 / 10, 29 / 10,
+// 29 / 6.5.  Random graphs of degree 8 to 76 and two of them joined by one edge return every
+// 0.35 n to 0.7 n steps (100,000 vertices of degree 20, 512 trees: 208 / 453 ms; two halves of
+// 50,000, 64 trees: 2.6 / 4.2 s).
 //
 // A road-like graph of 44,780 would gain (512 trees: 3,199 against 6,145 ms), a grid
 // thinned to the same degree lose (40,000 vertices, 8 trees: 1,128 against 583 ms);
@@ -252,7 +253,7 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 int kc_host::route_of(const kc_graph *g, int64_t count, int slots) {
     const int64_t root_degree = g->h_off[(size_t)g->root + 1] - g->h_off[(size_t)g->root];
     const bool meets_root = g->bfs_depth <= 12 && 16 * g->two_m <= g->n * root_degree;
-    if (g->n > kc::LDS_MAX_N) return meets_root && g->two_m >= 8 * g->n ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
+    if (g->n > kc::LDS_MAX_N) return meets_root ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
     if (meets_root || slots < std::min<int64_t>(count, 2048) || count <= 7 * resident_slots(1)) return kc::ROUTE_LDS;
     const bool lattice = 2 * g->two_m >= 7 * g->n && g->bfs_depth > 12;
     const int per_cu = kc::frontier_blocks_per_cu(kc::ROUTE_LDS, g->n, g->traversal);
@@ -299,8 +300,24 @@ int kc_host::balanced_slots(int slots, int64_t count) {
     return (int)((count + waves - 1) / waves);
 }
 
-// The graph's device arrays as the kernels see them.
-kc::GraphDev kc_host::graph_dev(const kc_graph *g) {
+// On a shallow tau0 f is evaluated by path sums, which look at the vertices with terms of
+// their own one by one (2% of them on power laws, 4% on random graphs of degree 76, 15% on
+// preferential attachment of degree 6, 40% and more on random graphs of degree up to 12), or
+// from volumes and a numbering, which do not depend on them.  Path sums against the numbering,
+// 512 trees of 100,000 vertices: power law 5.1 / 11.4 ms (5% of the vertices), preferential
+// attachment of degree 6 17.4 / 19.7 (15%), of degree 4 25.5 / 20.4 (30%), one large vertex in a
+// random graph of degree 6 33.9 / 23.5 (47%), random graph of degree 12 16.8 / 15.8 (51%, and
+// 3.5 / 4.7 at 33,000 vertices and 44%), of degree 8 33.8 / 16.2 (90%).  Small trees always gain
+// (3,000 vertices of degree 6, 84%, 2,560 trees: 1.59 / 2.40 ms).  One wavefront per tree takes
+// them one after the other: estimates of 512 trees by the chains, 217 / 123 ms (degree 8, 90%),
+// 219 / 210 (degree 20, 26%), but 95 / 97 (degree 76, 4%).
+bool kc_host::path_sums(const kc_graph *g, bool one_wavefront) {
+    if (g->n <= 8000) return true;
+    return g->term_share <= (one_wavefront ? 0.1 : g->two_m >= 8 * g->n ? 0.5 : 0.25);
+}
+
+// The graph's device arrays as the kernels of a launch see them.
+kc::GraphDev kc_host::graph_dev(const kc_graph *g, int mode, int route) {
     kc::GraphDev gd;
     gd.n = (int32_t)g->n;
     gd.root = g->root;
@@ -314,9 +331,10 @@ kc::GraphDev kc_host::graph_dev(const kc_graph *g) {
     gd.eoff = g->d_eoff;
     gd.elist = g->d_elist;
     gd.vrec = g->d_vrec;
-    gd.int0 = g->d_int0;
-    gd.anc0 = g->d_anc0;
-    gd.anc_depth = g->anc_depth;
+    const bool paths = path_sums(g, (mode == kc::RUN_SAMPLE || mode == kc::RUN_ESTIMATE) && route == kc::ROUTE_CHAINS);
+    gd.int0 = paths ? g->d_int0 : nullptr;
+    gd.anc0 = paths ? g->d_anc0 : nullptr;
+    gd.anc_depth = paths ? g->anc_depth : 0;
     return gd;
 }
 
@@ -339,7 +357,7 @@ void kc_host::fill_run_options(const kc_graph *g, kc::RunParams &rp) {
 kc_status kc_host::launch_checked(kc_graph *g, const kc::SlotDev &sd, const kc::RunParams &rp, int slots,
                          hipStream_t stream) {
     HIP_TRY(kc::launch_reset_ctl(g->d_ctl, stream));
-    HIP_TRY(kc::launch_persistent(graph_dev(g), sd, rp, g->chains, slots, stream));
+    HIP_TRY(kc::launch_persistent(graph_dev(g, rp.mode, rp.route), sd, rp, g->chains, slots, stream));
     int32_t ctl[4] = {0, 0, 0, 0};
     HIP_TRY(hipMemcpyAsync(ctl, g->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
@@ -631,6 +649,17 @@ kc_status prepare_graph(const std::vector<int64_t> &off, const std::vector<int32
             }
         }
     }
+    // vertices expected to have a tau0 ancestor x whose tau0 edge is in a tree (it is with
+    // probability R(x, p0(x)), at most about 1/d(x) + 1/d(p0(x))): those whose terms the path
+    // sums look at one by one
+    double terms = 0.0;
+    for (int64_t x = 0; x < n; ++x) {
+        if (x == root || out0[(size_t)x] == in0[(size_t)x]) continue;
+        const int64_t z = p0[(size_t)x];
+        const double r = 1.0 / (double)(off[(size_t)x + 1] - off[(size_t)x]) + 1.0 / (double)(off[(size_t)z + 1] - off[(size_t)z]);
+        terms += (double)(out0[(size_t)x] - in0[(size_t)x]) * std::min(r, 1.0);
+    }
+    pg->term_share = terms / (double)n;
     // per-vertex graph record for the sampler: offset, degree, first six neighbours
     std::vector<int32_t> &vrec = pg->vrec;
     vrec.assign((size_t)n * 8, -1);
@@ -675,6 +704,7 @@ kc_status rebuild_graph(kc_graph *g, int32_t root, hipStream_t stream, PreparedG
     g->root = pg.root;
     g->depth0 = pg.depth0;
     g->bfs_depth = pg.bfs_depth;
+    g->term_share = pg.term_share;
     g->nblk = pg.nblk;
     g->max_degree = 0;
     for (int64_t v = 0; v < n; ++v)

@@ -14,6 +14,7 @@
 struct PreparedGraph {
     int32_t root = -1, depth0 = 0, nblk = 0, anc_depth = 0;
     int32_t bfs_depth = 0;  // of the breadth-first search from the root, whatever tau0
+    double term_share = 0.0;  // expected share of vertices with terms of their own in the path sums
     std::vector<int32_t> order, p0, pre0, out0, eoff, elist, vrec, anc0;
     std::vector<uint32_t> int0;
 };
@@ -22,6 +23,7 @@ struct kc_graph {
     int64_t n = 0, two_m = 0;
     int32_t root = -1, depth0 = 0, max_degree = 0;
     int32_t bfs_depth = 0;  // largest distance from the root
+    double term_share = 0.0;  // as PreparedGraph's
     int32_t traversal = KC_TRAV_WALK;
     int32_t walkers = 64;
     int32_t chains = 1024;
@@ -109,7 +111,9 @@ int64_t workspace_budget(const kc_graph *g, size_t free_b);
 // Slots that split `count` samples into equal waves (at most `slots`).
 int balanced_slots(int slots, int64_t count);
 // The graph's device arrays as the kernels see them.
-kc::GraphDev graph_dev(const kc_graph *g);
+kc::GraphDev graph_dev(const kc_graph *g, int mode, int route);
+// Whether f is evaluated by path sums where tau0 is shallow enough for them.
+bool path_sums(const kc_graph *g, bool one_wavefront);
 // The options of g that every launch carries (walkers, traversal, step cap, status word).
 void fill_run_options(const kc_graph *g, kc::RunParams &rp);
 // Launch the persistent kernel on a prepared workspace and check the status it reports.

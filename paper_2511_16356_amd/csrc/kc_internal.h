@@ -2,6 +2,7 @@
 // and its kernels (kc_device.hip).  Not part of the public ABI.
 #pragma once
 
+#include <cstddef>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,6 +28,7 @@ struct GraphDev {
                           //       (i+1)-th ancestor of v, -1 past the root; null if tau0 is deep
     int32_t anc_depth;    //       levels in anc0 (4 or 8), 0 without the table
 };
+static_assert(offsetof(GraphDev, anc_depth) == 104, "the launch tests read it there");
 
 // Per-slot workspace: one slot = one sample in flight = one workgroup.
 //

@@ -18,6 +18,7 @@ struct Launch {
     uint32_t grid, block;
     size_t lds;
     void *out;  // reduce_kernel: where it writes
+    int levels; // kernels over one graph: levels of its table of tau0 ancestors
 };
 std::map<const void *, std::string> &names() {
     static std::map<const void *, std::string> m;
@@ -47,6 +48,7 @@ void stub_set(size_t free_b, int blocks_per_cu) { free_bytes = free_b; per_cu = 
 int stub_launches() { return (int)launches.size(); }
 const char *stub_name(int i) { return launches[(size_t)i].name.c_str(); }
 int stub_grid(int i) { return (int)launches[(size_t)i].grid; }
+int stub_levels(int i) { return launches[(size_t)i].levels; }
 int stub_block(int i) { return (int)launches[(size_t)i].block; }
 size_t stub_lds(int i) { return launches[(size_t)i].lds; }
 size_t stub_limit(const char *kernel) {  // the dynamic LDS it may take (of one whose name holds this)
@@ -77,7 +79,9 @@ int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *lds, void **s) {
 }
 static int last_error = 0;
 int hipLaunchKernel(const void *f, Dim3 g, Dim3 b, void **args, size_t lds, void *) {
-    Launch l{names()[f], g.x, b.x, lds, nullptr};
+    Launch l{names()[f], g.x, b.x, lds, nullptr, -1};
+    for (const char *k : {"tree_kernel", "frontier_kernel", "persistent_kernel"})  // GraphDev comes first, its last word
+        if (l.name.find(k) != std::string::npos) memcpy(&l.levels, static_cast<char *>(args[0]) + 104, 4);
     if (l.name.find("reduce_kernel") != std::string::npos) l.out = *static_cast<void **>(args[4]);
     launches.push_back(l);
     if (lds > (64u << 10) && lds > lds_limit[f]) last_error = 1;

@@ -281,3 +281,29 @@ def test_step_limit_counts_two_frontier_rounds_as_one(kc, gen, name):
         with pytest.raises(kc.KcError) as ei:
             G.estimate(3, 5, 1)
         assert ei.value.status == 6
+
+
+def test_path_sums_by_one_wavefront_on_a_power_law(kc, oracle_lib, gen):
+    """The chains sample a power law whose root is a leaf; few vertices have terms of their own, so
+    its one wavefront takes path sums, with more vertices than its map has bits."""
+    g = gen.chung_lu(72000, 2.2, 10.0, 1300.0, seed=1)
+    root = int(np.argmin(g.degrees))
+    assert g.n > 65536
+    P = oracle_lib.prepare_graph(g, root=root)
+    with kc.Graph.from_graph(g, root=root) as G:
+        assert G.info["depth0"] <= 8
+        samples_match(G, oracle_lib, P, 3, 70, 3)
+        assert on_chains(kc, G, 3, 70, 3)
+
+
+@pytest.mark.parametrize("kind,n", [("ba2", 12000), ("random", 9001), ("ba2", 40000), ("hub", 40000)])
+def test_numbering_on_a_shallow_tau0(kc, oracle_lib, gen, kind, n):
+    """Graphs many of whose vertices have terms of their own: estimates and held trees."""
+    import torch
+    g = gen.barabasi_albert(n, 2, 1) if kind == "ba2" else random_graph(gen, n, 6, hub=3000 if kind == "hub" else 0)
+    P = oracle_lib.prepare_graph(g)
+    with kc.Graph.from_graph(g) as G:
+        samples_match(G, oracle_lib, P, 5, 7, 4)
+        par, _, _ = oracle_lib.sample(P, seed=5, s0=7, count=4, threads=8)
+        f, _ = oracle_lib.estimate_f(P, seed=5, s0=7, count=4, threads=8)
+        assert np.array_equal(G.evaluate_trees(torch.from_numpy(par).cuda()).cpu().numpy(), f)

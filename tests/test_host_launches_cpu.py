@@ -32,7 +32,7 @@ def graph(g, root=-1):
     return h
 def launches(clear=True):
     out = [dict(name=stub.stub_name(i).decode(), grid=stub.stub_grid(i), block=stub.stub_block(i), lds=stub.stub_lds(i),
-                out=stub.stub_out(i)) for i in range(stub.stub_launches())]
+                out=stub.stub_out(i), levels=stub.stub_levels(i)) for i in range(stub.stub_launches())]
     if clear: stub.stub_clear()
     return out
 def estimate(h, count):
@@ -259,3 +259,31 @@ def test_autotune_tries_what_the_sampler_has(run, tmp_path):
         print(json.dumps(out))
     """ % str(tmp_path / "tune-"))
     assert r == [["lds", 3, 1, 0, False], ["chains", 5, 1, 1, True]]
+
+
+def test_path_sums_where_few_vertices_have_terms(run):
+    """A shallow tau0's table goes to the kernels where the path sums are the faster evaluation."""
+    r = run(ROUTE_GRAPHS + """
+def evaluate(h, n):
+    par, f = np.zeros(n, np.int32), np.zeros(1, np.int64)
+    stub.stub_clear()
+    assert lib.kc_evaluate_trees(h, par.ctypes.data, 1, f.ctypes.data, None) == 0
+    return [l["levels"] for l in launches() if "tree_kernel" in l["name"]][0]
+out = {}
+for name, g in (("small", random_graph(3000, 8)), ("deg8", random_graph(9000, 8)), ("deg12", random_graph(33000, 12)),
+                ("social", gen.chung_lu(20000, 2.2, 10.0, 700.0, seed=0)), ("star", gen.star(40000)),
+                ("ba2", gen.barabasi_albert(20000, 2, 1))):
+    h = graph(g)
+    out[name] = [evaluate(h, g.n) > 0, sampler(estimate(h, 4)[1])["levels"] > 0]
+print(json.dumps(out))
+""")
+    assert r == {"small": [True, True], "deg8": [False, False], "deg12": [True, False], "social": [True, True],
+                 "star": [True, True], "ba2": [False, False]}
+
+
+def test_sparse_graphs_with_a_large_root_take_the_frontier_sampler(run):
+    r = run("""
+        print(json.dumps([kind(estimate(graph(g), 64)[1]) for g in (gen.barabasi_albert(40000, 2, 1), gen.star(40000),
+                          gen.chung_lu(60000, 2.2, 4.0, 2000.0, seed=0))]))
+    """)
+    assert r == ["global", "global", "global"]
