@@ -113,7 +113,8 @@ enum {
                               it claims has its arrow word and graph record read in the next
                               round (fewer lines where most looks meet the tree, one more
                               round per claim): 0 = when the mean degree is at least 8
-                              (default), 1 = off, 2 = on.  Results do not depend on it. */
+                              and the root holds at least 16/n of the edge ends (default),
+                              1 = off, 2 = on.  Results do not depend on it. */
 };
 
 /* Sample maintenance of a resident set (section 4). */

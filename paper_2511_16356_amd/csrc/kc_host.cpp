@@ -210,6 +210,12 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 
 }  // namespace
 
+// Whether walks soon meet the root (see route_of).
+bool kc_host::meets_root(const kc_graph *g) {
+    const int64_t root_degree = g->h_off[(size_t)g->root + 1] - g->h_off[(size_t)g->root];
+    return g->bfs_depth <= 12 && 16 * g->two_m <= g->n * root_degree;
+}
+
 // The frontier sampler takes every graph whose words fit a CU's LDS: a step of a
 // walk is an LDS read there, and an L2 round trip in the chain sampler (2,000 trees
 // of the 32 x 32 grid: 10.9 against 50.9 ms; 256 of a road-like graph of 8,609
@@ -251,10 +257,8 @@ kc_status ensure_fbuf(kc_graph *g, int64_t count) {
 // vertices: 57 against 77 ms).  Hence the limits below, in full waves of trees; the chains need
 // most of their slots for it (2,048 of 2,560).
 int kc_host::route_of(const kc_graph *g, int64_t count, int slots) {
-    const int64_t root_degree = g->h_off[(size_t)g->root + 1] - g->h_off[(size_t)g->root];
-    const bool meets_root = g->bfs_depth <= 12 && 16 * g->two_m <= g->n * root_degree;
-    if (g->n > kc::LDS_MAX_N) return meets_root ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
-    if (meets_root || slots < std::min<int64_t>(count, 2048) || count <= 7 * resident_slots(1)) return kc::ROUTE_LDS;
+    if (g->n > kc::LDS_MAX_N) return meets_root(g) ? kc::ROUTE_GLOBAL : kc::ROUTE_CHAINS;
+    if (meets_root(g) || slots < std::min<int64_t>(count, 2048) || count <= 7 * resident_slots(1)) return kc::ROUTE_LDS;
     const bool lattice = 2 * g->two_m >= 7 * g->n && g->bfs_depth > 12;
     const int per_cu = kc::frontier_blocks_per_cu(kc::ROUTE_LDS, g->n, g->traversal);
     const int waves = per_cu == 1 ? (lattice ? 7 : 12) : per_cu == 2 && lattice ? 14 : 0;
@@ -343,9 +347,11 @@ kc::GraphDev kc_host::graph_dev(const kc_graph *g, int mode, int route) {
 void kc_host::fill_run_options(const kc_graph *g, kc::RunParams &rp) {
     rp.walkers = g->walkers;
     rp.traversal = g->traversal;
-    // lean looks pay where walks are short, so that most looks at a walk's next
-    // vertex meet the tree: by default when the mean degree is at least 8
-    rp.lean = g->lean_opt == 2 || (g->lean_opt == 0 && g->two_m >= 8 * g->n);
+    // lean looks pay where walks are short, so that most looks at a walk's next vertex meet
+    // the tree: by default when the mean degree is at least 8 and the root is large (2,560
+    // trees of a random graph of 100,000 vertices of degree 12, whose walks are long: 278 ms with
+    // them, 239 without; 512 of degree 40 220 and 190)
+    rp.lean = g->lean_opt == 2 || (g->lean_opt == 0 && g->two_m >= 8 * g->n && meets_root(g));
     rp.route = route_of(g);
     rp.iter_cap = g->step_limit > 0 ? g->step_limit : 1024 * g->n + (1 << 22);
     rp.ctl = g->d_ctl;

@@ -105,6 +105,7 @@ int default_slots(const kc_graph *g, int mode, int route, int64_t count);
 // Slots the workspace is sized for when the slots option is 0: the most any launch of up to
 // count samples on g takes.
 int workspace_slots(const kc_graph *g, int count);
+bool meets_root(const kc_graph *g);
 // How a launch of count samples with up to `slots` in flight samples g's trees (kc::Route).
 int route_of(const kc_graph *g, int64_t count = 1, int slots = 1 << 20);
 int64_t workspace_budget(const kc_graph *g, size_t free_b);

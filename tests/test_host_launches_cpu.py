@@ -287,3 +287,18 @@ def test_sparse_graphs_with_a_large_root_take_the_frontier_sampler(run):
                           gen.chung_lu(60000, 2.2, 4.0, 2000.0, seed=0))]))
     """)
     assert r == ["global", "global", "global"]
+
+
+def test_lean_looks_by_default_where_walks_are_short(run):
+    """The chain sampler's variants by their names' last argument; walks are long on a random graph,
+    and a lean graph with a large root takes the chains in a batch with a grid."""
+    r = run(ROUTE_GRAPHS + BATCH + """
+def lean(ls): return "Lb1E" in sampler(ls)["name"]
+h = graph(random_graph(33000, 12))
+out = [lean(estimate(h, 4)[1])]
+lib.kc_set_option(h, kc.KC_OPT_LEAN_LOOKS, 2)
+out.append(lean(estimate(h, 4)[1]))
+out.append(lean(batch((random_graph(33000, 12), 4), (hubs(33000, 10), 4))))
+print(json.dumps(out))
+""")
+    assert r == [False, True, False]
