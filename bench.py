@@ -41,9 +41,9 @@ LIB_SRC = os.path.join(ROOT, "paper_2511_16356_amd", "csrc")
 # counters were taken on (library_sha): other sources, or another workload,
 # sample count or seed, report traffic = null.
 MEASURED_TRAFFIC = {
-    "103e1fa892a0465ab627a6cac9441050e0a23ca470b5c9028a9e3c4601b84726": [
+    "cc2bf73a2e3050eb14e6ed4c7f6b1e0a59091aa4e51ee72ee996e48d2b8bd46c": [
         {"workload": "dense", "samples": 4096, "seed": 0,
-         "fetch_bytes": 9.0747e12, "write_bytes": 5.8886e11, "bytes": 9.6636e12},
+         "fetch_bytes": 9.0632e12, "write_bytes": 5.8890e11, "bytes": 9.6521e12},
     ],
     # earlier sources, kept for the record (records of the path sums loaded apart)
     "0dc1fa6282e0590f767e09a4940bc52cee6671ec4ac0c9022a4b7371a6a6af6b": [
